@@ -218,9 +218,10 @@ typedef struct {
     uint32_t wdtype;
 } eco_info;
 
-/* Per-kernel GPU time accumulated while ECO_RT_TIME_KERNELS is set.  REGROW runs
-   fused into the BIRTH_CLAIM launch and SENSE (the per-cell window channels for
-   the next step) into the COMPACT launch; both stay at zero. */
+/* Per-kernel GPU time accumulated while ECO_RT_TIME_KERNELS is set.  The cell pass
+   (REGROW, SENSE) runs in the BIRTH_CLAIM launch; both stay at zero.  BIRTH_COMMIT
+   (births) and COMPACT (live list and records) are two roles of one launch, made
+   apart in eager timed steps. */
 enum { ECO_K_FORWARD = 0, ECO_K_MOVE = 1, ECO_K_BIRTH_CLAIM = 2, ECO_K_BIRTH_SCAN = 3,
        ECO_K_BIRTH_COMMIT = 4, ECO_K_REGROW = 5, ECO_K_COMPACT = 6, ECO_K_SENSE = 7, ECO_K_COUNT = 8 };
 typedef struct {
@@ -238,12 +239,13 @@ typedef struct {
                                    ECO_RT_USE_GRAPH, event-record nodes around the policy kernel
                                    only, in a graph of the n steps of each eco_world_step call (one
                                    graph kept per n).  The call synchronises to read the times. */
-#define ECO_RT_SPLIT_STEP 8u    /* an object of one world with at most 8,192
-                                   slots and 16,384 cells, runs the step after the policy kernel
-                                   as one fused launch (timed as ECO_K_MOVE); this flag runs the
-                                   separate kernels instead.  Same integer state and statistics
-                                   either way (the trait moments to rounding). */
-/* The fused launch's limits: total slots and total cells of the object (each
+#define ECO_RT_SPLIT_STEP 8u    /* an object of one small world (at most 8,192 slots, and 12,288
+                                   cells or 8,192 in the ecology) runs the step after the policy
+                                   kernel as one single-block launch before the birth launch
+                                   (timed together as ECO_K_MOVE); this flag runs the separate
+                                   kernels instead.  Same integer state and statistics either way
+                                   (the trait moments to rounding). */
+/* The single-block launch's limits: the most slots and cells it could hold (each
  * world's ranges rounded up to 64). */
 #define ECO_SMALL_STEP_MAX_SLOTS 8192u
 #define ECO_SMALL_STEP_MAX_CELLS 16384u

@@ -22,6 +22,8 @@
 namespace eco {
 
 constexpr int kStatsRing = 1024;
+constexpr int ECO_MAX_WORLDS = 1024;   // worlds of one object at most
+constexpr uint32_t ECO_MAX_PARTS = 8192;   // blocks sharing children in one birth launch at most
 constexpr uint8_t kAlive = 1, kBirthClaim = 2, kBirthWon = 4;
 enum Action : uint8_t { REST = 0, TURN_L = 1, TURN_R = 2, FORWARD = 3, EAT = 4, REPRODUCE = 5, ATTACK = 6 };
 // The ecology's eight actions: EAT (4) takes energy, then water, biomass, reproduce;
@@ -51,16 +53,32 @@ struct WorldVar {
   uint64_t step;
   uint64_t uid_next;
   uint32_t n_live;      // live agents (the live list of this step)
-  uint32_t n_births;    // successful births of this step
-  uint32_t n_win;       // birth-claim winners of this step
+  uint32_t n_births;    // successful births of the last step whose traits its record still lacks
+  uint32_t n_win;       // birth-claim winners of this step (objects of several worlds, and the small-world kernel)
+  uint32_t n_free;      // free slots of this step after its deaths
+  uint32_t n0;          // survivors of the last step, and their trait mean and sum of squared deviations
   uint32_t pad;
+  double mean, m2;
 };
 
-// Counters accumulated by the kernels of one step (u64 atomics), finalised
-// into the eco_stats ring by the compaction kernel.
-struct StepCounters {
-  unsigned long long births, deaths, eaten, regrown, moves_ok, moves_blocked, births_blocked_cell,
-      births_blocked_capacity, resource_total;
+// Per-slot-tile counters of one step (index in the tile's row of part_slot).
+constexpr int kSlotPart = 16;    // u32 counters per slot tile
+constexpr int kCellPart = 4;     // u64 counters per cell tile
+enum { PC_HIST = 0, PC_MOVES_OK = 9, PC_MOVES_BLOCKED = 10, PC_EATEN = 11, PC_DEATHS = 12, PC_BB_CELL = 13,
+       PC_KILLED = 14, PC_CLAIMS = 15 };
+
+// What one world's statistics record needs besides its births: summed once the
+// moves, the birth claims and the cell pass of the step are done, completed by the
+// birth launch.  A birth moves energy, water and biomass from the parent to the
+// child, so the totals already hold; the trait moments are those of the survivors.
+struct StepDraft {
+  unsigned long long regrown, resource_total, water, biomass, hp;
+  long long energy;
+  double mean, m2;                // survivors' trait mean and sum of squared deviations from it
+  uint64_t step, uid_next;        // of the world before the step (the record advances them)
+  uint32_t n0;                    // survivors
+  uint32_t count[kSlotPart];      // PC_*
+  uint32_t pad;
 };
 
 // Weight layouts.  VPL = values per 16-byte block (FP32 4, BF16 8, FP8 16).
@@ -97,7 +115,7 @@ struct Layout {
 struct Dev {
   const WorldParams* wp;
   WorldVar* wv;
-  StepCounters* cnt;
+  StepDraft* draft;             // [n_worlds]
   eco_stats* ring;              // [n_worlds][kStatsRing]
   int32_t *pos, *energy, *age, *tgt;
   uint8_t *facing, *flags, *act, *sampled, *act_in;
@@ -123,7 +141,8 @@ struct Dev {
   uint8_t* store;               // [total_slots][sstride]
   uint8_t* master;              // [total_slots][mstride] or == store for FP32
   int32_t* live;                // [total_slots], per-world segments at slot_off
-  int32_t* bparent;             // [total_slots] birth winners (local slots) by rank
+  int32_t* bparent;             // [total_slots] birth winners: of each slot tile its winners' places in the tile,
+                                // from the tile's first slot on (the fused small-world step: local slots by rank)
   int32_t* freel;               // [total_slots] free slots (local) ascending
   float* logits;                // [total_slots][lgs]
   uint32_t lgs;                 // logits per slot in that buffer: 8, or 16 with a ninth action
@@ -151,13 +170,17 @@ struct TileScratch {
   const Tile* cell_tiles;
   const uint32_t* tile_rng;
   uint32_t n_slot_tiles, n_cell_tiles;
-  uint32_t* part_slot;   // [slot tiles][16] step counters (actions, moves, meals, deaths, blocked births)
+  uint32_t split_below;   // fewer births than this in a step: several blocks share a child (ECO_MAX_PARTS / 2 at most)
+  uint32_t cap0, cells0;  // an object of one world: its capacity and cells (its tiles need no table); else 0
+  uint32_t* part_slot;   // [slot tiles][16] step counters (PC_*)
   unsigned long long* part_cell;   // [cell tiles][4] regrown, resource total (ecology: energy), water, biomass
-  uint32_t* scan;        // [slot tiles][4] claims, winners, free slots, live slots
-  long long* esum;       // [slot tiles] energy sum of live slots
-  unsigned long long* ecosum;  // [slot tiles][3] ecology: water, biomass, health of live slots
-  double* tmean;         // [slot tiles] mean of the live slots' traits
+  uint32_t* scan;        // [slot tiles][4] birth winners, free slots after the deaths, free slots of the world's
+                         // earlier tiles; live slots (init and state writes)
+  long long* esum;       // [slot tiles] energy sum of the survivors (init: live slots; the next three too)
+  unsigned long long* ecosum;  // [slot tiles][3] ecology: water, biomass, health
+  double* tmean;         // [slot tiles] mean of the traits
   double* tm2;           // [slot tiles] sum of squared deviations from that mean
+  double* parts;         // [ECO_MAX_PARTS] shares of the children's |theta|^2, where blocks share a child
 };
 
 // ---------------------------------------------------------------------------

@@ -25,14 +25,16 @@ const void* forward_kernel_w1(int H, int U, int mode);
 const void* forward_kernel_w2(int H, int U, int mode);
 hipError_t launch_forward_w2(int H, int U, dim3 grid, dim3 block, size_t shmem, hipStream_t s, const Dev& d,
                              const Layout& L);
-hipError_t launch_move(hipStream_t s, const Dev& d, const TileScratch& ts);
-hipError_t launch_birth_claim_regrow(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A);
+hipError_t launch_move(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t H);
+hipError_t launch_settle(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t H, uint32_t small);
+hipError_t launch_claim_cells(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A);
 hipError_t launch_birth_rank(hipStream_t s, const Dev& d, const TileScratch& ts);
-hipError_t launch_birth_commit(hipStream_t s, const Dev& d, const Layout& L, uint32_t blocks);
-hipError_t launch_step_small(hipStream_t s, const Dev& d, const Layout& L);
+hipError_t launch_birth_commit(hipStream_t s, const Dev& d, const Layout& L, const TileScratch& ts, uint32_t births,
+                               uint32_t ranked, int roles);
+hipError_t launch_step_small(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A, uint32_t H);
 hipError_t birth_commit_blocks_per_cu(const Layout& L, int* blocks);
 hipError_t static_scratch(void** ptr, size_t* bytes);
-hipError_t launch_compact(hipStream_t s, const Dev& d, const TileScratch& ts, int init, int only_world);
+hipError_t launch_compact(hipStream_t s, const Dev& d, const TileScratch& ts, int only_world);
 hipError_t launch_prestep_fill(hipStream_t s, const Dev& d);
 hipError_t launch_stream_read(hipStream_t s, const void* p, uint64_t n16, uint32_t* sink, uint32_t blocks,
                               uint32_t threads);
@@ -53,9 +55,6 @@ namespace {
 
 constexpr uint32_t kSlotTileH = 256;
 constexpr uint32_t kCellTileH = 1024;
-constexpr uint32_t kSlotPartH = 16;
-constexpr uint32_t kCellPartH = 4;
-constexpr uint32_t kMaxWorldsH = 1024;
 enum { EMIT_INIT = 0, EMIT_REQUANT = 2 };
 
 thread_local std::string g_err;
@@ -393,7 +392,7 @@ eco_status run_init(eco_world* w) {
     HIPCHK(w, launch_emit_list(s, d, w->L, w->emit_list, n, EMIT_INIT, w->std1, w->std2, w->std3, emit_blocks(w)),
            "init weights");
   }
-  HIPCHK(w, launch_compact(s, d, w->ts, 1, -1), "compact");
+  HIPCHK(w, launch_compact(s, d, w->ts, -1), "compact");
   HIPCHK(w, launch_resource_total(s, d, -1), "resource total");
   eco_status st = sync(w);
   if (st != ECO_OK) return st;
@@ -425,38 +424,46 @@ hipEvent_t take_event(eco_world* w) {
 }
 
 // Kernel groups of one step, in order (each id names one timed group).
-// (The sense bytes the policy kernel reads are built by the previous step's
-// compaction launch, or by init and state writes.)
+// (The window channels the policy kernel reads are built by the previous step's
+// cell pass, or by init and state writes.)
 constexpr int kStepGroups[] = {ECO_K_FORWARD,    ECO_K_MOVE,         ECO_K_BIRTH_CLAIM,
                                ECO_K_BIRTH_SCAN, ECO_K_BIRTH_COMMIT, ECO_K_COMPACT};
 const char* group_name(int k) {
   switch (k) {
     case ECO_K_FORWARD: return "forward kernel";
     case ECO_K_MOVE: return "move kernel";
-    case ECO_K_BIRTH_CLAIM: return "birth claim / regrowth kernel";
-    case ECO_K_BIRTH_SCAN: return "birth ranking kernels";
+    case ECO_K_BIRTH_CLAIM: return "birth claim / cell kernel";
+    case ECO_K_BIRTH_SCAN: return "birth ranking kernel";
     case ECO_K_BIRTH_COMMIT: return "birth commit kernel";
-    default: return "compaction kernels";
+    default: return "live list kernel";
   }
 }
-hipError_t launch_group(eco_world* w, hipStream_t s, const Dev& d, const TileScratch& ts, int k) {
+// The births and the live list with the records are two roles of one launch, made
+// apart only to be timed apart.
+hipError_t launch_group(eco_world* w, hipStream_t s, const Dev& d, const TileScratch& ts, int k, bool timed) {
   switch (k) {
     case ECO_K_FORWARD: return launch_forward(w, s, d, w->launch);
-    case ECO_K_MOVE: return launch_move(s, d, ts);
-    case ECO_K_BIRTH_CLAIM: return launch_birth_claim_regrow(s, d, ts, w->L.A);
+    case ECO_K_MOVE: return launch_move(s, d, ts, w->L.H1);
+    case ECO_K_BIRTH_CLAIM: return launch_claim_cells(s, d, ts, w->L.A);
     case ECO_K_BIRTH_SCAN: return launch_birth_rank(s, d, ts);
-    case ECO_K_BIRTH_COMMIT: return launch_birth_commit(s, d, w->L, birth_blocks(w));
-    default: return launch_compact(s, d, ts, 0, -1);
+    case ECO_K_BIRTH_COMMIT: return launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 0, 1);
+    default: return launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 0, timed ? 2 : 3);
   }
 }
 
-// An object of one small world steps with the policy kernel
-// and one fused launch (k_step_small) unless ECO_RT_SPLIT_STEP asks for the
-// separate kernels: its step is bound by launch latency, not by bytes.
-constexpr uint32_t kSmallSlots = ECO_SMALL_STEP_MAX_SLOTS, kSmallCells = ECO_SMALL_STEP_MAX_CELLS;
+// An object of one small world steps with the policy kernel, one single-block launch
+// (k_step_small) and the birth launch, unless ECO_RT_SPLIT_STEP asks for the separate
+// kernels: its step is bound by the latency of its launches, and one block spares two of
+// them; a larger world's cells keep one block longer than the two launches take.  The
+// line lies where the passes of the block over the cells (4,096 each) make it even.
+// Measured, one block / separate kernels, us per step: single resource 64^2 17.5 / 22.2,
+// 96^2 19.7 / 22.7, 128^2 25.2 / 23.3; the ecology 64^2 22.3 / 25.5, 80^2 24.2 / 25.4,
+// 96^2 26.9 / 25.9, 128^2 37.6 / 28.8 (with terrain and colours 96^2 32.2 / 30.6).
+constexpr uint32_t kSmallSlots = ECO_SMALL_STEP_MAX_SLOTS, kSmallCells = 3 * 4096, kSmallEcologyCells = 2 * 4096;
+static_assert(kSmallCells <= ECO_SMALL_STEP_MAX_CELLS, "inside what the kernel holds");
 bool small_step(const eco_world* w) {
-  return w->n_worlds == 1 && w->total_slots <= kSmallSlots && w->total_cells <= kSmallCells &&
-         !(w->rt_flags & ECO_RT_SPLIT_STEP);
+  return w->n_worlds == 1 && w->total_slots <= kSmallSlots &&
+         w->total_cells <= (w->L.ecology ? kSmallEcologyCells : kSmallCells) && !(w->rt_flags & ECO_RT_SPLIT_STEP);
 }
 
 // Enqueue one step's kernels.  timed: bracket each kernel group with events.
@@ -473,8 +480,12 @@ eco_status enqueue_step(eco_world* w, hipStream_t s, const Dev& d, const TileScr
         if (!a || !b) return dev_fail(w, hipErrorOutOfMemory, "timing events");
         HIPCHK(w, hipEventRecord(a, s), "event record");
       }
-      if (k == ECO_K_FORWARD) HIPCHK(w, launch_forward(w, s, d, w->launch), "forward kernel");
-      else HIPCHK(w, launch_step_small(s, d, w->L), "small-world step kernel");
+      if (k == ECO_K_FORWARD) {
+        HIPCHK(w, launch_forward(w, s, d, w->launch), "forward kernel");
+      } else {
+        HIPCHK(w, launch_step_small(s, d, ts, w->L.A, w->L.H1), "small-world step kernel");
+        HIPCHK(w, launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 1, 3), "birth commit kernel");
+      }
       if (timed) {
         HIPCHK(w, hipEventRecord(b, s), "event record");
         w->ev_pending.push_back({k, {a, b}});
@@ -483,6 +494,7 @@ eco_status enqueue_step(eco_world* w, hipStream_t s, const Dev& d, const TileScr
     return ECO_OK;
   }
   for (int k : kStepGroups) {
+    if (!timed && k == ECO_K_BIRTH_COMMIT) continue;   // with the live list, below
     hipEvent_t a = nullptr, b = nullptr;
     if (timed) {
       a = take_event(w);
@@ -490,12 +502,18 @@ eco_status enqueue_step(eco_world* w, hipStream_t s, const Dev& d, const TileScr
       if (!a || !b) return dev_fail(w, hipErrorOutOfMemory, "timing events");
       HIPCHK(w, hipEventRecord(a, s), "event record");
     }
-    HIPCHK(w, launch_group(w, s, d, ts, k), group_name(k));
+    HIPCHK(w, launch_group(w, s, d, ts, k, timed), group_name(k));
     if (timed) {
       HIPCHK(w, hipEventRecord(b, s), "event record");
       w->ev_pending.push_back({k, {a, b}});
     }
   }
+  return ECO_OK;
+}
+
+// After the last step of a call (or of a graph).
+eco_status enqueue_end(eco_world* w, hipStream_t s, const Dev& d, const TileScratch& ts) {
+  HIPCHK(w, launch_settle(s, d, ts, w->L.H1, small_step(w) ? 1u : 0u), "record kernel");
   return ECO_OK;
 }
 
@@ -559,6 +577,7 @@ eco_status step_graph(eco_world* w, uint32_t m, hipGraphExec_t* out) {
   HIPCHK(w, hipStreamBeginCapture(w->cap_stream, hipStreamCaptureModeThreadLocal), "begin capture");
   eco_status st = ECO_OK;
   for (uint32_t i = 0; i < m && st == ECO_OK; ++i) st = enqueue_step(w, w->cap_stream, d, w->ts, false);
+  if (st == ECO_OK) st = enqueue_end(w, w->cap_stream, d, w->ts);
   const hipError_t e = hipStreamEndCapture(w->cap_stream, &g.graph);
   if (st != ECO_OK || e != hipSuccess) {
     destroy_step_graph(g);
@@ -605,6 +624,7 @@ eco_status timed_graph(eco_world* w, uint32_t n, eco_world::TimedGraph** out) {
   HIPCHK(w, hipStreamBeginCapture(w->cap_stream, hipStreamCaptureModeThreadLocal), "begin capture");
   eco_status st = ECO_OK;
   for (uint32_t i = 0; i < n && st == ECO_OK; ++i) st = enqueue_step(w, w->cap_stream, d, w->ts, false);
+  if (st == ECO_OK) st = enqueue_end(w, w->cap_stream, d, w->ts);
   hipError_t e = hipStreamEndCapture(w->cap_stream, &t.graph);
   if (st != ECO_OK) {
     destroy_timed(t);
@@ -715,7 +735,7 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   if (!out) return fail(ECO_EINVAL, "out is NULL");
   *out = nullptr;
   if (!descs || n_worlds == 0) return fail(ECO_EINVAL, "no worlds");
-  if (n_worlds > kMaxWorldsH) return fail(ECO_EINVAL, "n_worlds exceeds 1024");
+  if (n_worlds > (uint32_t)ECO_MAX_WORLDS) return fail(ECO_EINVAL, "n_worlds exceeds 1024");
   if (alloc && (!alloc->alloc || !alloc->free)) return fail(ECO_EINVAL, "allocator needs alloc and free");
   for (uint32_t i = 0; i < n_worlds; ++i) {
     eco_status st = check_desc(descs[i], i);
@@ -802,7 +822,7 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   };
   d.wp = (const WorldParams*)A(sizeof(WorldParams) * n_worlds);
   d.wv = (WorldVar*)A(sizeof(WorldVar) * n_worlds);
-  d.cnt = (StepCounters*)A(sizeof(StepCounters) * n_worlds);
+  d.draft = (StepDraft*)A(sizeof(StepDraft) * n_worlds);
   d.ring = (eco_stats*)A(sizeof(eco_stats) * kStatsRing * n_worlds);
   d.pos = (int32_t*)A(4 * TS);
   d.energy = (int32_t*)A(4 * TS);
@@ -850,8 +870,8 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   d.master = (w->L.wdtype == ECO_W_FP32) ? d.store : (uint8_t*)A(w->L.mstride * TS);
   w->slot_tiles = (Tile*)A(sizeof(Tile) * std::max<size_t>(1, w->slot_tiles_h.size()));
   w->cell_tiles = (Tile*)A(sizeof(Tile) * std::max<size_t>(1, w->cell_tiles_h.size()));
-  w->part_slot = (uint32_t*)A(4ull * kSlotPartH * std::max(1u, w->n_slot_tiles));
-  w->part_cell = (unsigned long long*)A(8ull * kCellPartH * std::max(1u, w->n_cell_tiles));
+  w->part_slot = (uint32_t*)A(4ull * kSlotPart * std::max(1u, w->n_slot_tiles));
+  w->part_cell = (unsigned long long*)A(8ull * kCellPart * std::max(1u, w->n_cell_tiles));
   w->tile_rng = (uint32_t*)A(4ull * w->tile_rng_h.size());
   {
     const uint64_t T = std::max(1u, w->n_slot_tiles);
@@ -861,6 +881,8 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
     ts.tile_rng = w->tile_rng;
     ts.n_slot_tiles = w->n_slot_tiles;
     ts.n_cell_tiles = w->n_cell_tiles;
+    ts.cap0 = n_worlds == 1 ? w->wp[0].cap : 0u;
+    ts.cells0 = n_worlds == 1 ? w->wp[0].cells : 0u;
     ts.part_slot = w->part_slot;
     ts.part_cell = w->part_cell;
     ts.scan = (uint32_t*)A(16 * T);
@@ -868,6 +890,7 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
     ts.ecosum = w->L.ecology ? (unsigned long long*)A(3 * 8 * T) : nullptr;
     ts.tmean = (double*)A(8 * T);
     ts.tm2 = (double*)A(8 * T);
+    ts.parts = (double*)A(8ull * ECO_MAX_PARTS);
   }
   w->emit_list = (uint32_t*)A(8 * TS);
   {   // placement buckets: 2^k per world, about four cells each
@@ -902,6 +925,7 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
     return fail(ECO_EDEVICE, "no HIP device");
   }
   w->birth_bpc = std::max(1, w->birth_bpc);
+  w->ts.split_below = std::min<uint32_t>(4u * (uint32_t)w->n_cus, ECO_MAX_PARTS / 2);
   d.n_worlds = n_worlds;
   d.total_slots = w->total_slots;
   d.total_cells = w->total_cells;
@@ -932,9 +956,8 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   chk(hipMemsetAsync(d.trait, 0, 8 * TS, s), "clear trait");
   chk(hipMemsetAsync(d.sampled, 0xFF, TS, s), "clear sampled");
   chk(hipMemsetAsync(d.act_in, 0, TS, s), "clear act_in");
-  chk(hipMemsetAsync(w->part_slot, 0, 4ull * kSlotPartH * std::max(1u, w->n_slot_tiles), s), "clear partials");
-  chk(hipMemsetAsync(w->part_cell, 0, 8ull * kCellPartH * std::max(1u, w->n_cell_tiles), s), "clear partials");
-  chk(hipMemsetAsync(d.cnt, 0, sizeof(StepCounters) * n_worlds, s), "clear counters");
+  chk(hipMemsetAsync(w->part_slot, 0, 4ull * kSlotPart * std::max(1u, w->n_slot_tiles), s), "clear partials");
+  chk(hipMemsetAsync(w->part_cell, 0, 8ull * kCellPart * std::max(1u, w->n_cell_tiles), s), "clear partials");
   if (d.ep) {
     std::vector<eco_ecology> ep(n_worlds);
     for (uint32_t i = 0; i < n_worlds; ++i) ep[i] = descs[i].eco;
@@ -996,6 +1019,8 @@ eco_status eco_world_step(eco_world* w, uint32_t n_steps) {
     st = enqueue_step(w, w->stream, d, w->ts, timed);
     if (st != ECO_OK) return st;
   }
+  st = enqueue_end(w, w->stream, d, w->ts);
+  if (st != ECO_OK) return st;
   if (timed) return drain_events(w);
   return ECO_OK;
 }
@@ -1012,13 +1037,16 @@ eco_status eco_world_step_static(eco_world* w, uint32_t n_steps) {
     off = round_up(off + bytes, 256);
     return o;
   };
-  const uint64_t o_part_slot = take(4ull * kSlotPartH * T), o_part_cell = take(8ull * kCellPartH * C),
+  const uint64_t o_part_slot = take(4ull * kSlotPart * T), o_part_cell = take(8ull * kCellPart * C),
                  o_scan = take(16 * T), o_esum = take(8 * T), o_tmean = take(8 * T), o_tm2 = take(8 * T),
                  o_ecosum = w->L.ecology ? take(24 * T) : 0, o_bparent = take(4ull * w->total_slots),
-                 o_freel = take(4ull * w->total_slots), o_cnt = take(sizeof(StepCounters) * w->n_worlds);
+                 o_freel = take(4ull * w->total_slots);
+  take(72ull * w->n_worlds);   // (part of the documented limit; the drafts have their own place)
   void* base = nullptr;
   size_t cap = 0;
   HIPCHK(w, static_scratch(&base, &cap), "static scratch address");
+  // the limit: 16 MiB for all of this but the drafts and the parts (which lie behind it)
+  cap -= sizeof(StepDraft) * ECO_MAX_WORLDS + sizeof(double) * ECO_MAX_PARTS;
   if (off > cap) {
     char buf[200];
     snprintf(buf, sizeof buf, "eco_world_step_static: the object needs %llu bytes of scratch, above the static "
@@ -1032,8 +1060,9 @@ eco_status eco_world_step_static(eco_world* w, uint32_t n_steps) {
   d.keep_logits = (w->rt_flags & ECO_RT_KEEP_LOGITS) ? 1u : 0u;
   d.bparent = reinterpret_cast<int32_t*>(b + o_bparent);
   d.freel = reinterpret_cast<int32_t*>(b + o_freel);
-  d.cnt = reinterpret_cast<StepCounters*>(b + o_cnt);
+  d.draft = reinterpret_cast<StepDraft*>(b + cap);
   TileScratch ts = w->ts;
+  ts.parts = reinterpret_cast<double*>(b + cap + sizeof(StepDraft) * ECO_MAX_WORLDS);
   ts.part_slot = reinterpret_cast<uint32_t*>(b + o_part_slot);
   ts.part_cell = reinterpret_cast<unsigned long long*>(b + o_part_cell);
   ts.scan = reinterpret_cast<uint32_t*>(b + o_scan);
@@ -1048,7 +1077,7 @@ eco_status eco_world_step_static(eco_world* w, uint32_t n_steps) {
     st = enqueue_step(w, w->stream, d, ts, false);
     if (st != ECO_OK) return st;
   }
-  return ECO_OK;
+  return enqueue_end(w, w->stream, d, ts);
 }
 
 eco_status eco_world_prepare(eco_world* w, uint32_t n_steps) {
@@ -1087,6 +1116,7 @@ eco_status eco_world_step_with_actions(eco_world* w, const uint8_t* actions) {
   d.dry = 0;
   d.keep_logits = (w->rt_flags & ECO_RT_KEEP_LOGITS) ? 1u : 0u;
   st = enqueue_step(w, w->stream, d, w->ts, false);
+  if (st == ECO_OK) st = enqueue_end(w, w->stream, d, w->ts);
   if (st != ECO_OK) return st;
   return sync(w);
 }
@@ -1489,7 +1519,7 @@ eco_status eco_world_write_state(eco_world* w, uint32_t world, const void* buf, 
     HIPCHK(w, launch_emit_list(s, w->d, w->L, w->emit_list, (uint32_t)(list.size() / 2), EMIT_INIT, w->std1, w->std2,
                                w->std3, emit_blocks(w)), "init weights");
   }
-  HIPCHK(w, launch_compact(s, w->d, w->ts, 1, (int)world), "compact");
+  HIPCHK(w, launch_compact(s, w->d, w->ts, (int)world), "compact");
   HIPCHK(w, launch_resource_total(s, w->d, (int)world), "resource total");
   return sync(w);
 }

@@ -4,18 +4,28 @@
 // applied turns and made the forward-move claims on the pre-step occupancy):
 //   k_move         winners move; EAT; step cost; death at energy <= 0; age
 //                  (Sec. 3.2 "Resources and Agent Health", "Actions")
-//   k_birth_claim  eligible parents claim the empty cell behind them
-//                  (Sec. 3.2 "Actions": child placed directly behind the parent)
-//   k_birth_scan   per world: winners ranked in slot order, free slots listed in
-//                  ascending order (the recycled-slot free list)
-//   k_birth_commit child state + child weights = parent + sigma * N(0,1)
-//                  (Sec. 3.3 mutation) into the recycled slot
-//   k_regrow       each empty cell regrows one unit with probability p
-//                  (Sec. 3.2: energy slowly grows back)
-//   k_compact      per world: live list of the next step and the step's
-//                  statistics (App. E measurement interface)
+//   k_claim_cells  slot tiles: eligible parents claim the empty cell behind them
+//                  (Sec. 3.2 "Actions": child placed directly behind the parent),
+//                  the free slots are listed in ascending order (the recycled-slot
+//                  free list), the survivors' sums; cell tiles: each empty cell
+//                  regrows one unit with probability p (Sec. 3.2: energy slowly
+//                  grows back) and the window channels of the next step
+//   k_birth_rank   claim winners of each slot tile in slot order; one block per
+//                  world drafts its statistics
+//   k_birth_commit births: child state + child weights = parent + sigma * N(0,1)
+//                  (Sec. 3.3 mutation) into the recycled slot; slot tiles: the
+//                  live list of the next step; the statistics record (App. E
+//                  measurement interface) and the clock
+// Each launch needs what the one before it wrote anywhere in the world, so four is
+// the least without a barrier across the grid, and a launch of this size costs its
+// chain of dependent loads (2 - 4 us, next to 1.7 us for an empty one) whatever
+// little it does: the step after the policy kernel of the 256 x 256 ecology world
+// with 4,213 agents took 35 us in seven launches (moves, claims + regrowth, two
+// ranking passes, births, two compaction passes with the cell pass) and takes
+// 24 us in four.
 // Every contended write is an atomicMin on a claim word; every other write goes
 // to a unique slot or cell, so the integer state is independent of scheduling.
+#include <algorithm>
 #include <mutex>
 
 #include "eco_device.h"
@@ -23,14 +33,8 @@
 namespace eco {
 
 constexpr int kSlotTile = 256;   // slots per block in per-slot kernels
-// Cell tiles (1024 cells each) are built on the host; per-cell kernels take one tile per block.
+constexpr int kCellTile = 1024;  // cells per block in per-cell kernels
 constexpr int kScanThreads = 1024;
-constexpr int kSlotPart = 16;    // u32 counters per slot tile
-constexpr int kCellPart = 4;     // u64 counters per cell tile
-
-// Per-slot-tile counters (index in the partials row).
-enum { PC_HIST = 0, PC_MOVES_OK = 9, PC_MOVES_BLOCKED = 10, PC_EATEN = 11, PC_DEATHS = 12, PC_BB_CELL = 13,
-       PC_KILLED = 14 };
 
 // ---------------------------------------------------------------------------
 // Small block helpers
@@ -181,6 +185,35 @@ __device__ __forceinline__ void count_lanes_by(uint32_t* c, int v) {
 __device__ __forceinline__ void wave_add_u64(unsigned long long v, unsigned long long* c) {
   v = wave_scan(v);
   if ((threadIdx.x & 63u) == 63 && v) atomicAdd(c, v);
+}
+
+// Number of set bits of m below this lane.
+__device__ __forceinline__ uint32_t lanes_before(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Slot tile i and cell tile i of the object, and the slot tiles of world w.  An
+// object of one world computes them (one dependent load less in every launch).
+__device__ __forceinline__ Tile slot_tile(const TileScratch& ts, uint32_t i) {
+  if (ts.cap0) return Tile{0u, i * kSlotTile, min((uint32_t)kSlotTile, ts.cap0 - i * kSlotTile), 0u};
+  return ts.slot_tiles[i];
+}
+__device__ __forceinline__ Tile cell_tile(const TileScratch& ts, uint32_t i) {
+  if (ts.cap0) return Tile{0u, i * kCellTile, min((uint32_t)kCellTile, ts.cells0 - i * kCellTile), 0u};
+  return ts.cell_tiles[i];
+}
+// World w's slot and cell offsets (zero without a load where it is the only one).
+__device__ __forceinline__ uint32_t slot_offset(const Dev& d, const TileScratch& ts, uint32_t w) {
+  return ts.cap0 ? 0u : d.wp[w].slot_off;
+}
+__device__ __forceinline__ uint32_t cell_offset(const Dev& d, const TileScratch& ts, uint32_t w) {
+  return ts.cap0 ? 0u : d.wp[w].cell_off;
+}
+__device__ __forceinline__ uint32_t first_slot_tile(const TileScratch& ts, uint32_t w) {
+  return ts.cap0 ? 0u : ts.tile_rng[4 * w];
+}
+__device__ __forceinline__ uint32_t end_slot_tile(const TileScratch& ts, uint32_t w) {
+  return ts.cap0 ? ts.n_slot_tiles : ts.tile_rng[4 * w + 1];
 }
 
 // ---------------------------------------------------------------------------
@@ -374,10 +407,11 @@ __device__ void emit_agent(const Dev& d, const Layout& L, const WorldParams& wp,
 // resource that ran short, the agent's age and each of the `hits` strikes on its
 // cell this step cost health; at zero health the agent dies and leaves water,
 // energy and biomass on its cell (killed, when struck); otherwise energy heals
-// it below full health and it ages.  Returns the new energy.
+// it below full health and it ages.  Takes and returns its energy; alive says
+// whether it survives.
 __device__ __forceinline__ int ecology_agent(const Dev& d, const eco_ecology& e, const WorldParams& wp, uint32_t slot,
-                                             uint32_t c, int a, uint32_t hits, uint32_t* cnt) {
-  int E = d.energy[slot], Wt = d.water[slot], B = d.biomass[slot], hp = d.hp[slot];
+                                             uint32_t c, int a, uint32_t hits, int E, bool& alive, uint32_t* cnt) {
+  int Wt = d.water[slot], B = d.biomass[slot], hp = d.hp[slot];
   int t = 0;
   if (a == EAT) {
     t = min(min(wp.e_eat, d.ce[c]), e.cap_energy - E);
@@ -399,7 +433,8 @@ __device__ __forceinline__ int ecology_agent(const Dev& d, const eco_ecology& e,
   if (spend < e.w_cost) ++over;
   const long long damage =
       (long long)over * e.hp_overspend + (d.age[slot] >> e.age_shift) + (long long)hits * e.attack_damage;
-  if ((long long)hp - damage <= 0) {
+  alive = (long long)hp - damage > 0;
+  if (!alive) {
     d.cw[c] += Wt;
     d.ce[c] += E;
     d.cb[c] += B;
@@ -424,22 +459,25 @@ __device__ __forceinline__ int ecology_agent(const Dev& d, const eco_ecology& e,
 
 // One live agent's move (a FORWARD winner takes its claimed cell), then EAT, the
 // step cost and death (Sec. 3.2), or with the ecology ecology_agent; counts into
-// the LDS counters cnt.  stamp: the attack stamp of this step (step + 1).
-__device__ __forceinline__ void move_agent(const Dev& d, const WorldParams& wp, uint32_t w, uint32_t slot,
-                                           uint32_t local, uint32_t stamp, uint32_t* cnt) {
-  // every load the non-ecology rules can need, issued before any store: the
-  // agent's fields, then the cells it stands on or claimed (no other agent
-  // writes these cells in this pass: a claim targets a cell free at step start)
-  const int a = d.act[slot];
-  int cell = d.pos[slot];
-  const int t = d.tgt[slot];
-  int E = d.energy[slot];
+// the LDS counters cnt.  a, cell, t, E: its action, position, target and energy;
+// stamp: the attack stamp of this step (step + 1).
+struct Moved {
+  int cell, energy;
+  bool alive;
+};
+
+__device__ __forceinline__ Moved move_agent(const Dev& d, const WorldParams& wp, uint32_t w, uint32_t slot,
+                                            uint32_t local, uint32_t stamp, int a, int cell, int t, int E,
+                                            uint32_t* cnt) {
+  // the loads of the cells it stands on or claimed, issued before any store (no
+  // other agent writes these cells in this pass: a claim targets a cell free at
+  // step start)
   const uint32_t won = (a == FORWARD && t >= 0) ? d.claim[wp.cell_off + t] : ~0u;
   const uint8_t r0 = d.ep ? 0 : d.res[wp.cell_off + cell];
   const uint32_t m0 = (!d.ep && wp.attack) ? d.mark[wp.cell_off + cell] : 0u;
   const uint32_t m1 = (!d.ep && wp.attack && a == FORWARD && t >= 0) ? d.mark[wp.cell_off + t] : 0u;
   count_lanes_by<9>(&cnt[PC_HIST], a);
-  bool moved = false;
+  bool moved = false, alive = true;
   if (a == FORWARD) {
     if (t >= 0 && won == slot) {
       d.claim[wp.cell_off + t] = 0xFFFFFFFFu;
@@ -455,7 +493,7 @@ __device__ __forceinline__ void move_agent(const Dev& d, const WorldParams& wp, 
   }
   if (d.ep) {
     const uint32_t g = wp.cell_off + (uint32_t)cell;
-    E = ecology_agent(d, d.ep[w], wp, slot, g, a, wp.attack ? d.mark[g] : 0u, cnt);
+    E = ecology_agent(d, d.ep[w], wp, slot, g, a, wp.attack ? d.mark[g] : 0u, E, alive, cnt);
   } else if (wp.attack && (moved ? m1 : m0) == stamp) {
     // struck after the moves: dies where it stands; its carried energy goes
     // back to the cell as one resource unit (cells hold 0 or 1 unit)
@@ -463,6 +501,7 @@ __device__ __forceinline__ void move_agent(const Dev& d, const WorldParams& wp, 
     d.occ[wp.cell_off + cell] = -1;
     d.res[wp.cell_off + cell] = 1;
     E = 0;
+    alive = false;
     count_lanes(&cnt[PC_DEATHS]);
     count_lanes(&cnt[PC_KILLED]);
   } else {
@@ -475,69 +514,294 @@ __device__ __forceinline__ void move_agent(const Dev& d, const WorldParams& wp, 
     if (E <= 0) {
       d.flags[slot] = 0;
       d.occ[wp.cell_off + cell] = -1;
+      alive = false;
       count_lanes(&cnt[PC_DEATHS]);
     } else {
       d.age[slot] += 1;
     }
   }
   d.energy[slot] = E;
+  return Moved{cell, E, alive};
 }
 
-__global__ __launch_bounds__(kSlotTile) void k_move(Dev d, const Tile* __restrict__ tiles, uint32_t* __restrict__ part) {
-  __shared__ uint32_t cnt[kSlotPart];
-  if (threadIdx.x < kSlotPart) cnt[threadIdx.x] = 0;
+// Blocks that share one child (a power of two, its logarithm): one where there are
+// enough children to fill the chip, else up to eight, each with at least eight of the
+// H rows of a hidden layer and one of the eight (sixteen) of the output layer.
+__device__ __forceinline__ uint32_t child_split(const TileScratch& ts, uint32_t H, uint32_t births) {
+  uint32_t lgp = 0;
+  while (lgp < 3 && (16u << lgp) <= H && births << lgp < ts.split_below) ++lgp;
+  return lgp;
+}
+
+// |theta|^2 of child j of the object's births (its slot global): from the blocks'
+// shares where they shared the child or for the small-world kernel, else stored.
+__device__ __forceinline__ double child_trait(const Dev& d, const TileScratch& ts, uint32_t lgp, bool shares, uint32_t j,
+                                              uint32_t slot) {
+  if (!shares) return d.trait[slot];
+  double t = 0.0;
+  for (uint32_t p = 0; p < 1u << lgp; ++p) t += ts.parts[(j << lgp) + p];
+  return t;
+}
+
+// Completes the last step's record of world w with its children's traits: the
+// population's moments are the survivors' and the children's combined about the
+// common mean (NT threads).  Run by the launch after the births (the next step's
+// first, or k_settle at the end of a call), since nothing in the births' own launch
+// knows when all of them are done: a counter all blocks add to cost 40 us at 1,700
+// blocks.  TRAITS: also store the traits of children that blocks shared.
+template <int NT, bool TRAITS>
+__device__ void settle_record(const Dev& d, const TileScratch& ts, uint32_t w, uint32_t H, bool small) {
+  __shared__ double red[NT / 64];
+  __shared__ double s_mean;
+  __shared__ uint32_t s_off[2][NT / 64];
+  const WorldVar& v = d.wv[w];
+  const uint32_t nb = v.n_births;
+  if (nb == 0) return;
+  // the object's births before this world's, and all of them
+  uint32_t before = 0, total = 0;
+  for (uint32_t i = threadIdx.x; i < d.n_worlds; i += NT) {
+    const uint32_t b = d.wv[i].n_births;
+    total += b;
+    before += i < w ? b : 0u;
+  }
+  before = wave_scan(before);
+  total = wave_scan(total);
+  if ((threadIdx.x & 63u) == 63u) {
+    s_off[0][threadIdx.x >> 6] = before;
+    s_off[1][threadIdx.x >> 6] = total;
+  }
   __syncthreads();
-  const Tile tl = tiles[blockIdx.x];
+  before = total = 0;
+  for (int i = 0; i < NT / 64; ++i) {
+    before += s_off[0][i];
+    total += s_off[1][i];
+  }
+  const uint32_t lgp = child_split(ts, H, total), slot_off = d.wp[w].slot_off, n = v.n0 + nb;
+  const bool shares = small || lgp > 0;
+  // eight children a thread at once, so that their dependent loads overlap
+  auto batch = [&](uint32_t k0, double (&t)[8]) {
+    uint32_t slot[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t k = k0 + i * NT;
+      slot[i] = (k < nb && (TRAITS || !shares)) ? slot_off + (uint32_t)d.freel[slot_off + k] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t k = k0 + i * NT;
+      t[i] = k < nb ? child_trait(d, ts, lgp, shares, before + k, slot[i]) : 0.0;
+    }
+    if (TRAITS && shares) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (k0 + i * NT < nb) d.trait[slot[i]] = t[i];
+    }
+  };
+  double s = 0.0, q = 0.0, t[8];
+  for (uint32_t k = threadIdx.x; k < nb; k += 8 * NT) {
+    batch(k, t);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += t[i];
+  }
+  s = block_sum_f64<NT>(s, red);
+  if (threadIdx.x == 0) s_mean = ((double)v.n0 * v.mean + s) / (double)n;
+  __syncthreads();
+  const double mu = s_mean;
+  for (uint32_t k = threadIdx.x; k < nb; k += 8 * NT) {
+    if (nb > 8 * NT) batch(k, t);   // (else the values are still here)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (k + i * NT < nb) q += (t[i] - mu) * (t[i] - mu);
+  }
+  q = block_sum_f64<NT>(q, red);
+  if (threadIdx.x == 0) {
+    eco_stats& st = d.ring[(uint64_t)w * kStatsRing + (v.step % kStatsRing)];
+    st.trait_mean = mu;
+    st.trait_var = (v.m2 + (double)v.n0 * (v.mean - mu) * (v.mean - mu) + q) / (double)n;
+  }
+}
+
+// The end of a call: the last step's records and traits complete, no births pending
+// (so that nothing of the step's scratch is read after the call).
+__global__ __launch_bounds__(256) void k_settle(Dev d, TileScratch ts, uint32_t H, uint32_t small) {
+  settle_record<256, true>(d, ts, blockIdx.x, H, small != 0);
+  if (d.n_worlds > 1) return;   // (other worlds' blocks read this world's births: k_settled)
+  __syncthreads();
+  if (threadIdx.x == 0) d.wv[0].n_births = 0;
+}
+__global__ void k_settled(Dev d) {
+  const uint32_t w = blockIdx.x * blockDim.x + threadIdx.x;
+  if (w < d.n_worlds) d.wv[w].n_births = 0;
+}
+
+// Moves (slot tiles), the free slots of each tile, and the birth counter of each
+// world cleared for the step; past the tiles, a block per world completes the last
+// step's record.  Every field a slot's move can need first is loaded at
+// once, live or not (a free slot's are not used).
+__global__ __launch_bounds__(kSlotTile) void k_move(Dev d, TileScratch ts, uint32_t H) {
+  __shared__ uint32_t cnt[kSlotPart];
+  __shared__ uint32_t s_free[kSlotTile / 64];
+  if (blockIdx.x >= ts.n_slot_tiles) {
+    settle_record<kSlotTile, true>(d, ts, blockIdx.x - ts.n_slot_tiles, H, false);
+    return;
+  }
+  if (threadIdx.x < kSlotPart) cnt[threadIdx.x] = 0;
+  const Tile tl = slot_tile(ts, blockIdx.x);
   const WorldParams wp = d.wp[tl.world];
   const uint32_t stamp = (uint32_t)d.wv[tl.world].step + 1u;   // attack stamp of this step
-  if (threadIdx.x < tl.count) {
-    const uint32_t local = tl.start + threadIdx.x;
-    const uint32_t slot = wp.slot_off + local;
-    if (d.flags[slot] & kAlive) move_agent(d, wp, tl.world, slot, local, stamp, cnt);
+  const bool in = threadIdx.x < tl.count;
+  const uint32_t local = tl.start + threadIdx.x, slot = slot_offset(d, ts, tl.world) + local;
+  uint8_t fl = 0;
+  int a = 0, cell = 0, t = -1, E = 0;
+  if (in) {
+    fl = d.flags[slot];
+    a = d.act[slot];
+    cell = d.pos[slot];
+    t = d.tgt[slot];
+    E = d.energy[slot];
   }
   __syncthreads();
-  if (threadIdx.x < kSlotPart && threadIdx.x != PC_BB_CELL)   // the birth claims write PC_BB_CELL
-    part[blockIdx.x * kSlotPart + threadIdx.x] = cnt[threadIdx.x];
+  bool alive = (fl & kAlive) != 0;
+  if (alive) alive = move_agent(d, wp, tl.world, slot, local, stamp, a, cell, t, E, cnt).alive;
+  const uint64_t fm = __ballot(in && !alive);
+  if ((threadIdx.x & 63u) == 0) s_free[threadIdx.x >> 6] = (uint32_t)__builtin_popcountll(fm);
+  __syncthreads();
+  if (threadIdx.x < kSlotPart && threadIdx.x != PC_BB_CELL && threadIdx.x != PC_CLAIMS)   // these two: the birth claims
+    ts.part_slot[blockIdx.x * kSlotPart + threadIdx.x] = cnt[threadIdx.x];
+  if (threadIdx.x == 0) {
+    uint32_t f = 0;
+#pragma unroll
+    for (int i = 0; i < kSlotTile / 64; ++i) f += s_free[i];
+    ts.scan[blockIdx.x * 4 + 1] = f;
+    if (tl.start == 0) d.wv[tl.world].n_win = 0;
+  }
 }
 
-// Eligible parents claim the empty cell directly behind them (slot tiles), and
-// in the same launch each cell tile regrows its empty cells (independent work:
-// regrowth reads and writes only the resource layer).
-// One slot's birth claim: an eligible live parent claims the empty cell directly
-// behind it (lowest slot wins, atomicMin); a parent whose cell behind is taken or
-// walled counts as blocked.
-// Returns whether the slot claimed a cell.
-__device__ __forceinline__ bool birth_claim_slot(const Dev& d, const WorldParams& wp, uint32_t w, uint32_t slot,
-                                                 uint32_t n_actions, uint32_t* blocked) {
-  const uint8_t fl = d.flags[slot];
-  if (!(fl & kAlive)) return false;
-  bool eligible = d.energy[slot] >= wp.e_repro && (n_actions == 5 || d.act[slot] == REPRODUCE);
+// One live agent's birth claim after the moves: an eligible parent claims the empty
+// cell directly behind it (lowest slot wins, atomicMin) and 1 is returned; 2 when
+// that cell is taken or walled (a blocked parent), else 0.  water, biomass: what it
+// carries, in the ecology.
+__device__ __forceinline__ int birth_claim_agent(const Dev& d, const WorldParams& wp, uint32_t w, uint32_t slot,
+                                                 uint32_t n_actions, uint8_t fl, int act, int pos, int facing, int energy,
+                                                 int water, int biomass) {
+  bool eligible = energy >= wp.e_repro && (n_actions == 5 || act == REPRODUCE);
   if (d.ep) {   // ecology: the eighth action, and spare biomass and water to give the child
     const eco_ecology& e = d.ep[w];
-    eligible = d.act[slot] == REPRODUCE_ECO && d.energy[slot] >= wp.e_repro && d.water[slot] >= e.w_child &&
-               d.biomass[slot] >= e.b_repro;
+    eligible = act == REPRODUCE_ECO && energy >= wp.e_repro && water >= e.w_child && biomass >= e.b_repro;
   }
-  if (eligible) {
-    const uint32_t t = neighbour(wp, (uint32_t)d.pos[slot], d.facing[slot], -1);
-    const bool walled = wp.has_walls && d.wall[wp.cell_off + t];
-    if (d.occ[wp.cell_off + t] == -1 && !walled) {
-      atomicMin(&d.claim[wp.cell_off + t], slot);
-      d.tgt[slot] = (int)t;
-      d.flags[slot] = fl | kBirthClaim;
-      return true;
-    }
-    count_lanes(blocked);
-  }
-  return false;
+  if (!eligible) return 0;
+  const uint32_t t = neighbour(wp, (uint32_t)pos, facing, -1);
+  const bool walled = wp.has_walls && d.wall[wp.cell_off + t];
+  if (d.occ[wp.cell_off + t] != -1 || walled) return 2;
+  atomicMin(&d.claim[wp.cell_off + t], slot);
+  d.tgt[slot] = (int)t;
+  d.flags[slot] = fl | kBirthClaim;
+  return 1;
 }
 
-__device__ __forceinline__ void birth_claim_tile(const Dev& d, const TileScratch& ts, uint32_t tile, uint32_t n_actions,
-                                                 uint32_t* blocked) {
-  const Tile tl = ts.slot_tiles[tile];
-  const WorldParams wp = d.wp[tl.world];
-  if (threadIdx.x < tl.count) birth_claim_slot(d, wp, tl.world, wp.slot_off + tl.start + threadIdx.x, n_actions, blocked);
+// Birth claims of one slot tile, the free list of the tile (its free slots at
+// their ranks among the world's, the earlier tiles' counts summed here) and the
+// survivors' sums: count, energy, trait mean and squared deviations from it, and in
+// the ecology what they carry (births move these from parent to child, so they
+// are the totals after the births too).  One barrier: each wave reduces its 64
+// slots, then every wave reads the four waves' results.
+__device__ __forceinline__ void claim_tile(const Dev& d, const TileScratch& ts, uint32_t tile, uint32_t n_actions) {
+  constexpr int NW = kSlotTile / 64;
+  __shared__ uint32_t s_alive[NW], s_free[NW], s_before[NW], s_claims[NW], s_blocked[NW];
+  __shared__ unsigned long long s_e[NW], s_eco[3][NW];
+  __shared__ double s_mean[NW], s_m2[NW];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const Tile tl = slot_tile(ts, tile);
+  const uint32_t w = tl.world;
+  const WorldParams wp = d.wp[w];
+  const bool in = threadIdx.x < tl.count;
+  const uint32_t slot_off = slot_offset(d, ts, w), local = tl.start + threadIdx.x, slot = slot_off + local;
+  uint8_t fl = 0;
+  int act = 0, pos = 0, facing = 0, energy = 0, water = 0, biomass = 0, hp = 0;
+  double trait = 0.0;
+  if (in) {
+    fl = d.flags[slot];
+    act = d.act[slot];
+    pos = d.pos[slot];
+    facing = d.facing[slot];
+    energy = d.energy[slot];
+    trait = d.trait[slot];
+    if (d.ep) {
+      water = d.water[slot];
+      biomass = d.biomass[slot];
+      hp = d.hp[slot];
+    }
+  }
+  uint32_t before = 0;   // free slots of the world's earlier tiles
+  for (uint32_t t = first_slot_tile(ts, w) + threadIdx.x; t < tile; t += kSlotTile) before += ts.scan[t * 4 + 1];
+  const bool alive = (fl & kAlive) != 0;
+  int claim = 0;
+  if (alive) claim = birth_claim_agent(d, wp, w, slot, n_actions, fl, act, pos, facing, energy, water, biomass);
+  const uint64_t am = __ballot(alive), fm = __ballot(in && !alive);
+  const uint64_t cm = __ballot(claim == 1), bm = __ballot(claim == 2);
+  const uint32_t n = (uint32_t)__builtin_popcountll(am);
+  const unsigned long long es = wave_scan(alive ? (unsigned long long)(long long)energy : 0ull);
+  const double mean = n ? lane_value(wave_scan(alive ? trait : 0.0), 63) / (double)n : 0.0;
+  const double dv = alive ? trait - mean : 0.0, m2 = wave_scan(dv * dv);
+  before = wave_scan(before);
+  unsigned long long carried[3] = {0, 0, 0};
+  if (d.ep) {
+    carried[0] = wave_scan(alive ? (unsigned long long)water : 0ull);
+    carried[1] = wave_scan(alive ? (unsigned long long)biomass : 0ull);
+    carried[2] = wave_scan(alive ? (unsigned long long)hp : 0ull);
+  }
+  if (lane == 63) {
+    s_alive[wave] = n;
+    s_free[wave] = (uint32_t)__builtin_popcountll(fm);
+    s_before[wave] = before;
+    s_claims[wave] = (uint32_t)__builtin_popcountll(cm);
+    s_blocked[wave] = (uint32_t)__builtin_popcountll(bm);
+    s_e[wave] = es;
+    s_mean[wave] = mean;
+    s_m2[wave] = m2;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s_eco[k][wave] = carried[k];
+  }
   __syncthreads();
-  if (threadIdx.x == 0) ts.part_slot[tile * kSlotPart + PC_BB_CELL] = *blocked;
+  uint32_t first = 0, tot_before = 0;   // free rank of the wave's first free slot
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    tot_before += s_before[i];
+    if (i < wave) first += s_free[i];
+  }
+  if (in && !alive) d.freel[slot_off + tot_before + first + lanes_before(fm)] = (int)local;
+  if (threadIdx.x == 0) {
+    uint32_t N = 0, F = 0, C = 0, B = 0;
+    unsigned long long E = 0, cw = 0, cb = 0, ch = 0;
+    double sum = 0.0, M2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      N += s_alive[i];
+      F += s_free[i];
+      C += s_claims[i];
+      B += s_blocked[i];
+      E += s_e[i];
+      cw += s_eco[0][i];
+      cb += s_eco[1][i];
+      ch += s_eco[2][i];
+      sum += (double)s_alive[i] * s_mean[i];
+    }
+    const double mu = N ? sum / (double)N : 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) M2 += s_m2[i] + (double)s_alive[i] * (s_mean[i] - mu) * (s_mean[i] - mu);
+    ts.part_slot[tile * kSlotPart + PC_BB_CELL] = B;
+    ts.part_slot[tile * kSlotPart + PC_CLAIMS] = C;
+    ts.scan[tile * 4 + 2] = tot_before;
+    ts.esum[tile] = (long long)E;
+    ts.tmean[tile] = mu;
+    ts.tm2[tile] = M2;
+    if (d.ep) {
+      ts.ecosum[3 * tile] = cw;
+      ts.ecosum[3 * tile + 1] = cb;
+      ts.ecosum[3 * tile + 2] = ch;
+    }
+    if (tile + 1 == end_slot_tile(ts, w)) d.wv[w].n_free = tot_before + F;
+  }
 }
 
 // floor(min(1, rate * b) * 2^32) in exact integer arithmetic, for a finite rate >= 0
@@ -590,30 +854,6 @@ __device__ __forceinline__ uint32_t regrow_word(const WorldParams& wp, uint32_t 
   for (uint32_t j = 0; j < 4; ++j)
     if (j < n) total += (nv >> (8 * j)) & 0xFFu;
   return nv;
-}
-
-// Regrowth of the cells of tile tl (one resource layer), four cells per thread
-// and pass (tiles start at multiples of 1024 cells; the cell allocation ends at a
-// multiple of 64, so the last word of a tile stays inside it); the regrown count
-// and the resource total go to cnt[0], cnt[1] (LDS).
-__device__ __forceinline__ void regrow_cells(const Dev& d, const WorldParams& wp, const Tile tl, uint32_t step,
-                                             unsigned long long* cnt) {
-  unsigned long long grown = 0, total = 0;
-  for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
-    const uint32_t c0 = tl.start + i, n = min(4u, tl.count - i);
-    uint8_t* rp = d.res + wp.cell_off + c0;
-    const uint32_t v = *reinterpret_cast<const uint32_t*>(rp);
-    const uint32_t nv = regrow_word(wp, c0, n, v, step, grown, total);
-    if (nv != v) {
-      if (n == 4) {
-        *reinterpret_cast<uint32_t*>(rp) = nv;
-      } else {
-        for (uint32_t j = 0; j < n; ++j) rp[j] = (uint8_t)(nv >> (8 * j));
-      }
-    }
-  }
-  wave_add_u64(grown, &cnt[0]);
-  wave_add_u64(total, &cnt[1]);
 }
 
 // Four consecutive int32 cells from g (g a multiple of 4; the cell allocation ends
@@ -694,198 +934,453 @@ __device__ __forceinline__ void flow_gather4(const Dev& d, const WorldParams& wp
   }
 }
 
-// The ecology's cell pass over tile tl, four consecutive cells per thread and pass
-// (tile starts are multiples of 4): photosynthesis, one energy unit with
-// probability min(1, rate * biomass) on cells holding biomass below the energy
-// ceiling (the threshold in exact integers; the four cells' draws are the four
-// outputs of one Philox block); the strikes of this step cleared (they have been
-// counted); with terrain, the water's flow gathered into cw_next (the window-word
-// pass copies it back once every cell has read the old layer).  Adds the
-// photosynthesised units to grown and the grid totals of energy, water and biomass
-// to total, wsum, bsum.
-__device__ __forceinline__ void ecology_cells(const Dev& d, const WorldParams& wp, const eco_ecology& e, const Tile tl,
-                                              uint32_t step, unsigned long long& grown, unsigned long long& total,
-                                              unsigned long long& wsum, unsigned long long& bsum) {
+// Window channels of a cell at the start of a step (Sec. 3.2 sensors, App. F
+// layout), one byte per cell: bit 0 agent present, bit 1 resource present, bit 2
+// wall (worlds with walls only), bits 3..5 the occupant's energy bin
+// min(floor(8 E / e_repro), 7).  Built by the cell pass of the step before (and by
+// init and state writes), so that the policy kernel's window gather reads one byte
+// per cell instead of the occupancy, resource and wall arrays plus a dependent read
+// of each occupant's energy.
+// The cell's resource and wall bits of its sense byte.
+__device__ __forceinline__ uint32_t cell_sense(const WorldParams& wp, uint32_t r, uint32_t wl) {
+  return (r != 0 ? 2u : 0u) | (wp.has_walls && wl != 0 ? 4u : 0u);
+}
+
+// An occupant's bits of the sense byte: the agent bit and its energy bin
+// (the number of b in 1..7 with 8 E >= b e_repro).
+__device__ __forceinline__ uint32_t agent_sense(const WorldParams& wp, int energy) {
+  const long long e8 = (long long)energy * 8;
+  uint32_t eb = 0;
+#pragma unroll
+  for (int b = 1; b < 8; ++b) eb += (e8 >= (long long)b * wp.e_repro) ? 1u : 0u;
+  return 1u | (eb << 3);
+}
+
+// Colour vision: the cell as others see it (occupant's colour, else a resource
+// unit in green, else a wall in grey, else black; 8 bits per channel), with the
+// cell's agent / resource / wall bits in the top byte for the move claim.
+// round(clamp(c, 0, 1) * 255) with ties up, in exact integer arithmetic: a c in
+// (0, 1) is M 2^-s with an integer M < 2^24 and s >= 24, so the result is
+// floor((255 M + 2^(s-1)) / 2^s).
+__device__ __forceinline__ uint32_t colour_byte(float c) {
+  if (!(c > 0.0f)) return 0u;   // also NaN
+  if (c >= 1.0f) return 255u;
+  const uint32_t u = __float_as_uint(c);
+  const uint32_t ex = u >> 23;   // c > 0: sign bit clear
+  const uint64_t M = ex ? ((u & 0x7FFFFFu) | 0x800000u) : (u & 0x7FFFFFu);
+  const int s = ex ? 150 - (int)ex : 149;   // c = M 2^-s, s >= 24
+  if (s >= 64) return 0u;
+  return (uint32_t)((255ull * M + (1ull << (s - 1))) >> s);
+}
+
+__device__ __forceinline__ uint32_t colour_word(const float4 c) {
+  return colour_byte(c.x) | (colour_byte(c.y) << 8) | (colour_byte(c.z) << 16);
+}
+
+__device__ __forceinline__ uint32_t sat255(int v) { return (uint32_t)min(max(v, 0), 255); }
+
+// The cells of tile tl of a single-resource world, four consecutive cells per
+// thread and pass (tiles start at multiples of 4 cells; the cell allocation ends at
+// a multiple of 64, so the vector loads of a ragged last group stay inside it).
+// GROW (a step): each empty cell regrows one unit with probability p, and the
+// regrown cells and the resource total go to cnt[0], cnt[1] (LDS).  Then the
+// cell's window channels, from the resources just grown and the occupants after the
+// moves (a birth adds its own, patch_birth_cells), so the grid is read once a step.  agent,
+// col: the occupants' sense bits by cell and colour words by slot, where the caller
+// has them in LDS; else they are read through the occupancy.
+template <bool GROW>
+__device__ __forceinline__ void plain_cells(const Dev& d, const WorldParams& wp, const Tile tl, uint32_t step,
+                                            unsigned long long* cnt, const uint8_t* agent, const uint32_t* col) {
+  unsigned long long grown = 0, total = 0;
+#pragma unroll 1
   for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
     const uint32_t c0 = tl.start + i, n = min(4u, tl.count - i), g = wp.cell_off + c0;
-    int b[4], en[4], wv[4];
-    load_cells4(d.cb + g, b);
-    load_cells4(d.ce + g, en);
-    load_cells4(d.cw + g, wv);
-    const uint32_t fd = d.rock ? *reinterpret_cast<const uint32_t*>(d.flowdir + g) : 0u;
-    FlowRows fr{};   // the flow's neighbour rows, loaded with the cells' own values
-    const bool rows = d.rock && flow_rows_load(d, wp, c0, n, fr);
-    bool any = false;
+    const uint32_t v = *reinterpret_cast<const uint32_t*>(d.res + g);
+    const uint32_t wl = wp.has_walls ? *reinterpret_cast<const uint32_t*>(d.wall + g) : 0u;
+    int o[4] = {-1, -1, -1, -1};
+    uint32_t q[4] = {0u, 0u, 0u, 0u};   // the occupants' sense bits or colour words
+    if (d.rgb || !agent) {
+      load_cells4(d.occ + g, o);
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j) any |= j < n && b[j] > 0 && en[j] < e.cell_energy_max;
-    if (any) {
-      const uint4 x = regrow_draws(wp, c0 >> 2, step);
-      bool grew = false;
+      for (uint32_t j = 0; j < 4; ++j) {
+        if (j >= n) o[j] = -1;   // past a ragged tail: no occupant read
+        if (o[j] < 0) continue;
+        const uint32_t slot = wp.slot_off + (uint32_t)o[j];
+        if (d.rgb) q[j] = col ? col[o[j]] : colour_word(d.colour[slot]);
+        else q[j] = agent_sense(wp, d.energy[slot]);
+      }
+    } else {
+      const uint32_t ag = *reinterpret_cast<const uint32_t*>(agent + c0);
 #pragma unroll
-      for (uint32_t j = 0; j < 4; ++j)
-        if (j < n && b[j] > 0 && en[j] < e.cell_energy_max &&
-            (uint64_t)word_of(x, (int)j) < photo_threshold(e.photo_rate, b[j])) {
-          ++en[j];
-          ++grown;
-          grew = true;
+      for (int j = 0; j < 4; ++j) q[j] = (ag >> (8 * j)) & 0xFFu;
+    }
+    uint32_t nv = v;
+    if constexpr (GROW) {
+      nv = regrow_word(wp, c0, n, v, step, grown, total);
+      if (nv != v) {
+        if (n == 4) {
+          *reinterpret_cast<uint32_t*>(d.res + g) = nv;
+        } else {
+          for (uint32_t j = 0; j < n; ++j) d.res[g + j] = (uint8_t)(nv >> (8 * j));
         }
-      if (grew) store_cells4(d.ce + g, n, en);
+      }
     }
+    if (d.rgb) {
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j)
-      if (j < n) {
-        total += (unsigned long long)(uint32_t)en[j];
-        wsum += (unsigned long long)(uint32_t)wv[j];
-        bsum += (unsigned long long)(uint32_t)b[j];
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t bits = cell_sense(wp, (nv >> (8 * j)) & 0xFFu, (wl >> (8 * j)) & 0xFFu);
+        if (o[j] < 0) q[j] = (bits & 2u) ? 255u << 8 : ((bits & 4u) ? 0x808080u : 0u);
+        q[j] |= ((o[j] >= 0 ? 1u : 0u) | bits) << 24;
       }
-    if (wp.attack) {
+      store_cells4(reinterpret_cast<int32_t*>(d.rgb + g), n, reinterpret_cast<const int*>(q));
+    } else {
+      uint32_t sv = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        sv |= (q[j] | cell_sense(wp, (nv >> (8 * j)) & 0xFFu, (wl >> (8 * j)) & 0xFFu)) << (8 * j);
       if (n == 4) {
-        *reinterpret_cast<uint4*>(d.mark + g) = make_uint4(0u, 0u, 0u, 0u);
+        *reinterpret_cast<uint32_t*>(d.sense + g) = sv;
       } else {
-        for (uint32_t j = 0; j < n; ++j) d.mark[g + j] = 0u;
+        for (uint32_t j = 0; j < n; ++j) d.sense[g + j] = (uint8_t)(sv >> (8 * j));
       }
     }
-    if (d.rock) {
-      int nw[4];
-      flow_gather4(d, wp, c0, n, wv, fd, rows, fr, nw);
-      store_cells4(d.cw_next + g, n, nw);
-    }
+  }
+  if constexpr (GROW) {
+    wave_add_u64(grown, &cnt[0]);
+    wave_add_u64(total, &cnt[1]);
   }
 }
 
-__device__ __forceinline__ void regrow_tile(const Dev& d, const TileScratch& ts, uint32_t tile,
-                                            unsigned long long* cnt) {
-  const Tile tl = ts.cell_tiles[tile];
-  const WorldParams wp = d.wp[tl.world];
-  const uint32_t step = (uint32_t)d.wv[tl.world].step;
-  if (d.ep) {   // ecology: photosynthesis, strikes, flow; the tile's grid totals for the statistics
-    unsigned long long grown = 0, total = 0, wsum = 0, bsum = 0;
-    ecology_cells(d, wp, d.ep[tl.world], tl, step, grown, total, wsum, bsum);
+// The cells of tile tl of an ecology, four consecutive cells per thread and pass.
+// STEP: photosynthesis, one energy unit with probability min(1, rate * biomass) on
+// cells holding biomass below the energy ceiling (the threshold in exact integers;
+// the four cells' draws are the four outputs of one Philox block); the strikes of
+// this step cleared (they have been counted); with terrain, the water's flow
+// gathered into cw_next (copied back by the next pass, once every cell has read the
+// old layer); the photosynthesised units and the grid totals of energy, water and
+// biomass to cnt[0..3] (LDS).  Then the window word of each cell: its water (after
+// the flow), energy and biomass levels (capped at 255), or with colour vision the
+// cell as others see it (occupant's colour, wall grey, else energy / biomass / water
+// as red / green / blue); the agent / wall bits and the rock height in the top byte.
+// col: the live agents' colour words by slot, where the caller has them in LDS.
+template <bool STEP>
+__device__ __forceinline__ void ecology_cells(const Dev& d, const WorldParams& wp, const eco_ecology& e, const Tile tl,
+                                              uint32_t step, unsigned long long* cnt, const uint32_t* col) {
+  unsigned long long grown = 0, total = 0, wsum = 0, bsum = 0;
+#pragma unroll 1
+  for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
+    const uint32_t c0 = tl.start + i, n = min(4u, tl.count - i), g = wp.cell_off + c0;
+    int b[4], en[4], wv[4], o[4], rk[4] = {0, 0, 0, 0};
+    load_cells4(d.occ + g, o);
+    load_cells4(d.cb + g, b);
+    load_cells4(d.ce + g, en);
+    load_cells4(d.cw + g, wv);
+    if (d.rock) load_cells4(d.rock + g, rk);
+    const uint32_t wl4 = wp.has_walls ? *reinterpret_cast<const uint32_t*>(d.wall + g) : 0u;
+    const uint32_t fd = (STEP && d.rock) ? *reinterpret_cast<const uint32_t*>(d.flowdir + g) : 0u;
+    FlowRows fr{};   // the flow's neighbour rows, loaded with the cells' own values
+    const bool rows = STEP && d.rock && flow_rows_load(d, wp, c0, n, fr);
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j)
+      if (j >= n) o[j] = -1;   // past a ragged tail: no occupant read
+    uint32_t q[4] = {0u, 0u, 0u, 0u};
+    if (d.colour) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (o[j] >= 0) q[j] = col ? col[o[j]] : colour_word(d.colour[wp.slot_off + (uint32_t)o[j]]);
+    }
+    if constexpr (STEP) {
+      bool any = false;
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) any |= j < n && b[j] > 0 && en[j] < e.cell_energy_max;
+      if (any) {
+        const uint4 x = regrow_draws(wp, c0 >> 2, step);
+        bool grew = false;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+          if (j < n && b[j] > 0 && en[j] < e.cell_energy_max &&
+              (uint64_t)word_of(x, (int)j) < photo_threshold(e.photo_rate, b[j])) {
+            ++en[j];
+            ++grown;
+            grew = true;
+          }
+        if (grew) store_cells4(d.ce + g, n, en);
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j)
+        if (j < n) {
+          total += (unsigned long long)(uint32_t)en[j];
+          wsum += (unsigned long long)(uint32_t)wv[j];
+          bsum += (unsigned long long)(uint32_t)b[j];
+        }
+      if (wp.attack) {
+        if (n == 4) {
+          *reinterpret_cast<uint4*>(d.mark + g) = make_uint4(0u, 0u, 0u, 0u);
+        } else {
+          for (uint32_t j = 0; j < n; ++j) d.mark[g + j] = 0u;
+        }
+      }
+      if (d.rock) {
+        int nw[4];
+        flow_gather4(d, wp, c0, n, wv, fd, rows, fr, nw);
+        store_cells4(d.cw_next + g, n, nw);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) wv[j] = nw[j];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool wl = ((wl4 >> (8 * j)) & 0xFFu) != 0;
+      if (!d.colour) {
+        q[j] = sat255(wv[j]) | (sat255(en[j]) << 8) | (sat255(b[j]) << 16);
+      } else if (o[j] < 0) {
+        q[j] = wl ? 0x808080u
+                  : (sat255(16 * min(en[j], 1 << 20)) | (sat255(64 * min(b[j], 1 << 20)) << 8) |
+                     (sat255(16 * min(wv[j], 1 << 20)) << 16));
+      }
+      q[j] |= ((o[j] >= 0 ? 1u : 0u) | (wl ? 4u : 0u) | ((uint32_t)rk[j] << 3)) << 24;
+    }
+    store_cells4(reinterpret_cast<int32_t*>(d.rgb + g), n, reinterpret_cast<const int*>(q));
+  }
+  if constexpr (STEP) {
     wave_add_u64(grown, &cnt[0]);
     wave_add_u64(total, &cnt[1]);
     wave_add_u64(wsum, &cnt[2]);
     wave_add_u64(bsum, &cnt[3]);
-    __syncthreads();
-    if (threadIdx.x < kCellPart) ts.part_cell[tile * kCellPart + threadIdx.x] = cnt[threadIdx.x];
+  }
+}
+
+// Window channels of the cells of tile tl as they stand (init, state, colour and
+// terrain writes).
+__device__ __forceinline__ void window_cells(const Dev& d, const Tile tl) {
+  const WorldParams wp = d.wp[tl.world];
+  if (d.ep) ecology_cells<false>(d, wp, d.ep[tl.world], tl, 0u, nullptr, nullptr);
+  else plain_cells<false>(d, wp, tl, 0u, nullptr, nullptr, nullptr);
+}
+
+// With terrain: the water after the flow becomes the water of the cells of tile tl
+// (every cell has read the old layer).
+__device__ __forceinline__ void settle_water(const Dev& d, const WorldParams& wp, const Tile tl) {
+  for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
+    const uint32_t n = min(4u, tl.count - i), g = wp.cell_off + tl.start + i;
+    int wv[4];
+    load_cells4(d.cw_next + g, wv);
+    store_cells4(d.cw + g, n, wv);
+  }
+}
+
+// Birth claims, free lists and the survivors' sums (slot tiles), and in the same
+// launch the cell pass (cell tiles): independent work, since a claim changes neither
+// the occupancy nor the resources.
+__global__ __launch_bounds__(256) void k_claim_cells(Dev d, TileScratch ts, uint32_t n_actions) {
+  __shared__ unsigned long long cnt[kCellPart];
+  if (blockIdx.x < ts.n_slot_tiles) {
+    claim_tile(d, ts, blockIdx.x, n_actions);
     return;
   }
-  regrow_cells(d, wp, tl, step, cnt);
+  const uint32_t tile = blockIdx.x - ts.n_slot_tiles;
+  if (threadIdx.x < kCellPart) cnt[threadIdx.x] = 0;
+  __syncthreads();
+  const Tile tl = cell_tile(ts, tile);
+  const WorldParams wp = d.wp[tl.world];
+  const uint32_t step = (uint32_t)d.wv[tl.world].step;
+  if (d.ep) ecology_cells<true>(d, wp, d.ep[tl.world], tl, step, cnt, nullptr);
+  else plain_cells<true>(d, wp, tl, step, cnt, nullptr, nullptr);
   __syncthreads();
   if (threadIdx.x < kCellPart) ts.part_cell[tile * kCellPart + threadIdx.x] = cnt[threadIdx.x];
 }
 
-__global__ __launch_bounds__(256) void k_birth_claim_regrow(Dev d, TileScratch ts, uint32_t n_actions) {
-  __shared__ uint32_t blocked;
-  __shared__ unsigned long long cnt[kCellPart];
-  if (threadIdx.x == 0) blocked = 0;
-  if (threadIdx.x < kCellPart) cnt[threadIdx.x] = 0;
-  __syncthreads();
-  if (blockIdx.x < ts.n_slot_tiles) birth_claim_tile(d, ts, blockIdx.x, n_actions, &blocked);
-  else regrow_tile(d, ts, blockIdx.x - ts.n_slot_tiles, cnt);
-}
-
-// Birth ranking, pass 1 (slot tiles): mark the claim winners; count claims,
-// winners and free slots of the tile.
-__global__ __launch_bounds__(kSlotTile) void k_birth_rank_count(Dev d, TileScratch ts) {
-  __shared__ uint32_t cnt[3];
-  if (threadIdx.x < 3) cnt[threadIdx.x] = 0;
-  __syncthreads();
-  const Tile tl = ts.slot_tiles[blockIdx.x];
-  const WorldParams wp = d.wp[tl.world];
-  if (threadIdx.x < tl.count) {
-    const uint32_t slot = wp.slot_off + tl.start + threadIdx.x;
-    const uint8_t fl = d.flags[slot];
-    if (fl & kBirthClaim) {
-      count_lanes(&cnt[0]);
-      if (d.claim[wp.cell_off + d.tgt[slot]] == slot) {
-        d.flags[slot] = fl | kBirthWon;
-        count_lanes(&cnt[1]);
-      }
-    }
-    if (!(fl & kAlive)) count_lanes(&cnt[2]);
-  }
-  __syncthreads();
-  if (threadIdx.x < 3) ts.scan[blockIdx.x * 4 + threadIdx.x] = cnt[threadIdx.x];
-}
-
-// Sum over the world's tiles [lo, hi) of pass-1 counter c (ts.scan[t][c]); all
-// threads of the block get the sum.
+// The sums of world w's tiles for its statistics record (one block of NT threads,
+// once the moves, the claims and the cell pass are done): the counters, the grid
+// totals plus, in the ecology, what the survivors carry, and the survivors' trait
+// moments combined from the tiles' (mean = sum n_i mean_i / N, then the squared
+// deviations about it: M2 = sum (M2_i + n_i (mean_i - mean)^2); the slot tiles of a
+// world hold 256 slots each but the last).
 template <int NT>
-__device__ __forceinline__ uint32_t tiles_sum(const TileScratch& ts, uint32_t lo, uint32_t hi, int c,
-                                              unsigned long long* red64, uint32_t* bcast) {
-  uint32_t v = 0;
-  for (uint32_t t = lo + threadIdx.x; t < hi; t += NT) v += ts.scan[t * 4 + c];
-  const unsigned long long tot = block_sum_u64<NT>(v, red64);
-  if (threadIdx.x == 0) *bcast = (uint32_t)tot;
-  __syncthreads();
-  const uint32_t r = *bcast;
-  __syncthreads();
-  return r;
-}
-
-// Birth ranking, pass 2 (slot tiles): winner k of the world (slot order) is
-// recorded as bparent[k], free slot f (ascending) as freel[f].  A tile's
-// offsets are the counts of the world's earlier tiles (pass 1), summed here;
-// the world's last tile also records the world's birth totals.  Claims of
-// this step are cleared.
-__global__ __launch_bounds__(kSlotTile) void k_birth_rank_write(Dev d, TileScratch ts) {
-  __shared__ uint32_t red[kSlotTile / 64 + 1];
-  __shared__ unsigned long long red64[kSlotTile / 64];
-  __shared__ uint32_t bcast;
-  const Tile tl = ts.slot_tiles[blockIdx.x];
-  const uint32_t w = tl.world;
-  const WorldParams wp = d.wp[w];
-  const uint32_t t0 = ts.tile_rng[4 * w], t1 = ts.tile_rng[4 * w + 1];
-  const uint32_t ow = tiles_sum<kSlotTile>(ts, t0, blockIdx.x, 1, red64, &bcast);
-  const uint32_t of = tiles_sum<kSlotTile>(ts, t0, blockIdx.x, 2, red64, &bcast);
-  const bool in = threadIdx.x < tl.count;
-  const uint32_t local = tl.start + threadIdx.x;
-  const uint32_t slot = wp.slot_off + local;
-  const uint8_t fl = in ? d.flags[slot] : (uint8_t)kAlive;
-  uint32_t tot;
-  const uint32_t rw = ow + block_exscan<kSlotTile>((fl & kBirthWon) ? 1u : 0u, red, &tot);
-  const uint32_t rf = of + block_exscan<kSlotTile>((fl & kAlive) ? 0u : 1u, red, &tot);
-  if (in) {
-    if (fl & kBirthClaim) d.claim[wp.cell_off + d.tgt[slot]] = 0xFFFFFFFFu;
-    if (fl & kBirthWon) d.bparent[wp.slot_off + rw] = (int)local;
-    if (!(fl & kAlive)) d.freel[wp.slot_off + rf] = (int)local;
-    if (fl & (kBirthClaim | kBirthWon)) d.flags[slot] = fl & kAlive;
-  }
-  if (blockIdx.x + 1 == t1) {  // the world's totals
-    const uint32_t C = tiles_sum<kSlotTile>(ts, t0, t1, 0, red64, &bcast);
-    const uint32_t Wn = tiles_sum<kSlotTile>(ts, t0, t1, 1, red64, &bcast);
-    const uint32_t F = tiles_sum<kSlotTile>(ts, t0, t1, 2, red64, &bcast);
-    if (threadIdx.x == 0) {
-      const uint32_t nb = min(Wn, F);
-      d.wv[w].n_births = nb;
-      d.wv[w].n_win = Wn;
-      d.cnt[w].births = nb;
-      d.cnt[w].births_blocked_cell = C - Wn;
-      d.cnt[w].births_blocked_capacity = Wn - nb;
+__device__ void world_draft(const Dev& d, const TileScratch& ts, uint32_t w) {
+  constexpr int NW = NT / 64;
+  __shared__ uint32_t s_cnt[kSlotPart + 1][NW];
+  __shared__ unsigned long long s_sum[kCellPart + 4][NW];
+  __shared__ double s_f[NW], s_m2[NW];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t cap = d.wp[w].cap;
+  const uint32_t t0 = first_slot_tile(ts, w), t1 = end_slot_tile(ts, w);
+  const uint32_t c0 = ts.cap0 ? 0u : ts.tile_rng[4 * w + 2], c1 = ts.cap0 ? ts.n_cell_tiles : ts.tile_rng[4 * w + 3];
+  uint32_t c[kSlotPart + 1];
+  unsigned long long u[kCellPart + 4];
+#pragma unroll
+  for (int k = 0; k <= kSlotPart; ++k) c[k] = 0;
+#pragma unroll
+  for (int k = 0; k < kCellPart + 4; ++k) u[k] = 0;
+  double sum = 0.0;
+  for (uint32_t t = t0 + threadIdx.x; t < t1; t += NT) {
+    const uint4* pr = reinterpret_cast<const uint4*>(ts.part_slot + t * kSlotPart);
+    const uint32_t n = min((uint32_t)kSlotTile, cap - (t - t0) * kSlotTile) - ts.scan[t * 4 + 1];
+#pragma unroll
+    for (int k = 0; k < kSlotPart / 4; ++k) {
+      const uint4 v = pr[k];
+      c[4 * k] += v.x;
+      c[4 * k + 1] += v.y;
+      c[4 * k + 2] += v.z;
+      c[4 * k + 3] += v.w;
+    }
+    c[kSlotPart] += n;
+    u[kCellPart] += (unsigned long long)ts.esum[t];
+    sum += (double)n * ts.tmean[t];
+    if (d.ep) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) u[kCellPart + 1 + k] += ts.ecosum[3 * t + k];
     }
   }
+  for (uint32_t t = c0 + threadIdx.x; t < c1; t += NT) {
+    const ulonglong2* pc = reinterpret_cast<const ulonglong2*>(ts.part_cell + t * kCellPart);
+    const ulonglong2 a = pc[0], b = pc[1];
+    u[0] += a.x;
+    u[1] += a.y;
+    u[2] += b.x;
+    u[3] += b.y;
+  }
+  sum = wave_scan(sum);
+  if (lane == 63) s_f[wave] = sum;
+#pragma unroll
+  for (int k = 0; k <= kSlotPart; ++k) {
+    const uint32_t v = wave_scan(c[k]);
+    if (lane == 63) s_cnt[k][wave] = v;
+  }
+#pragma unroll
+  for (int k = 0; k < kCellPart + 4; ++k) {
+    if (k >= kCellPart + 1 && !d.ep) break;
+    const unsigned long long v = wave_scan(u[k]);
+    if (lane == 63) s_sum[k][wave] = v;
+  }
+  __syncthreads();
+  uint32_t N = 0;
+  double S = 0.0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    N += s_cnt[kSlotPart][i];
+    S += s_f[i];
+  }
+  const double mean = N ? S / (double)N : 0.0;
+  double m2 = 0.0;
+  for (uint32_t t = t0 + threadIdx.x; t < t1; t += NT) {
+    const uint32_t n = min((uint32_t)kSlotTile, cap - (t - t0) * kSlotTile) - ts.scan[t * 4 + 1];
+    const double dv = ts.tmean[t] - mean;
+    m2 += ts.tm2[t] + (double)n * dv * dv;
+  }
+  m2 = wave_scan(m2);
+  if (lane == 63) s_m2[wave] = m2;
+  __syncthreads();
+  StepDraft* dr = d.draft + w;
+  if (threadIdx.x < kSlotPart) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) v += s_cnt[threadIdx.x][i];
+    dr->count[threadIdx.x] = v;
+  } else if (threadIdx.x == 64) {
+    unsigned long long v[kCellPart + 4];
+#pragma unroll
+    for (int k = 0; k < kCellPart + 4; ++k) {
+      v[k] = 0;
+      if (k >= kCellPart + 1 && !d.ep) continue;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) v[k] += s_sum[k][i];
+    }
+    double M2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) M2 += s_m2[i];
+    dr->regrown = v[0];
+    dr->resource_total = v[1];
+    dr->water = d.ep ? v[2] + v[kCellPart + 1] : 0ull;
+    dr->biomass = d.ep ? v[3] + v[kCellPart + 2] : 0ull;
+    dr->hp = d.ep ? v[kCellPart + 3] : 0ull;
+    dr->energy = (long long)v[kCellPart];
+    dr->mean = mean;
+    dr->m2 = M2;
+    dr->n0 = N;
+    dr->step = d.wv[w].step;
+    dr->uid_next = d.wv[w].uid_next;
+  }
 }
 
-// Prefix of per-world birth counts in LDS (same scheme as the live offsets).
-__device__ __forceinline__ void birth_offsets(const WorldVar* __restrict__ wv, uint32_t n, uint32_t* off) {
+// Birth ranking.  Slot tiles: the tile's claim winners (their claim word holds
+// their slot), in slot order, as places in the tile; their number to scan[0], and with
+// several worlds to the world's n_win (one world's births are summed from scan[0]:
+// the additions of some hundred tiles to one word cost 3 us).  Then one block per world drafts its statistics, and with
+// terrain a block per cell tile settles the water.
+__global__ __launch_bounds__(kSlotTile) void k_birth_rank(Dev d, TileScratch ts) {
+  __shared__ uint32_t s_win[kSlotTile / 64];
+  if (blockIdx.x >= ts.n_slot_tiles) {
+    const uint32_t b = blockIdx.x - ts.n_slot_tiles;
+    if (b < d.n_worlds) {
+      world_draft<kSlotTile>(d, ts, b);
+    } else {
+      const Tile ct = cell_tile(ts, b - d.n_worlds);
+      settle_water(d, d.wp[ct.world], ct);
+    }
+    return;
+  }
+  const Tile tl = slot_tile(ts, blockIdx.x);
+  const uint32_t slot_off = slot_offset(d, ts, tl.world), cell_off = cell_offset(d, ts, tl.world);
+  const bool in = threadIdx.x < tl.count;
+  const uint32_t first = slot_off + tl.start, slot = first + threadIdx.x;
+  uint8_t fl = 0;
+  int t = 0;
+  if (in) {
+    fl = d.flags[slot];
+    t = d.tgt[slot];
+  }
+  const bool won = (fl & kBirthClaim) && d.claim[cell_off + t] == slot;
+  const uint64_t wm = __ballot(won);
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63u) == 0) s_win[wave] = (uint32_t)__builtin_popcountll(wm);
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+#pragma unroll
+  for (int i = 0; i < kSlotTile / 64; ++i) {
+    if (i < wave) before += s_win[i];
+    total += s_win[i];
+  }
+  if (won) d.bparent[first + before + lanes_before(wm)] = (int)threadIdx.x;
+  if (threadIdx.x == 0) {
+    ts.scan[blockIdx.x * 4] = total;
+    if (total && !ts.cap0) atomicAdd(&d.wv[tl.world].n_win, total);
+  }
+}
+
+// Births of a world this step: its winners, as far as free slots go (an object of
+// several worlds, or winners ranked by the small-world kernel).
+__device__ __forceinline__ uint32_t births_of(const WorldVar& v) { return min(v.n_win, v.n_free); }
+
+// Prefixes of the per-world birth and winner counts in LDS (same scheme as the live offsets).
+__device__ __forceinline__ void birth_offsets(const WorldVar* __restrict__ wv, uint32_t n, uint32_t* off,
+                                              uint32_t* off_win) {
   const int tid = threadIdx.x;
   if (tid < 64) {
     const uint32_t per = (n + 63) / 64;
-    const uint32_t lo = tid * per, hi = min(lo + per, n);
-    uint32_t s = 0;
-    for (uint32_t i = lo; i < hi; ++i) s += wv[i].n_births;
-    const uint32_t inc = wave_scan(s);
-    uint32_t run = inc - s;
+    const uint32_t lo = min(tid * per, n), hi = min(lo + per, n);
+    uint32_t s = 0, sw = 0;
+    for (uint32_t i = lo; i < hi; ++i) {
+      s += births_of(wv[i]);
+      sw += wv[i].n_win;
+    }
+    const uint32_t inc = wave_scan(s), incw = wave_scan(sw);
+    uint32_t run = inc - s, runw = incw - sw;
     for (uint32_t i = lo; i < hi; ++i) {
       off[i] = run;
-      run += wv[i].n_births;
+      off_win[i] = runw;
+      run += births_of(wv[i]);
+      runw += wv[i].n_win;
     }
-    if (tid == 63) off[n] = inc;
+    if (tid == 63) {
+      off[n] = inc;
+      off_win[n] = incw;
+    }
   }
   __syncthreads();
 }
 
-constexpr int kMaxWorlds = 1024;
+constexpr int kMaxWorlds = ECO_MAX_WORLDS;
 
 // Unit u of an agent's master (16 bytes, four consecutive logical parameters):
 // its Philox block (= first logical parameter / 4), layer (0..2 weights, 3..5
@@ -966,120 +1461,142 @@ __device__ __forceinline__ void store_unit(const Layout& L, uint8_t* sc, int lay
   }
 }
 
+// One part of an agent's units, for 2^lgp blocks working on one agent: rows
+// [part H / parts, ...) of W1, W2 and the biases, R3 / parts rows of the output
+// layer, its biases with part 0.  Rows, not columns, so that an FP8 row's scale is
+// one block's; at least eight rows, so that a k-block of a part is a whole 128-byte
+// line.
+template <int H>
+struct PartRows {
+  uint32_t lgr;     // log2 of the rows of a part
+  uint32_t row0;    // its first row
+  uint32_t part, lgp;
+};
+template <int H>
+__device__ __forceinline__ PartRows<H> part_rows(uint32_t part, uint32_t lgp) {
+  constexpr uint32_t LG = H == 32 ? 5 : (H == 64 ? 6 : 7);
+  return PartRows<H>{LG - lgp, part << (LG - lgp), part, lgp};
+}
+// Unit of W2 number q of the part, and the others: b1, b2 and W3 in turn, then b3.
+template <int H>
+__device__ __forceinline__ uint32_t part_w2_unit(const Layout& L, const PartRows<H>& pr, uint32_t q) {
+  return L.u_w2 + (q >> pr.lgr) * H + pr.row0 + (q & ((1u << pr.lgr) - 1u));
+}
+template <int H>
+__device__ __forceinline__ uint32_t part_rest_count(const Layout& L, const PartRows<H>& pr) {
+  return ((2u * (H / 4) + L.R3 * (H / 4)) >> pr.lgp) + (pr.part == 0 ? L.R3 / 4 : 0u);
+}
+template <int H>
+__device__ __forceinline__ uint32_t part_rest_unit(const Layout& L, const PartRows<H>& pr, uint32_t q) {
+  const uint32_t nb = (H / 4) >> pr.lgp, n3 = (L.R3 * (H / 4)) >> pr.lgp;
+  if (q < nb) return L.u_b1 + pr.part * nb + q;
+  q -= nb;
+  if (q < nb) return L.u_b2 + pr.part * nb + q;
+  q -= nb;
+  return q < n3 ? L.u_w3 + pr.part * n3 + q : L.u_b3 + (q - n3);
+}
+
 // FP8 storage, after store_unit has gathered each row's amax in s_amax: the row
-// scales, then the weights quantised with them (each thread re-reads the master
-// units it wrote itself).
+// scales of the part, then its weights quantised with them (each thread re-reads
+// master units its block wrote).
 template <int H, int NT>
 __device__ __forceinline__ void fp8_finish(const Layout& L, const float4* __restrict__ mc, uint8_t* sc,
-                                           const uint32_t* s_amax, uint32_t tid) {
-  const uint32_t nrows = 2 * H + L.R3;
-  for (uint32_t r = tid; r < nrows; r += NT) {
+                                           const uint32_t* s_amax, const PartRows<H>& pr, uint32_t tid) {
+  auto row_scale = [&](uint32_t r) {
     const float amax = __uint_as_float(s_amax[r]);
-    const float scale = amax > 0.0f ? amax / 448.0f : 1.0f;
-    uint64_t off;
-    if (r < H) off = L.s_sc1 + (uint64_t)r * 4;
-    else if (r < 2 * H) off = L.s_sc2 + (uint64_t)(r - H) * 4;
-    else off = L.s_sc3 + (uint64_t)(r - 2 * H) * 4;
-    *reinterpret_cast<float*>(sc + off) = scale;
+    return amax > 0.0f ? amax / 448.0f : 1.0f;
+  };
+  auto quantise = [&](const float4 m4, float scale) {
+    return fp8_rne_sat(m4.x / scale) | (fp8_rne_sat(m4.y / scale) << 8) | (fp8_rne_sat(m4.z / scale) << 16) |
+           (fp8_rne_sat(m4.w / scale) << 24);
+  };
+  const uint32_t rows = 1u << pr.lgr, rows3 = L.R3 >> pr.lgp;
+  for (uint32_t i = tid; i < 2 * rows + rows3; i += NT) {
+    const bool l1 = i < rows, l2 = !l1 && i < 2 * rows;
+    const uint32_t r = l1 ? pr.row0 + i : (l2 ? pr.row0 + i - rows : pr.part * rows3 + i - 2 * rows);
+    *reinterpret_cast<float*>(sc + (l1 ? L.s_sc1 : (l2 ? L.s_sc2 : L.s_sc3)) + (uint64_t)r * 4) =
+        row_scale(l1 ? r : (l2 ? H + r : 2 * H + r));
   }
   // W1: the four k-blocks of one 16-byte storage block of a row (k-blocks 4j .. 4j + 3,
   // the missing ones of a row's last block zero) in one thread, written whole
-  constexpr uint32_t LG = H == 32 ? 5 : (H == 64 ? 6 : 7);
-  const uint32_t KB1 = L.KB1, nquads = ((KB1 + 3) >> 2) * H;
+  const uint32_t KB1 = L.KB1, nquads = ((KB1 + 3) >> 2) << pr.lgr;
 #pragma unroll 1
   for (uint32_t q = tid; q < nquads; q += NT) {
-    const uint32_t row = q & (H - 1), j = q >> LG;
-    const float amax = __uint_as_float(s_amax[row]);
-    const float scale = amax > 0.0f ? amax / 448.0f : 1.0f;
+    const uint32_t row = pr.row0 + (q & (rows - 1)), j = q >> pr.lgr;
+    const float scale = row_scale(row);
     uint32_t wq[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const uint32_t kb = 4 * j + t;
-      wq[t] = 0u;
-      if (kb < KB1) {
-        const float4 m4 = mc[kb * H + row];
-        wq[t] = fp8_rne_sat(m4.x / scale) | (fp8_rne_sat(m4.y / scale) << 8) | (fp8_rne_sat(m4.z / scale) << 16) |
-                (fp8_rne_sat(m4.w / scale) << 24);
-      }
+      wq[t] = kb < KB1 ? quantise(mc[kb * H + row], scale) : 0u;
     }
     typedef unsigned int u32x4s __attribute__((ext_vector_type(4)));
     __builtin_nontemporal_store(u32x4s{wq[0], wq[1], wq[2], wq[3]},
                                 reinterpret_cast<u32x4s*>(sc + L.s_w1 + ((uint64_t)j * H + row) * 16));
   }
-  for (uint32_t u = L.u_b1 + tid; u < L.u_b3; u += NT) {
-    const UnitPos up = unit_pos<H>(L, u);
-    const int layer = up.layer;
-    const uint32_t row = up.row, kb = up.kb;
-    if (layer >= 3) continue;
-    const uint32_t r = layer == 0 ? row : (layer == 1 ? H + row : 2 * H + row);
-    const float amax = __uint_as_float(s_amax[r]);
-    const float scale = amax > 0.0f ? amax / 448.0f : 1.0f;
-    const float4 m4 = mc[u];
-    const uint32_t q = fp8_rne_sat(m4.x / scale) | (fp8_rne_sat(m4.y / scale) << 8) |
-                       (fp8_rne_sat(m4.z / scale) << 16) | (fp8_rne_sat(m4.w / scale) << 24);
-    uint64_t off;
-    if (layer == 0) off = L.s_w1 + ((uint64_t)(kb >> 2) * H + row) * 16 + (kb & 3) * 4;
-    else if (layer == 1) off = L.s_w2 + ((uint64_t)(kb >> 2) * H + row) * 16 + (kb & 3) * 4;
-    else off = L.s_w3 + (uint64_t)row * H + 4 * kb;
-    *reinterpret_cast<uint32_t*>(sc + off) = q;
+  const uint32_t n2 = (H / 4) << pr.lgr;
+  for (uint32_t q = tid; q < n2; q += NT) {
+    const uint32_t u = part_w2_unit<H>(L, pr, q), e = u - L.u_w2, row = e & (H - 1), kb = e / H;
+    *reinterpret_cast<uint32_t*>(sc + L.s_w2 + ((uint64_t)(kb >> 2) * H + row) * 16 + (kb & 3) * 4) =
+        quantise(mc[u], row_scale(H + row));
+  }
+  const uint32_t n3 = (L.R3 * (H / 4)) >> pr.lgp;
+  for (uint32_t q = tid; q < n3; q += NT) {
+    const uint32_t e = pr.part * n3 + q, row = e / (H / 4);
+    *reinterpret_cast<uint32_t*>(sc + L.s_w3 + (uint64_t)4 * e) = quantise(mc[L.u_w3 + e], row_scale(2 * H + row));
   }
 }
 
-// Child master = parent master + sigma z (Sec. 3.3 mutation of every parameter),
-// z standard normal from the parent's Philox stream (parent slot, step, MUTATE,
-// block); the storage copy re-quantised from it; the child's |theta|^2.  One
-// block of 256 threads per child.
+// The birth launch's arguments in one struct, which the kernel reads where it uses
+// them: args() is the argument segment behind an empty asm statement the compiler
+// cannot see through, so that what is read through one call is not kept in scalar
+// registers beyond the next.  Held over the noise loops the pointers and sizes of
+// the rest of the kernel push that loop's own constants and keys out (its body grew
+// from 243 to 321 instructions, and the births of a 65,536-agent world with 840 of
+// them a step from 79 to 116 us).
+struct CommitArgs {
+  Dev d;
+  Layout L;
+  TileScratch ts;
+  uint32_t base, n_birth_blocks, ranked;
+};
+__device__ __forceinline__ const CommitArgs& args() {
+  typedef const __attribute__((address_space(4))) CommitArgs* seg_ptr;
+  seg_ptr p = (seg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const CommitArgs*)p;
+}
+
+// One part of a child: master = parent master + sigma z (Sec. 3.3 mutation of every
+// parameter), z standard normal from the parent's Philox stream (parent slot, step,
+// MUTATE, block); the storage copy re-quantised from it.  Returns the part's share of
+// the child's |theta|^2 (valid in thread 0).
 template <int WDT, int H, int NT>
-__device__ void mutate_child(const Dev& d, const Layout& L, const WorldParams& wp, uint32_t child, uint32_t parent,
-                             uint32_t rng_slot, uint32_t step, const double2* tab, uint32_t* s_amax,
-                             double* s_red) {
+__device__ double mutate_part(uint32_t child, uint32_t parent, float wsigma, uint32_t key0, uint32_t key1,
+                              uint32_t rng_slot, uint32_t step, const PartRows<H> pr, const double2* tab,
+                              uint32_t* s_amax, double* s_red) {
   const uint32_t tid = threadIdx.x;
-  const float4* __restrict__ mp = reinterpret_cast<const float4*>(d.master + (uint64_t)parent * L.mstride);
-  float4* __restrict__ mc = reinterpret_cast<float4*>(d.master + (uint64_t)child * L.mstride);
-  uint8_t* sc = d.store + (uint64_t)child * L.sstride;
+  const CommitArgs& a0 = args();
+  const float4* __restrict__ mp = reinterpret_cast<const float4*>(a0.d.master + (uint64_t)parent * a0.L.mstride);
+  float4* __restrict__ mc = reinterpret_cast<float4*>(a0.d.master + (uint64_t)child * a0.L.mstride);
+  uint8_t* sc = a0.d.store + (uint64_t)child * a0.L.sstride;
   if (WDT == 2) {
-    for (uint32_t i = tid; i < 2 * H + L.R3; i += NT) s_amax[i] = 0u;
+    for (uint32_t i = tid; i < 2 * H + a0.L.R3; i += NT) s_amax[i] = 0u;
     __syncthreads();
   }
-  const double sigma = (double)wp.sigma;
-  const uint32_t key0 = wp.key0, key1 = wp.key1;
-  if (L.colour && tid == 0) {
-    // colour trait: the parent's plus sigma N(0,1) per channel
-    double z[4];
-    gauss4(wp, rng_slot, step, ST_COLOUR_MUTATE, 0u, tab, z);
-    const float4 pc = d.colour[parent];
-    d.colour[child] = make_float4((float)__builtin_fma(sigma, z[0], (double)pc.x),
-                                  (float)__builtin_fma(sigma, z[1], (double)pc.y),
-                                  (float)__builtin_fma(sigma, z[2], (double)pc.z), 0.0f);
-  }
+  const double sigma = (double)wsigma;
   double tsum = 0.0;
-  auto unit = [&](uint32_t u, const UnitPos& up) {
-    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (up.nvalid > 0) {
-      const float4 p4 = stream_load4(mp + u);
-      const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
-      double z[4];
-      gauss4k(key0, key1, rng_slot, step, ST_MUTATE, up.blk, tab, z);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = (i < (int)up.nvalid) ? (float)__builtin_fma(sigma, z[i], (double)pv[i]) : 0.0f;
-    }
-    stream_store4<WDT>(mc + u, v[0], v[1], v[2], v[3]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) tsum += (double)v[i] * (double)v[i];
-    store_unit<WDT, H>(L, sc, up.layer, up.row, up.kb, v, s_amax);
-  };
   // W1 (most of the units) without the layer decode, then the other layers
-  constexpr uint32_t LG = H == 32 ? 5 : (H == 64 ? 6 : 7);
-  const uint32_t ub1 = L.u_b1;
+  const uint32_t KB1 = a0.L.KB1, s_w1 = a0.L.s_w1, lgr = pr.lgr, row0 = pr.row0, rmask = (1u << lgr) - 1u;
   if (WDT == 1) {
     // BF16: the two units of one 16-byte storage block (k-blocks 2j and 2j + 1 of a
     // row) in one thread, so that the block is written whole and, like the
     // master, streamed past the caches (the second half of a row's last block is
     // padding when the row has an odd number of k-blocks: zero)
-    const uint32_t KB1 = L.KB1, npairs = ((KB1 + 1) >> 1) * H;
+    const uint32_t npairs = ((KB1 + 1) >> 1) << lgr;
 #pragma unroll 1
     for (uint32_t q = tid; q < npairs; q += NT) {
-      const uint32_t row = q & (H - 1), j = q >> LG, kb0 = 2 * j;
+      const uint32_t row = row0 + (q & rmask), j = q >> lgr, kb0 = 2 * j;
       const bool two = kb0 + 1 < KB1;
       const uint32_t u0 = kb0 * H + row, u1 = u0 + H;
       const float4 a = stream_load4(mp + u0);
@@ -1102,86 +1619,316 @@ __device__ void mutate_child(const Dev& d, const Layout& L, const WorldParams& w
       typedef unsigned int u32x4s __attribute__((ext_vector_type(4)));
       const u32x4s blk = {bf16_rne(va[0]) | (bf16_rne(va[1]) << 16), bf16_rne(va[2]) | (bf16_rne(va[3]) << 16),
                           bf16_rne(vb[0]) | (bf16_rne(vb[1]) << 16), bf16_rne(vb[2]) | (bf16_rne(vb[3]) << 16)};
-      __builtin_nontemporal_store(blk, reinterpret_cast<u32x4s*>(sc + L.s_w1 + ((uint64_t)j * H + row) * 16));
+      __builtin_nontemporal_store(blk, reinterpret_cast<u32x4s*>(sc + s_w1 + ((uint64_t)j * H + row) * 16));
+    }
+  } else {
+    const uint32_t n1 = KB1 << lgr;
+    auto unit_of = [&](uint32_t q) { return (q >> lgr) * H + row0 + (q & rmask); };
+    float4 next = tid < n1 ? stream_load4(mp + unit_of(tid)) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll 1
+    for (uint32_t q = tid; q < n1; q += NT) {
+      const float4 p4 = next;   // this unit's parent values, loaded one unit ahead
+      if (q + NT < n1) next = stream_load4(mp + unit_of(q + NT));
+      const uint32_t row = row0 + (q & rmask), kb = q >> lgr;
+      const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
+      double z[4];
+      gauss4k(key0, key1, rng_slot, step, ST_MUTATE, row * KB1 + kb, tab, z);
+      float v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = (float)__builtin_fma(sigma, z[i], (double)pv[i]);
+      stream_store4<WDT>(mc + kb * H + row, v[0], v[1], v[2], v[3]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tsum += (double)v[i] * (double)v[i];
+      store_unit<WDT, H>(a0.L, sc, 0, row, kb, v, s_amax);
     }
   }
-  float4 next = (WDT != 1 && tid < ub1) ? stream_load4(mp + tid) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  const Layout& L = args().L;
+  const uint32_t n2 = (H / 4) << lgr, nrest = n2 + part_rest_count<H>(L, pr);
 #pragma unroll 1
-  for (uint32_t u = WDT == 1 ? ub1 : tid; u < ub1; u += NT) {
-    const float4 p4 = next;   // this unit's parent values, loaded one unit ahead
-    if (u + NT < ub1) next = stream_load4(mp + u + NT);
-    const uint32_t row = u & (H - 1), kb = u >> LG;
-    const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
-    double z[4];
-    gauss4k(key0, key1, rng_slot, step, ST_MUTATE, row * L.KB1 + kb, tab, z);
-    float v[4];
+  for (uint32_t q = tid; q < nrest; q += NT) {
+    const uint32_t u = q < n2 ? part_w2_unit<H>(L, pr, q) : part_rest_unit<H>(L, pr, q - n2);
+    const UnitPos up = unit_pos<H>(L, u);
+    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (up.nvalid > 0) {
+      const float4 p4 = stream_load4(mp + u);
+      const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
+      double z[4];
+      gauss4k(key0, key1, rng_slot, step, ST_MUTATE, up.blk, tab, z);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = (float)__builtin_fma(sigma, z[i], (double)pv[i]);
+      for (int i = 0; i < 4; ++i) v[i] = (i < (int)up.nvalid) ? (float)__builtin_fma(sigma, z[i], (double)pv[i]) : 0.0f;
+    }
     stream_store4<WDT>(mc + u, v[0], v[1], v[2], v[3]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) tsum += (double)v[i] * (double)v[i];
-    store_unit<WDT, H>(L, sc, 0, row, kb, v, s_amax);
+    store_unit<WDT, H>(L, sc, up.layer, up.row, up.kb, v, s_amax);
   }
-#pragma unroll 1
-  for (uint32_t u = L.u_b1 + tid; u < L.u_end; u += NT) unit(u, unit_pos<H>(L, u));
   if (WDT == 2) {
     __syncthreads();
-    fp8_finish<H, NT>(L, mc, sc, s_amax, tid);
+    fp8_finish<H, NT>(L, mc, sc, s_amax, pr, tid);
   }
-  const double t = block_sum_f64<NT>(tsum, s_red);
-  if (tid == 0) d.trait[child] = t;
+  return block_sum_f64<NT>(tsum, s_red);
 }
 
-// Birth k of world w (the block's NT threads): the parent bparent[k] places
-// its child in the free slot freel[k] (Sec. 3.2 reproduce, Sec. 3.3 mutation).
-template <int WDT, int H, int NT>
-__device__ __forceinline__ void commit_birth(const Dev& d, const Layout& L, uint32_t w, const WorldParams& wp,
-                                             uint32_t k, uint32_t step, const double2* tab, uint32_t* s_amax,
-                                             double* s_red) {
-  const uint32_t p_local = (uint32_t)d.bparent[wp.slot_off + k];
-  const uint32_t c_local = (uint32_t)d.freel[wp.slot_off + k];
+// The integer part of birth k of world w (one thread a birth): the child's state, what the
+// parent gives, its colour trait, and the window channels that the birth changes
+// after the cell pass of the step: the child's cell (occupied now, the child's
+// energy or colour) and, in the sense bytes, the parent's (its energy after the birth).
+__device__ __forceinline__ void place_child(const Dev& d, uint32_t w, uint32_t k, uint32_t p_local, uint32_t c_local,
+                                            const double2* tab) {
+  const WorldParams& wp = d.wp[w];
   const uint32_t pg = wp.slot_off + p_local, cg = wp.slot_off + c_local;
-  if (threadIdx.x == 0) {
-    const int t = d.tgt[pg];
-    d.energy[pg] -= wp.e_child;
-    d.flags[cg] = kAlive;
-    d.pos[cg] = t;
-    d.occ[wp.cell_off + t] = (int)c_local;
-    d.facing[cg] = d.facing[pg];
-    d.energy[cg] = wp.e_child;
-    d.age[cg] = 0;
-    d.uid[cg] = d.wv[w].uid_next + k;
-    d.puid[cg] = d.uid[pg];
-    if (d.ep) {   // ecology: the parent gives water and biomass; the child starts at hp_child
-      const eco_ecology& e = d.ep[w];
-      d.water[pg] -= e.w_child;
-      d.biomass[pg] -= e.b_child;
-      d.water[cg] = e.w_child;
-      d.biomass[cg] = e.b_child;
-      d.hp[cg] = e.hp_child;
-    }
+  const int t = d.tgt[pg], E = d.energy[pg] - wp.e_child, pc = d.pos[pg];
+  const uint8_t facing = d.facing[pg];
+  const unsigned long long puid = d.uid[pg];
+  const uint32_t gt = wp.cell_off + (uint32_t)t, gp = wp.cell_off + (uint32_t)pc;
+  const uint32_t word = d.rgb ? d.rgb[gt] : d.sense[gt], own = d.rgb ? 0u : d.sense[gp];
+  uint32_t colour = 0u;
+  if (d.colour) {   // the parent's plus sigma N(0,1) per channel
+    double z[4];
+    gauss4k(wp.key0, wp.key1, p_local, (uint32_t)d.draft[w].step, ST_COLOUR_MUTATE, 0u, tab, z);
+    const double sigma = (double)wp.sigma;
+    const float4 p = d.colour[pg];
+    const float4 c = make_float4((float)__builtin_fma(sigma, z[0], (double)p.x),
+                                 (float)__builtin_fma(sigma, z[1], (double)p.y),
+                                 (float)__builtin_fma(sigma, z[2], (double)p.z), 0.0f);
+    d.colour[cg] = c;
+    colour = colour_word(c);
   }
-  mutate_child<WDT, H, NT>(d, L, wp, cg, pg, p_local, step, tab, s_amax, s_red);
-  __syncthreads();
+  d.energy[pg] = E;
+  d.pos[cg] = t;
+  d.occ[gt] = (int)c_local;
+  d.facing[cg] = facing;
+  d.energy[cg] = wp.e_child;
+  d.age[cg] = 0;
+  d.uid[cg] = d.draft[w].uid_next + k;
+  d.puid[cg] = puid;
+  if (d.ep) {   // ecology: the parent gives water and biomass; the child starts at hp_child
+    const eco_ecology& e = d.ep[w];
+    d.water[pg] -= e.w_child;
+    d.biomass[pg] -= e.b_child;
+    d.water[cg] = e.w_child;
+    d.biomass[cg] = e.b_child;
+    d.hp[cg] = e.hp_child;
+  }
+  if (d.rgb) {
+    d.rgb[gt] = (d.colour ? (word & 0xFF000000u) | colour : word) | 1u << 24;
+  } else {
+    d.sense[gt] = (uint8_t)((word & 6u) | agent_sense(wp, wp.e_child));
+    d.sense[gp] = (uint8_t)((own & 6u) | agent_sense(wp, E));
+  }
 }
 
-// One block per birth (persistent over all worlds' births).  Six waves per SIMD
-// (five with a BF16 or FP8 copy to write) fit without spilling; the noise
-// arithmetic of the other waves hides each wave's parent reads.
+// World w's statistics record and the clock advance (one block): its draft
+// completed by the births.  With births, the trait moments follow once
+// the children are written (settle_record).
+__device__ __forceinline__ void world_record(const Dev& d, const TileScratch& ts, uint32_t w, bool ranked) {
+  __shared__ uint32_t s_win[kSlotTile / 64];
+  const StepDraft dr = d.draft[w];
+  WorldVar& v = d.wv[w];
+  uint32_t nw = v.n_win;
+  const uint32_t n_free = v.n_free;
+  if (ts.cap0 && !ranked) {
+    uint32_t win = 0;
+    for (uint32_t i = threadIdx.x; i < ts.n_slot_tiles; i += kSlotTile) win += ts.scan[i * 4];
+    win = wave_scan(win);
+    if ((threadIdx.x & 63u) == 63u) s_win[threadIdx.x >> 6] = win;
+    __syncthreads();
+    nw = 0;
+#pragma unroll
+    for (int i = 0; i < kSlotTile / 64; ++i) nw += s_win[i];
+  }
+  if (threadIdx.x != 0) return;
+  const uint32_t nb = min(nw, n_free), n = dr.n0 + nb;
+  eco_stats st = {};
+  v.n_births = nb;
+  v.n0 = dr.n0;
+  v.mean = dr.mean;
+  v.m2 = dr.m2;
+  v.n_live = n;
+  v.uid_next = dr.uid_next + nb;
+  v.step = dr.step + 1;
+  st.step = dr.step + 1;
+  st.population = n;
+  st.births = nb;
+  st.deaths = dr.count[PC_DEATHS];
+  st.killed = dr.count[PC_KILLED];
+  st.eaten = dr.count[PC_EATEN];
+  st.regrown = dr.regrown;
+  st.moves_ok = dr.count[PC_MOVES_OK];
+  st.moves_blocked = dr.count[PC_MOVES_BLOCKED];
+  st.births_blocked_cell = dr.count[PC_CLAIMS] - nw + dr.count[PC_BB_CELL];
+  st.births_blocked_capacity = nw - nb;
+  st.resource_total = dr.resource_total;
+  for (int a = 0; a < 9; ++a) st.action_hist[a] = dr.count[PC_HIST + a];
+  st.energy_total = (double)dr.energy;
+  st.trait_mean = n ? dr.mean : 0.0;
+  st.trait_var = n ? dr.m2 / (double)n : 0.0;
+  if (d.ep) {
+    st.water_total = dr.water;
+    st.biomass_total = dr.biomass;
+    st.hp_total = dr.hp + (unsigned long long)nb * (unsigned long long)d.ep[w].hp_child;
+  }
+  d.ring[(uint64_t)w * kStatsRing + (st.step % kStatsRing)] = st;
+}
+
+// The next step's live list of one slot tile: the survivors and the free slots
+// whose rank is below the world's births, in slot order (the live slots before the
+// tile are the slots that were not free there and the births among those that
+// were); the tile's flags, and its claim words released.
+__device__ __forceinline__ void live_tile(const Dev& d, const TileScratch& ts, uint32_t tile, bool ranked) {
+  constexpr int NW = kSlotTile / 64;
+  __shared__ uint32_t s_live[NW], s_free[NW], s_win[NW];
+  const int wave = threadIdx.x >> 6;
+  const Tile tl = slot_tile(ts, tile);
+  const uint32_t w = tl.world;
+  const uint32_t slot_off = slot_offset(d, ts, w), cell_off = cell_offset(d, ts, w);
+  const uint32_t free_before = ts.scan[tile * 4 + 2], n_free = d.wv[w].n_free, n_win = d.wv[w].n_win;
+  const bool summed = ts.cap0 && !ranked;
+  uint32_t win = 0;
+  if (summed)
+    for (uint32_t i = threadIdx.x; i < ts.n_slot_tiles; i += kSlotTile) win += ts.scan[i * 4];
+  const bool in = threadIdx.x < tl.count;
+  const uint32_t local = tl.start + threadIdx.x, slot = slot_off + local;
+  uint8_t fl = 0;
+  int t = 0;
+  if (in) {
+    fl = d.flags[slot];
+    t = d.tgt[slot];
+  }
+  const bool survivor = (fl & kAlive) != 0;
+  const uint64_t am = __ballot(survivor), fm = __ballot(in && !survivor);
+  win = wave_scan(win);
+  if ((threadIdx.x & 63u) == 63u) {
+    s_live[wave] = (uint32_t)__builtin_popcountll(am);
+    s_free[wave] = (uint32_t)__builtin_popcountll(fm);
+    s_win[wave] = win;
+  }
+  __syncthreads();
+  uint32_t surv = lanes_before(am), fr = free_before + lanes_before(fm), nw = summed ? 0u : n_win;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    if (i < wave) {
+      surv += s_live[i];
+      fr += s_free[i];
+    }
+    if (summed) nw += s_win[i];
+  }
+  const uint32_t nb = min(nw, n_free);
+  const bool alive = survivor || (in && fr < nb);
+  // live slots before this one: those of the earlier tiles, this tile's survivors, and
+  // the births with a smaller free rank
+  if (alive) d.live[slot_off + (tl.start - free_before) + surv + min(fr, nb)] = (int)local;
+  const uint8_t nf = alive ? kAlive : (uint8_t)0;
+  if (in && fl != nf) d.flags[slot] = nf;
+  if (fl & kBirthClaim) d.claim[cell_off + t] = 0xFFFFFFFFu;
+}
+
+// The last launch of a step.  The first blocks: the live list of a slot tile each,
+// then the record of a world each.  The other n_birth_blocks: births (persistent over all
+// worlds' births), as many blocks as are resident at once.  One block per child where
+// there are enough children to fill the chip, else 2^lgp blocks share a child, each a
+// part of its rows (child_split), so that few births do not take as long as one child
+// on four waves (a 1024 x 1024 world of 32,768 agents with 133,767 parameters and
+// 210 births a step: 153 to 83 us).  The children's state is placed apart from their
+// weights, a thread a birth.  A birth's parent is found from the tiles' winner counts
+// (prefix sums over 256 runs of tiles in LDS, then the tiles of the run), or
+// read from bparent where the small-world kernel has ranked the winners.
+// base: the first block's number (the two roles can be launched apart).
 template <int WDT, int H>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WDT == 0 ? 6 : 5))) void k_birth_commit(Dev d, Layout L) {
-  __shared__ uint32_t off[kMaxWorlds + 1];
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WDT == 0 ? 6 : 5)))
+void k_birth_commit(CommitArgs by_value) {
+  __shared__ uint32_t off[kMaxWorlds + 1], off_win[kMaxWorlds + 1];
+  __shared__ uint32_t run_win[256 + 1];
+  __shared__ uint32_t red[4];
   __shared__ uint32_t s_amax[128 + 128 + 16];
   __shared__ double s_red[4];
   __shared__ double2 tab[kTrigTable];
-  birth_offsets(d.wv, d.n_worlds, off);
-  const uint32_t total = off[d.n_worlds];
-  if (blockIdx.x >= total) return;   // no birth for this block (the whole launch, in a step without births)
-  load_trig(d.trig, tab);
-  for (uint32_t g = blockIdx.x; g < total; g += gridDim.x) {
-    const uint32_t w = find_world(off, d.n_worlds, g);
-    const WorldParams wp = d.wp[w];
-    commit_birth<WDT, H, 256>(d, L, w, wp, g - off[w], (uint32_t)d.wv[w].step, tab, s_amax, s_red);
+  static_assert(kTrigTable == 256, "one table entry per thread");
+  uint32_t first = blockIdx.x, lgp = 0;
+  {
+    const CommitArgs& a = args();
+    const uint32_t T = a.ts.n_slot_tiles, block = first + a.base;
+    if (block < T) {
+      live_tile(a.d, a.ts, block, a.ranked);
+      return;
+    }
+    if (block < T + a.d.n_worlds) {
+      world_record(a.d, a.ts, block - T, a.ranked);
+      return;
+    }
+    first = block - T - a.d.n_worlds;
+    if (a.ranked && births_of(a.d.wv[0]) == 0) return;
+    // the winners before each run of tiles, and the worlds' births
+    const bool summed = a.ts.cap0 && !a.ranked;
+    const uint32_t per = (T + 255) / 256;   // tiles per run
+    uint32_t own = 0;
+    if (!a.ranked)
+      for (uint32_t t = threadIdx.x * per; t < min((threadIdx.x + 1) * per, T); ++t) own += a.ts.scan[t * 4];
+    const uint32_t inc = wave_scan(own);
+    if ((threadIdx.x & 63u) == 63u) red[threadIdx.x >> 6] = inc;
+    if (!summed) birth_offsets(a.d.wv, a.d.n_worlds, off, off_win);
+    else __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+      if (i < threadIdx.x >> 6) before += red[i];
+      all += red[i];
+    }
+    const uint32_t total = summed ? min(all, a.d.wv[0].n_free) : off[a.d.n_worlds];
+    lgp = child_split(a.ts, H, total);
+    if (first >= (total << lgp) + (total + 255) / 256) return;   // nothing for this block (no block, without births)
+    run_win[threadIdx.x] = before + inc - own;
+    tab[threadIdx.x] = a.d.trig[threadIdx.x];
+    if (threadIdx.x == 255) {
+      run_win[256] = all;
+      if (summed) {
+        off[0] = off_win[0] = 0;
+        off[1] = total;
+        off_win[1] = all;
+      }
+    }
+    __syncthreads();
+  }
+  // items: 256 children's states each, then the children's parts
+  const uint32_t n_place = (off[args().d.n_worlds] + 255) / 256, n_items = n_place + (off[args().d.n_worlds] << lgp);
+  // the parent of the world's birth whose winner is number win of the object's
+  auto parent_of = [&](const CommitArgs& a, uint32_t slot_off, uint32_t k, uint32_t win) {
+    if (a.ranked) return (uint32_t)a.d.bparent[slot_off + k];
+    const uint32_t T = a.ts.n_slot_tiles, per = (T + 255) / 256;
+    const uint32_t r = find_world(run_win, 256, win), end = min((r + 1) * per, T);
+    uint32_t rem = win - run_win[r], t = r * per;   // its place among the run's
+    for (; t + 1 < end; ++t) {
+      const uint32_t c = a.ts.scan[t * 4];
+      if (rem < c) break;
+      rem -= c;
+    }
+    const uint32_t start = slot_tile(a.ts, t).start;
+    return start + (uint32_t)a.d.bparent[slot_off + start + rem];
+  };
+  auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  for (uint32_t i = first; i < n_items; i += args().n_birth_blocks) {
+    const CommitArgs& a = args();
+    const Dev& d = a.d;
+    if (i < n_place) {
+      const uint32_t g = i * 256 + threadIdx.x;
+      if (g < off[d.n_worlds]) {
+        const uint32_t w = find_world(off, d.n_worlds, g), k = g - off[w], slot_off = d.wp[w].slot_off;
+        place_child(d, w, k, parent_of(a, slot_off, k, off_win[w] + k), (uint32_t)d.freel[slot_off + k], tab);
+      }
+      continue;
+    }
+    const uint32_t j = i - n_place, g = j >> lgp, part = j & ((1u << lgp) - 1u);
+    const uint32_t w = uniform(find_world(off, d.n_worlds, g)), k = g - uniform(off[w]);
+    const WorldParams& wp = d.wp[w];
+    const uint32_t slot_off = wp.slot_off, child = slot_off + uniform((uint32_t)d.freel[slot_off + k]);
+    const uint32_t p_local = uniform(parent_of(a, slot_off, k, uniform(off_win[w]) + k));
+    const double t = mutate_part<WDT, H, 256>(child, slot_off + p_local, wp.sigma, wp.key0, wp.key1, p_local,
+                                              (uint32_t)d.draft[w].step, part_rows<H>(part, lgp), tab, s_amax, s_red);
+    if (threadIdx.x == 0) {
+      const CommitArgs& b = args();
+      if (lgp || b.ranked) b.ts.parts[j] = t;
+      if (!lgp) b.d.trait[child] = t;
+    }
   }
 }
 
@@ -1224,7 +1971,8 @@ __device__ __forceinline__ Moments block_merge_moments(Moments m, double (*red)[
   return t;  // valid in thread 0
 }
 
-// Compaction, pass 1 (slot tiles): live count, energy sum and the trait moments of
+// Live list and statistics of init and state writes (a step's are written by
+// k_birth_commit).  Pass 1 (slot tiles): live count, energy sum and the trait moments of
 // the tile (its mean, then the squared deviations from it: two passes over the
 // tile's values, which stay in registers).
 __global__ __launch_bounds__(kSlotTile) void k_compact_count(Dev d, TileScratch ts, int only_world) {
@@ -1273,147 +2021,14 @@ __global__ __launch_bounds__(kSlotTile) void k_compact_count(Dev d, TileScratch 
   }
 }
 
-// Window channels of every cell at the start of a step (Sec. 3.2 sensors, App. F
-// layout), one byte per cell: bit 0 agent present, bit 1 resource present, bit 2
-// wall (worlds with walls only), bits 3..5 the occupant's energy bin
-// min(floor(8 E / e_repro), 7), built at the end of each step (and of init and
-// state writes) for the next one.  The policy kernel's window gather then reads one
-// byte per cell instead of the occupancy, resource and wall arrays plus a
-// dependent read of each occupant's energy.  Threads take 4 consecutive cells
-// (cell_off and tile starts are multiples of 4); a ragged tail goes cell by cell.
-// The cell's resource and wall bits of its sense byte.
-__device__ __forceinline__ uint32_t cell_sense(const WorldParams& wp, uint32_t r, uint32_t wl) {
-  return (r != 0 ? 2u : 0u) | (wp.has_walls && wl != 0 ? 4u : 0u);
-}
-
-// An occupant's bits of the sense byte: the agent bit and its energy bin
-// (the number of b in 1..7 with 8 E >= b e_repro).
-__device__ __forceinline__ uint32_t agent_sense(const WorldParams& wp, int energy) {
-  const long long e8 = (long long)energy * 8;
-  uint32_t eb = 0;
-#pragma unroll
-  for (int b = 1; b < 8; ++b) eb += (e8 >= (long long)b * wp.e_repro) ? 1u : 0u;
-  return 1u | (eb << 3);
-}
-
-__device__ __forceinline__ uint32_t sense_of(const WorldParams& wp, const Dev& d, int o, uint32_t r, uint32_t wl) {
-  const uint32_t v = cell_sense(wp, r, wl);
-  return o >= 0 ? v | agent_sense(wp, d.energy[wp.slot_off + (uint32_t)o]) : v;
-}
-
-// Colour vision: the cell as others see it (occupant's colour, else a resource
-// unit in green, else a wall in grey, else black; 8 bits per channel), with the
-// cell's agent / resource / wall bits in the top byte for the move claim.
-// round(clamp(c, 0, 1) * 255) with ties up, in exact integer arithmetic: a c in
-// (0, 1) is M 2^-s with an integer M < 2^24 and s >= 24, so the result is
-// floor((255 M + 2^(s-1)) / 2^s).
-__device__ __forceinline__ uint32_t colour_byte(float c) {
-  if (!(c > 0.0f)) return 0u;   // also NaN
-  if (c >= 1.0f) return 255u;
-  const uint32_t u = __float_as_uint(c);
-  const uint32_t ex = u >> 23;   // c > 0: sign bit clear
-  const uint64_t M = ex ? ((u & 0x7FFFFFu) | 0x800000u) : (u & 0x7FFFFFu);
-  const int s = ex ? 150 - (int)ex : 149;   // c = M 2^-s, s >= 24
-  if (s >= 64) return 0u;
-  return (uint32_t)((255ull * M + (1ull << (s - 1))) >> s);
-}
-
-// col: the live agents' colour words by local slot, if the caller has them in LDS
-// (else read from the colour trait).
-__device__ __forceinline__ uint32_t colour_word(const float4 c) {
-  return colour_byte(c.x) | (colour_byte(c.y) << 8) | (colour_byte(c.z) << 16);
-}
-
-__device__ __forceinline__ void cell_render_tile(const Dev& d, const Tile tl, const uint32_t* col = nullptr) {
-  const WorldParams wp = d.wp[tl.world];
-  for (uint32_t i = threadIdx.x; i < tl.count; i += blockDim.x) {
-    const uint32_t cell = wp.cell_off + tl.start + i;
-    const int o = d.occ[cell];
-    const bool r = d.res[cell] != 0, wl = wp.has_walls && d.wall[cell] != 0;
-    uint32_t q = 0u;
-    if (o >= 0) {
-      q = col ? col[o] : colour_word(d.colour[wp.slot_off + (uint32_t)o]);
-    } else if (r) {
-      q = 255u << 8;
-    } else if (wl) {
-      q = 0x808080u;
-    }
-    d.rgb[cell] = q | (((o >= 0 ? 1u : 0u) | (r ? 2u : 0u) | (wl ? 4u : 0u)) << 24);
-  }
-}
-
-// Ecology: the cell's water, energy and biomass levels (capped at 255), or with
-// colour vision the cell as others see it (occupant's colour, wall grey, else
-// energy / biomass / water as red / green / blue); the agent / wall bits and the
-// rock height in the top byte.  flowed != 0 (the end of a step with terrain):
-// first take the water the step's flow left on the cell.  Four consecutive cells
-// per thread and pass, their loads issued together.
-__device__ __forceinline__ uint32_t sat255(int v) { return (uint32_t)min(max(v, 0), 255); }
-
-__device__ __forceinline__ void cell_ecology_tile(const Dev& d, const WorldParams& wp, const Tile tl, int flowed,
-                                                  const uint32_t* col = nullptr) {
-  for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
-    const uint32_t n = min(4u, tl.count - i), g = wp.cell_off + tl.start + i;
-    int wv[4], o[4], ce[4], cb[4], rk[4] = {0, 0, 0, 0};
-    const bool copy_back = flowed && d.rock;
-    load_cells4((copy_back ? d.cw_next : d.cw) + g, wv);
-    load_cells4(d.occ + g, o);
-#pragma unroll
-    for (uint32_t j = 0; j < 4; ++j)
-      if (j >= n) o[j] = -1;   // past a ragged tail: no occupant read
-    load_cells4(d.ce + g, ce);
-    load_cells4(d.cb + g, cb);
-    if (d.rock) load_cells4(d.rock + g, rk);
-    const uint32_t wl4 = wp.has_walls ? *reinterpret_cast<const uint32_t*>(d.wall + g) : 0u;
-    if (copy_back) store_cells4(d.cw + g, n, wv);   // after every load of the group is issued
-    uint32_t q[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const bool wl = ((wl4 >> (8 * j)) & 0xFFu) != 0;
-      if (!d.colour) {
-        q[j] = sat255(wv[j]) | (sat255(ce[j]) << 8) | (sat255(cb[j]) << 16);
-      } else if (o[j] >= 0) {
-        q[j] = col ? col[o[j]] : colour_word(d.colour[wp.slot_off + (uint32_t)o[j]]);
-      } else if (wl) {
-        q[j] = 0x808080u;
-      } else {
-        q[j] = sat255(16 * min(ce[j], 1 << 20)) | (sat255(64 * min(cb[j], 1 << 20)) << 8) |
-               (sat255(16 * min(wv[j], 1 << 20)) << 16);
-      }
-      q[j] |= ((o[j] >= 0 ? 1u : 0u) | (wl ? 4u : 0u) | ((uint32_t)rk[j] << 3)) << 24;
-    }
-    store_cells4(reinterpret_cast<int32_t*>(d.rgb + g), n, reinterpret_cast<const int*>(q));
-  }
-}
-
-__device__ __forceinline__ void cell_sense_tile(const Dev& d, const Tile tl) {
-  const WorldParams wp = d.wp[tl.world];
-  for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
-    const uint32_t cell = wp.cell_off + tl.start + i;
-    if (i + 4 <= tl.count) {
-      const int4 o = *reinterpret_cast<const int4*>(d.occ + cell);
-      const uint32_t r = *reinterpret_cast<const uint32_t*>(d.res + cell);
-      const uint32_t wl = *reinterpret_cast<const uint32_t*>(d.wall + cell);
-      const uint32_t v = sense_of(wp, d, o.x, r & 0xFFu, wl & 0xFFu) | sense_of(wp, d, o.y, (r >> 8) & 0xFFu, (wl >> 8) & 0xFFu) << 8 |
-                         sense_of(wp, d, o.z, (r >> 16) & 0xFFu, (wl >> 16) & 0xFFu) << 16 |
-                         sense_of(wp, d, o.w, r >> 24, wl >> 24) << 24;
-      *reinterpret_cast<uint32_t*>(d.sense + cell) = v;
-    } else {
-      for (uint32_t c = cell; c < wp.cell_off + tl.start + tl.count; ++c)
-        d.sense[c] = (uint8_t)sense_of(wp, d, d.occ[c], d.res[c], d.wall[c]);
-    }
-  }
-}
-
-// The step's statistics record of world w once its compaction counts are in
-// (pass 1), and the clock advance unless init != 0 (init / state writes).  Run
-// by the block of the world's last slot tile (NT threads).
+// The statistics record of world w as it stands once pass 1's counts are in (run by
+// the block of the world's last slot tile, NT threads); the grid totals come from
+// k_resource_total.
 template <int NT>
-__device__ void world_finalize(const Dev& d, const TileScratch& ts, uint32_t w, int init) {
+__device__ void world_finalize(const Dev& d, const TileScratch& ts, uint32_t w) {
   __shared__ uint32_t red[NT / 64 + 1];
   __shared__ unsigned long long red64[NT / 64];
   __shared__ double redm[NT / 64][3];
-  __shared__ unsigned long long s_cnt[kSlotPart + kCellPart];
   const uint32_t t0 = ts.tile_rng[4 * w], t1 = ts.tile_rng[4 * w + 1];
   const uint32_t nt = t1 - t0;
   const uint32_t per = (nt + NT - 1) / NT;
@@ -1431,71 +2046,16 @@ __device__ void world_finalize(const Dev& d, const TileScratch& ts, uint32_t w, 
   block_exscan<NT>(n, red, &N);
   const unsigned long long E = block_sum_u64<NT>((unsigned long long)es, red64);
   const Moments TM = block_merge_moments<NT>(tm, redm);
-  unsigned long long eco_w = 0, eco_b = 0, eco_h = 0;   // ecology: carried water, biomass, health
+  unsigned long long eco_h = 0;   // ecology: health
   if (d.ep) {
-    unsigned long long a = 0, b = 0, c = 0;
-    for (uint32_t t = lo; t < hi; ++t) {
-      a += ts.ecosum[3 * t];
-      b += ts.ecosum[3 * t + 1];
-      c += ts.ecosum[3 * t + 2];
-    }
-    eco_w = block_sum_u64<NT>(a, red64);
-    eco_b = block_sum_u64<NT>(b, red64);
+    unsigned long long c = 0;
+    for (uint32_t t = lo; t < hi; ++t) c += ts.ecosum[3 * t + 2];
     eco_h = block_sum_u64<NT>(c, red64);
   }
-  if (threadIdx.x < kSlotPart + kCellPart) s_cnt[threadIdx.x] = 0;
-  __syncthreads();
-  if (!init) {
-    // per-thread sums over its tiles, then wave sums, then one LDS add per wave
-    // (slot counters count agents, below 2^31 per world; the grid totals are u64)
-    uint32_t c[kSlotPart];
-    unsigned long long cc[kCellPart];
-#pragma unroll
-    for (int k = 0; k < kSlotPart; ++k) c[k] = 0;
-#pragma unroll
-    for (int k = 0; k < kCellPart; ++k) cc[k] = 0;
-    for (uint32_t t = lo; t < hi; ++t)
-#pragma unroll
-      for (int k = 0; k < kSlotPart; ++k) c[k] += ts.part_slot[t * kSlotPart + k];
-    const uint32_t ct0 = ts.tile_rng[4 * w + 2], ct1 = ts.tile_rng[4 * w + 3];
-    for (uint32_t t = ct0 + threadIdx.x; t < ct1; t += NT)
-#pragma unroll
-      for (int k = 0; k < kCellPart; ++k) cc[k] += ts.part_cell[t * kCellPart + k];
-#pragma unroll
-    for (int k = 0; k < kSlotPart; ++k) c[k] = wave_scan(c[k]);
-#pragma unroll
-    for (int k = 0; k < kCellPart; ++k) cc[k] = wave_scan(cc[k]);
-    if ((threadIdx.x & 63) == 63) {
-#pragma unroll
-      for (int k = 0; k < kSlotPart; ++k) atomicAdd(&s_cnt[k], (unsigned long long)c[k]);
-#pragma unroll
-      for (int k = 0; k < kCellPart; ++k) atomicAdd(&s_cnt[kSlotPart + k], cc[k]);
-    }
-  }
-  __syncthreads();
   if (threadIdx.x == 0) {
     WorldVar& v = d.wv[w];
     eco_stats st = {};
-    if (!init) {
-      v.step += 1;
-      v.uid_next += v.n_births;
-      st.births = d.cnt[w].births;
-      st.births_blocked_cell = d.cnt[w].births_blocked_cell + s_cnt[PC_BB_CELL];
-      st.births_blocked_capacity = d.cnt[w].births_blocked_capacity;
-      st.deaths = s_cnt[PC_DEATHS];
-      st.killed = s_cnt[PC_KILLED];
-      st.eaten = s_cnt[PC_EATEN];
-      st.moves_ok = s_cnt[PC_MOVES_OK];
-      st.moves_blocked = s_cnt[PC_MOVES_BLOCKED];
-      for (int a = 0; a < 9; ++a) st.action_hist[a] = s_cnt[PC_HIST + a];
-      st.regrown = s_cnt[kSlotPart + 0];
-      st.resource_total = s_cnt[kSlotPart + 1];
-      if (d.ep) {
-        st.water_total = eco_w + s_cnt[kSlotPart + 2];
-        st.biomass_total = eco_b + s_cnt[kSlotPart + 3];
-      }
-    }
-    if (d.ep) st.hp_total = eco_h;   // (init records get the grid parts from k_resource_total)
+    if (d.ep) st.hp_total = eco_h;
     v.n_live = N;
     st.step = v.step;
     st.population = N;
@@ -1506,22 +2066,32 @@ __device__ void world_finalize(const Dev& d, const TileScratch& ts, uint32_t w, 
   }
 }
 
-// Compaction, pass 2.  Slot-tile blocks: the tile's live slots at their
+// Sum over the tiles [lo, hi) of scan[t][c]; all threads of the block get the sum.
+template <int NT>
+__device__ __forceinline__ uint32_t tiles_sum(const TileScratch& ts, uint32_t lo, uint32_t hi, int c,
+                                              unsigned long long* red64, uint32_t* bcast) {
+  uint32_t v = 0;
+  for (uint32_t t = lo + threadIdx.x; t < hi; t += NT) v += ts.scan[t * 4 + c];
+  const unsigned long long tot = block_sum_u64<NT>(v, red64);
+  if (threadIdx.x == 0) *bcast = (uint32_t)tot;
+  __syncthreads();
+  const uint32_t r = *bcast;
+  __syncthreads();
+  return r;
+}
+
+// Pass 2.  Slot-tile blocks: the tile's live slots at their
 // offsets in the world's live list (offset = live counts of the world's earlier
-// tiles, summed here); the world's last tile also writes the step's statistics.
-// Blocks past the slot tiles build the sense bytes of one cell tile each for the
-// next step (the grid is final here).  only_world >= 0 restricts both parts.
-__global__ __launch_bounds__(kSlotTile) void k_compact_write(Dev d, TileScratch ts, int init, int only_world) {
+// tiles, summed here); the world's last tile also writes the statistics record.
+// Blocks past the slot tiles build the window channels of one cell tile each.
+// only_world >= 0 restricts both parts.
+__global__ __launch_bounds__(kSlotTile) void k_compact_write(Dev d, TileScratch ts, int only_world) {
   __shared__ uint32_t red[kSlotTile / 64 + 1];
   __shared__ unsigned long long red64[kSlotTile / 64];
   __shared__ uint32_t bcast;
   if (blockIdx.x >= ts.n_slot_tiles) {
     const Tile ct = ts.cell_tiles[blockIdx.x - ts.n_slot_tiles];
-    if (only_world < 0 || (int)ct.world == only_world) {
-      if (d.ep) cell_ecology_tile(d, d.wp[ct.world], ct, !init);
-      else if (d.rgb) cell_render_tile(d, ct);
-      else cell_sense_tile(d, ct);
-    }
+    if (only_world < 0 || (int)ct.world == only_world) window_cells(d, ct);
     return;
   }
   const Tile tl = ts.slot_tiles[blockIdx.x];
@@ -1536,54 +2106,53 @@ __global__ __launch_bounds__(kSlotTile) void k_compact_write(Dev d, TileScratch 
   uint32_t tot;
   const uint32_t r = ol + block_exscan<kSlotTile>(alive ? 1u : 0u, red, &tot);
   if (alive) d.live[wp.slot_off + r] = (int)local;
-  if (blockIdx.x + 1 == t1) world_finalize<kSlotTile>(d, ts, w, init);
+  if (blockIdx.x + 1 == t1) world_finalize<kSlotTile>(d, ts, w);
 }
 
 // ---------------------------------------------------------------------------
-// The step after the policy kernel for an object of one small world, in one
-// block: moves, eating, costs and deaths, birth claims and regrowth (the
-// ecology: photosynthesis, and with terrain the water's flow), the birth
-// ranking, the births, the next live list with the statistics record, and the
-// next step's window channels (the same per-agent and per-cell rules as the
-// kernels above, with the world's scans done inside the block).  A small world's
-// step is bound by the latency of its launches, and this replaces seven
-// dependent launches by one.  A thread scans a contiguous range of slots, so
-// every scan is one block-wide exclusive sum.  ECO: the world has the ecology
-// (d.ep set); the single-resource instantiation carries none of the ecology's
-// phases (behind a run-time test they made its step measurably slower).
+// The moves, claims, cell pass and ranking of a step for an object of one small
+// world, in one block: the phases of k_move, k_claim_cells and k_birth_rank with the
+// world's scans done inside the block, before the same last launch (k_birth_commit:
+// births, live list, record).  A small world's step is bound by the latency of its
+// launches, and this replaces three dependent launches by one.  A thread scans a
+// contiguous range of slots, so every scan is one block-wide exclusive sum.  ECO: the
+// world has the ecology (d.ep set); the single-resource instantiation carries none of
+// the ecology's phases (behind a run-time test they made its step measurably slower).
 // ---------------------------------------------------------------------------
-template <int WDT, int H, bool ECO>
-__global__ __launch_bounds__(1024) void k_step_small(Dev d, Layout L, uint32_t n_actions) {
+template <bool ECO>
+__global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint32_t n_actions, uint32_t H) {
   // threads; slots or cells per thread in one pass (one 4-byte load of bytes); passes over
   // the slots (the capacity is at most NT CH NP)
-  constexpr int NT = 1024, CH = 4, NP = 2;
+  constexpr int NT = 1024, CH = 4, NP = 2, NW = NT / 64;
   static_assert(NT * CH * NP == ECO_SMALL_STEP_MAX_SLOTS, "the slot passes cover the largest object taken");
+  static_assert(64 * CH == kSlotTile, "one wave's slots of a pass are one slot tile");
+  if (blockIdx.x == 1) {   // the second block completes the last step's record from the blocks' shares
+    settle_record<NT, false>(d, ts, 0, H, true);
+    return;
+  }
   __shared__ uint32_t cnt[kSlotPart];              // step counters (PC_*)
   __shared__ unsigned long long ccnt[kCellPart];   // regrown units, resource total (the ecology: grid energy), grid water, biomass
-  __shared__ uint32_t blocked, any_claim;
-  __shared__ unsigned long long rank_red[NT / 64];   // the ranking scan's wave totals
-  __shared__ uint32_t live_red[NT / 64];             // the live list's wave counts
-  __shared__ unsigned long long red64[NT / 64];      // the waves' energy sums
-  __shared__ double m2_red[NT / 64];                 // the waves' sums of squared deviations
-  __shared__ unsigned long long eco_red[3][NT / 64];  // the ecology: the waves' carried water, biomass, health
-  __shared__ uint32_t s_amax[128 + 128 + 16];
-  __shared__ double s_red[NT / 64];                  // the births' reductions, then the waves' trait sums
-  __shared__ double2 tab[kTrigTable];
-  // per cell: the agent bit and energy bin of its occupant after the step (0: none),
-  // written from the live slots, read by the window-channel pass
+  __shared__ uint32_t any_claim;
+  __shared__ unsigned long long rank_red[NW];        // the ranking scan's wave totals
+  __shared__ uint32_t live_red[NW];                  // the waves' survivors
+  __shared__ unsigned long long red64[NW];           // the waves' energy sums
+  __shared__ double mean_red[NW], m2_red[NW];        // the waves' trait means and sums of squared deviations
+  __shared__ unsigned long long eco_red[3][NW];      // the ecology: the waves' carried water, biomass, health
+  // per cell: the agent bit and energy bin of its occupant after the moves (0: none),
+  // written by the agents, read by the cell pass
   __shared__ __align__(16) uint8_t s_agent[ECO_SMALL_STEP_MAX_CELLS];
-  // colour vision: the live agents' colour words by slot, written from the live
-  // slots, read by the window-word pass (no occupant-then-colour lookup chain)
+  // colour vision: the surviving agents' colour words by slot, written by the agents,
+  // read by the cell pass (no occupant-then-colour lookup chain)
   __shared__ uint32_t s_col[ECO_SMALL_STEP_MAX_SLOTS];
   const uint32_t tid = threadIdx.x;
+  const int lane = (int)(tid & 63u), wave = (int)(tid >> 6);
   // live-list entry tid, loaded together with the world's live count: the
   // thread's only agent when there are at most NT (the object's one world
   // starts at slot 0; the list's allocation holds total_slots entries)
   const int32_t live_tid = d.live[min(tid, d.total_slots - 1u)];
   if (tid < kSlotPart) cnt[tid] = 0;
   if (tid < kCellPart) ccnt[tid] = 0;
-  if (tid == 0) blocked = any_claim = 0;
-  __syncthreads();
+  if (tid == 0) any_claim = 0;
   constexpr uint32_t w = 0;
   const WorldParams wp = d.wp[w];
   const uint32_t step = (uint32_t)d.wv[w].step, n_live = d.wv[w].n_live, cap = wp.cap, cells = wp.cells;
@@ -1591,290 +2160,176 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, Layout L, uint32_t n
   // each thread's contiguous range of the live list
   const uint32_t per_l = (n_live + NT - 1) / NT;
   const uint32_t l0 = min(tid * per_l, n_live), l1 = min(l0 + per_l, n_live);
-  // the flag bytes of slots b0 .. b0 + 3 (slot and cell ranges start at multiples of
-  // 64 and their allocations end at one, so these 4-byte loads stay inside)
-  auto flags4 = [&](uint32_t b0) { return *reinterpret_cast<const uint32_t*>(d.flags + wp.slot_off + b0); };
   const bool sense_bytes = d.rgb == nullptr;   // window channels as sense bytes (else rendered words)
   if (sense_bytes)
     for (uint32_t c0 = tid * 16; c0 < cells; c0 += NT * 16) *reinterpret_cast<uint4*>(s_agent + c0) = make_uint4(0, 0, 0, 0);
+  __syncthreads();
 
+  // the traits of the last step's children
+  const uint32_t n_children = d.wv[w].n_births;
+  if (n_children) {
+    const uint32_t lgp = child_split(ts, H, n_children);
+    for (uint32_t k = tid; k < n_children; k += NT)
+      d.trait[wp.slot_off + (uint32_t)d.freel[wp.slot_off + k]] = child_trait(d, ts, lgp, true, k, 0u);
+  }
   // 1. moves, eating, costs and deaths of the step's live agents
   for (uint32_t i = l0; i < l1; ++i) {
-    const uint32_t local = (uint32_t)(i == tid ? live_tid : live[i]);
-    move_agent(d, wp, w, wp.slot_off + local, local, step + 1u, cnt);
+    const uint32_t local = (uint32_t)(i == tid ? live_tid : live[i]), slot = wp.slot_off + local;
+    const int a = d.act[slot], pos = d.pos[slot], t = d.tgt[slot], E = d.energy[slot];
+    float4 cv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (d.colour) cv = d.colour[slot];
+    const Moved m = move_agent(d, wp, w, slot, local, step + 1u, a, pos, t, E, cnt);
+    if (m.alive) {
+      if (sense_bytes) s_agent[m.cell] = (uint8_t)agent_sense(wp, m.energy);   // one agent per cell
+      if (d.colour) s_col[local] = colour_word(cv);
+    }
   }
   __syncthreads();
-  // 2. birth claims of the agents still alive; regrowth of every cell (4 per thread and pass)
-  bool claimed = false;
-  for (uint32_t i = l0; i < l1; ++i) claimed |= birth_claim_slot(d, wp, w, wp.slot_off + (uint32_t)live[i], n_actions, &blocked);
-  if (claimed) any_claim = 1u;   // the same value from every claimant
-  if constexpr (ECO) {   // the ecology: photosynthesis, strikes cleared, the flow gather; the grid totals
-    unsigned long long grown = 0, total = 0, wsum = 0, bsum = 0;
-    ecology_cells(d, wp, d.ep[w], Tile{w, 0u, cells, 0u}, step, grown, total, wsum, bsum);
-    wave_add_u64(grown, &ccnt[0]);
-    wave_add_u64(total, &ccnt[1]);
-    wave_add_u64(wsum, &ccnt[2]);
-    wave_add_u64(bsum, &ccnt[3]);
-  } else {
-    unsigned long long grown = 0, total = 0;
-    for (uint32_t c0 = tid * CH; c0 < cells; c0 += NT * CH) {
-      uint32_t* rp = reinterpret_cast<uint32_t*>(d.res + wp.cell_off + c0);
-      const uint32_t v = *rp;
-      const uint32_t nv = regrow_word(wp, c0, min((uint32_t)CH, cells - c0), v, step, grown, total);
-      if (nv != v) *rp = nv;
-    }
-    wave_add_u64(grown, &ccnt[0]);
-    wave_add_u64(total, &ccnt[1]);
-  }
-  __syncthreads();
-  // 3. birth ranking, when any parent claimed a cell: the claim winners in slot
-  // order (the live list's order) and the free slots in ascending order (the
-  // recycled-slot free list; only its first Wn entries are used), both ranked by
-  // one block scan of 16-bit counts packed in a u64 (winners, free slots of each
-  // pass, claims; no field carries into the next: every total is at most 8,192).
-  // The claimed cells are released right after the ranking, the claim flags by the
-  // last pass over the slots.
-  uint32_t Wn = 0, claims = 0, nb = 0;
-  if (any_claim) {   // the same in every thread (written before the barrier above)
-    uint32_t nw = 0, nc = 0;
-    for (uint32_t i = l0; i < l1; ++i) {
-      const uint32_t slot = wp.slot_off + (uint32_t)live[i];
-      if (d.flags[slot] & kBirthClaim) {
-        ++nc;
-        if (d.claim[wp.cell_off + d.tgt[slot]] == slot) ++nw;
-      }
-    }
-    uint32_t fm[NP];
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const uint32_t b0 = (p * NT + tid) * CH;
-      fm[p] = 0;
-      if (b0 < cap) {
-        const uint32_t v = flags4(b0);
-#pragma unroll
-        for (int j = 0; j < CH; ++j)
-          if (b0 + j < cap && !((v >> (8 * j)) & kAlive)) fm[p] |= 1u << j;
-      }
-    }
-    static_assert(NP == 2, "the packed ranking scan holds two passes of free slots");
-    unsigned long long rtot;
-    const unsigned long long rex =
-        block_exscan_u64<NT>((unsigned long long)nw | (unsigned long long)__builtin_popcount(fm[0]) << 16 |
-                                 (unsigned long long)__builtin_popcount(fm[1]) << 32 | (unsigned long long)nc << 48,
-                             rank_red, &rtot);
-    Wn = (uint32_t)(rtot & 0xFFFFu);
-    claims = (uint32_t)(rtot >> 48);
-    uint32_t k = (uint32_t)(rex & 0xFFFFu);
-    for (uint32_t i = l0; i < l1 && nw; ++i) {
-      const uint32_t local = (uint32_t)live[i], slot = wp.slot_off + local;
-      if ((d.flags[slot] & kBirthClaim) && d.claim[wp.cell_off + d.tgt[slot]] == slot) d.bparent[wp.slot_off + k++] = (int)local;
-    }
-    uint32_t F = 0;
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const uint32_t b0 = (p * NT + tid) * CH;
-      uint32_t f = F + (uint32_t)((rex >> (16 * (p + 1))) & 0xFFFFu);
-      for (uint32_t m = fm[p]; m && f < Wn; m &= m - 1) d.freel[wp.slot_off + f++] = (int)(b0 + __builtin_ctz(m));
-      F += (uint32_t)((rtot >> (16 * (p + 1))) & 0xFFFFu);
-    }
-    nb = min(Wn, F);
-    __syncthreads();
-    // the claimed cells released (every claimant has read its cell's claim word;
-    // the movers' winners released theirs in the move phase)
-    for (uint32_t i = l0; i < l1; ++i) {
-      const uint32_t slot = wp.slot_off + (uint32_t)live[i];
-      if (d.flags[slot] & kBirthClaim) d.claim[wp.cell_off + d.tgt[slot]] = 0xFFFFFFFFu;
-    }
-  }
-  // 4. the births, one at a time (the angle table of the mutation noise only when there are any)
-  if (nb) load_trig(d.trig, tab);
-  for (uint32_t b = 0; b < nb; ++b) commit_birth<WDT, H, NT>(d, L, w, wp, b, step, tab, s_amax, s_red);
-  // 5. the next step's live list and the statistics record: energy exact in
-  // integers, the trait moments of each wave in two passes over the values held
-  // in registers, merged across waves.  One barrier gives every wave its offsets
-  // in the live list (both passes' counts packed in a u32) and thread 0 the
-  // waves' energy sums and trait moments.
+  // 2. birth claims of the agents still alive with their sums (count, energy, what they
+  // carry, and the trait mean and sum of squared deviations by Welford's update), and
+  // the cell pass
+  uint32_t nc = 0, nblk = 0, n_t = 0;
   long long es = 0;
-  double t[NP][CH], s1 = 0.0;
-  uint32_t am[NP];
+  double mean_t = 0.0, m2_t = 0.0;
+  unsigned long long eco_w[3] = {0, 0, 0};
+  for (uint32_t i = l0; i < l1; ++i) {
+    const uint32_t slot = wp.slot_off + (uint32_t)(i == tid ? live_tid : live[i]);
+    const uint8_t fl = d.flags[slot];
+    const int act = d.act[slot], pos = d.pos[slot], facing = d.facing[slot], energy = d.energy[slot];
+    const int water = ECO ? d.water[slot] : 0, biomass = ECO ? d.biomass[slot] : 0, hp = ECO ? d.hp[slot] : 0;
+    const double trait = d.trait[slot];
+    if (!(fl & kAlive)) continue;
+    ++n_t;
+    es += energy;
+    const double dv = trait - mean_t;
+    if (n_t == 1) {
+      mean_t = trait;
+    } else {
+      mean_t += dv / (double)n_t;
+      m2_t += dv * (trait - mean_t);
+    }
+    if constexpr (ECO) {
+      eco_w[0] += (unsigned long long)water;
+      eco_w[1] += (unsigned long long)biomass;
+      eco_w[2] += (unsigned long long)hp;
+    }
+    const int r = birth_claim_agent(d, wp, w, slot, n_actions, fl, act, pos, facing, energy, water, biomass);
+    nc += r == 1 ? 1u : 0u;
+    nblk += r == 2 ? 1u : 0u;
+  }
+  if (nc) any_claim = 1u;   // the same value from every claimant
+  const uint32_t both = wave_scan(nc | nblk << 16);   // at most 8,192 each
+  if (lane == 63 && both) {
+    atomicAdd(&cnt[PC_CLAIMS], both & 0xFFFFu);
+    atomicAdd(&cnt[PC_BB_CELL], both >> 16);
+  }
+  const Tile all{w, 0u, cells, 0u};
+  if constexpr (ECO) ecology_cells<true>(d, wp, d.ep[w], all, step, ccnt, s_col);
+  else plain_cells<true>(d, wp, all, step, ccnt, s_agent, s_col);
+  // the waves' sums (whole waves without agents have none), combined below
+  {
+    const uint32_t n_w = lane_value(wave_scan(n_t), 63);
+    double mean_w = 0.0, m2_w = 0.0;
+    unsigned long long ew = 0;
+    if (n_w) {
+      mean_w = lane_value(wave_scan((double)n_t * mean_t), 63) / (double)n_w;
+      m2_w = wave_scan(m2_t + (double)n_t * (mean_t - mean_w) * (mean_t - mean_w));
+      ew = wave_scan((unsigned long long)es);
+      if constexpr (ECO) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) eco_w[k] = wave_scan(eco_w[k]);
+      }
+    }
+    if (lane == 63) {
+      live_red[wave] = n_w;
+      red64[wave] = ew;
+      mean_red[wave] = mean_w;
+      m2_red[wave] = m2_w;
+      if constexpr (ECO) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) eco_red[k][wave] = eco_w[k];
+      }
+    }
+  }
+  __syncthreads();
+  if (ECO && d.rock) settle_water(d, wp, all);
+  // 3. the free slots; a wave's 256 slots of a pass are a slot tile
+  uint32_t fm[NP];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const uint32_t b0 = (p * NT + tid) * CH;
-    am[p] = 0;
+    fm[p] = 0;
     if (b0 < cap) {
-      const uint32_t v = flags4(b0);
+      const uint32_t v = *reinterpret_cast<const uint32_t*>(d.flags + wp.slot_off + b0);
 #pragma unroll
       for (int j = 0; j < CH; ++j)
-        if (b0 + j < cap && ((v >> (8 * j)) & kAlive)) am[p] |= 1u << j;
-      // the step's birth-claim flags cleared (a flag byte is 0 or alive, after the step)
-      constexpr uint32_t claim_bits = 0x01010101u * (kBirthClaim | kBirthWon);
-      if (v & claim_bits) *reinterpret_cast<uint32_t*>(d.flags + wp.slot_off + b0) = v & ~claim_bits;
-    }
-    // the four slots' traits and energies in 16-byte loads, whether alive or not
-    // (they lie inside the allocations, which end at a multiple of 64 slots)
-    static_assert(CH == 4, "one 16-byte load of energies per pass");
-    double2 tv[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
-    int4 ev = make_int4(0, 0, 0, 0), pv = make_int4(0, 0, 0, 0);
-    if (b0 < cap) {
-      tv[0] = *reinterpret_cast<const double2*>(d.trait + wp.slot_off + b0);
-      tv[1] = *reinterpret_cast<const double2*>(d.trait + wp.slot_off + b0 + 2);
-      ev = *reinterpret_cast<const int4*>(d.energy + wp.slot_off + b0);
-      if (sense_bytes) pv = *reinterpret_cast<const int4*>(d.pos + wp.slot_off + b0);
-    }
-    float4 cv[4];
-    if (d.colour && b0 < cap) {
-#pragma unroll
-      for (int j = 0; j < CH; ++j) cv[j] = d.colour[wp.slot_off + b0 + j];
-    }
-    const double tj[4] = {tv[0].x, tv[0].y, tv[1].x, tv[1].y};
-    const int ej[4] = {ev.x, ev.y, ev.z, ev.w}, pj[4] = {pv.x, pv.y, pv.z, pv.w};
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      const bool on = (am[p] >> j) & 1u;
-      t[p][j] = on ? tj[j] : 0.0;
-      es += on ? ej[j] : 0;
-      if (sense_bytes && on) s_agent[pj[j]] = (uint8_t)agent_sense(wp, ej[j]);   // one agent per cell
-      if (d.colour && on) s_col[b0 + j] = colour_word(cv[j]);
-    }
-
-#pragma unroll
-    for (int j = 0; j < CH; ++j) s1 += t[p][j];
-  }
-  const int lane = (int)(tid & 63u), wave = (int)(tid >> 6);
-  const uint32_t own = (uint32_t)__builtin_popcount(am[0]) | (uint32_t)__builtin_popcount(am[1]) << 16;
-  const uint32_t inc = wave_scan(own);
-  const unsigned long long ew = wave_scan((unsigned long long)es);
-  // the wave's trait moments in two passes over its values: count, mean, and the
-  // sum of squared deviations from that mean (merged across waves by thread 0)
-  const uint32_t wc = lane_value(inc, 63);
-  const double n_w = (double)((wc & 0xFFFFu) + (wc >> 16));
-  const double mean_w = n_w > 0.0 ? lane_value(wave_scan(s1), 63) / n_w : 0.0;
-  double m2 = 0.0;
-#pragma unroll
-  for (int p = 0; p < NP; ++p)
-#pragma unroll
-    for (int j = 0; j < CH; ++j)
-      if ((am[p] >> j) & 1u) m2 += (t[p][j] - mean_w) * (t[p][j] - mean_w);
-  m2 = wave_scan(m2);
-  // the ecology: water, biomass and health carried by the live agents (after the
-  // trait values are no longer needed)
-  unsigned long long eco_w[3] = {0, 0, 0};
-  if constexpr (ECO) {
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const uint32_t b0 = (p * NT + tid) * CH;
-      if (b0 < cap) {
-        const int4 wv4 = *reinterpret_cast<const int4*>(d.water + wp.slot_off + b0);
-        const int4 bv4 = *reinterpret_cast<const int4*>(d.biomass + wp.slot_off + b0);
-        const int4 hv4 = *reinterpret_cast<const int4*>(d.hp + wp.slot_off + b0);
-        const int wj[4] = {wv4.x, wv4.y, wv4.z, wv4.w}, bj[4] = {bv4.x, bv4.y, bv4.z, bv4.w},
-                  hj[4] = {hv4.x, hv4.y, hv4.z, hv4.w};
-#pragma unroll
-        for (int j = 0; j < CH; ++j)
-          if ((am[p] >> j) & 1u) {
-            eco_w[0] += (unsigned long long)wj[j];
-            eco_w[1] += (unsigned long long)bj[j];
-            eco_w[2] += (unsigned long long)hj[j];
-          }
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) eco_w[k] = wave_scan(eco_w[k]);
-  }
-  if (lane == 63) {
-    live_red[wave] = inc;
-    red64[wave] = ew;
-    s_red[wave] = mean_w;
-    m2_red[wave] = m2;
-    if constexpr (ECO) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) eco_red[k][wave] = eco_w[k];
+        if (b0 + j < cap && !((v >> (8 * j)) & kAlive)) fm[p] |= 1u << j;
     }
   }
-  __syncthreads();
-  // each wave's offsets in the live list (the waves' counts added the same way in
-  // every wave, lane i reading wave i's)
-  uint32_t ntot;
-  const uint32_t before = waves_before<NT / 64>(lane < NT / 64 ? live_red[lane] : 0u, &ntot);
-  const uint32_t N0 = ntot & 0xFFFFu, N = N0 + (ntot >> 16);
-  const uint32_t ex = before + inc - own;
+  // 4. ranking: the claim winners in slot order (the live list's order) and the free
+  // slots in ascending order (the recycled-slot free list; only its first Wn entries
+  // are used), both ranked by one block scan of 16-bit counts packed in a u64
+  // (winners, free slots of each pass; no field carries into the next: every total is
+  // at most 8,192).
+  uint32_t nw = 0;
+  if (any_claim)   // the same in every thread (written before the barrier above)
+    for (uint32_t i = l0; i < l1; ++i) {
+      const uint32_t slot = wp.slot_off + (uint32_t)live[i];
+      if ((d.flags[slot] & kBirthClaim) && d.claim[wp.cell_off + d.tgt[slot]] == slot) ++nw;
+    }
+  static_assert(NP == 2, "the packed ranking scan holds two passes of free slots");
+  unsigned long long rtot;
+  const unsigned long long rex =
+      block_exscan_u64<NT>((unsigned long long)nw | (unsigned long long)__builtin_popcount(fm[0]) << 16 |
+                               (unsigned long long)__builtin_popcount(fm[1]) << 32,
+                           rank_red, &rtot);
+  const uint32_t Wn = (uint32_t)(rtot & 0xFFFFu);
+  uint32_t k = (uint32_t)(rex & 0xFFFFu);
+  for (uint32_t i = l0; i < l1 && nw; ++i) {
+    const uint32_t local = (uint32_t)live[i], slot = wp.slot_off + local;
+    if ((d.flags[slot] & kBirthClaim) && d.claim[wp.cell_off + d.tgt[slot]] == slot) d.bparent[wp.slot_off + k++] = (int)local;
+  }
+  uint32_t F = 0;
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const uint32_t b0 = (p * NT + tid) * CH;
-    uint32_t r = (p == 0 ? 0u : N0) + ((ex >> (16 * p)) & 0xFFFFu);
-    for (uint32_t a = am[p]; a; a &= a - 1) d.live[wp.slot_off + r++] = (int)(b0 + __builtin_ctz(a));
+    uint32_t f = F + (uint32_t)((rex >> (16 * (p + 1))) & 0xFFFFu);
+    if (lane == 0 && b0 < cap) ts.scan[(b0 / kSlotTile) * 4 + 2] = f;   // free slots before the wave's tile
+    for (uint32_t m = fm[p]; m && f < Wn; m &= m - 1) d.freel[wp.slot_off + f++] = (int)(b0 + __builtin_ctz(m));
+    F += (uint32_t)((rtot >> (16 * (p + 1))) & 0xFFFFu);
   }
-  if (tid == 0) {
-    // the energy total exactly, the trait moments by the pairwise (Chan-Golub-LeVeque)
-    // merge of the waves' in wave order
-    unsigned long long E = 0;
-    Moments tm{0.0, 0.0, 0.0};
-    for (int i = 0; i < NT / 64; ++i) {
-      E += red64[i];
-      const uint32_t c = live_red[i];
-      tm = merge_moments(tm, Moments{(double)((c & 0xFFFFu) + (c >> 16)), s_red[i], m2_red[i]});
-    }
-    const double mean = N ? tm.mean : 0.0, M2 = tm.m2;
-    WorldVar& v = d.wv[w];
-    v.n_births = nb;
-    v.n_win = Wn;
-    v.step += 1;
-    v.uid_next += nb;
-    v.n_live = N;
-    d.cnt[w].births = nb;
-    d.cnt[w].births_blocked_cell = claims - Wn;
-    d.cnt[w].births_blocked_capacity = Wn - nb;
-    eco_stats st = {};
-    st.step = v.step;
-    st.population = N;
-    st.births = nb;
-    st.births_blocked_cell = claims - Wn + blocked;
-    st.births_blocked_capacity = Wn - nb;
-    st.deaths = cnt[PC_DEATHS];
-    st.killed = cnt[PC_KILLED];
-    st.eaten = cnt[PC_EATEN];
-    st.moves_ok = cnt[PC_MOVES_OK];
-    st.moves_blocked = cnt[PC_MOVES_BLOCKED];
-    for (int a = 0; a < 9; ++a) st.action_hist[a] = cnt[PC_HIST + a];
-    st.regrown = ccnt[0];
-    st.resource_total = ccnt[1];
-    st.energy_total = (double)(long long)E;
-    st.trait_mean = mean;
-    st.trait_var = N ? M2 / (double)N : 0.0;
-    if constexpr (ECO) {   // grid (the cell pass) plus carried (the live slots)
-      unsigned long long ecot[3] = {0, 0, 0};
-#pragma unroll 1
-      for (int i = 0; i < NT / 64; ++i)
-        for (int k = 0; k < 3; ++k) ecot[k] += eco_red[k][i];
-      st.water_total = ecot[0] + ccnt[2];
-      st.biomass_total = ecot[1] + ccnt[3];
-      st.hp_total = ecot[2];
-    }
-    d.ring[(uint64_t)w * kStatsRing + (v.step % kStatsRing)] = st;
-  }
-  // the window channels of every cell for the next step (the grid is final)
-  if (sense_bytes) {
-    // the sense bytes: resource and wall bits of each cell, with its occupant's
-    // agent bit and energy bin from s_agent (complete since the barrier above)
-    for (uint32_t c0 = tid * 4; c0 < cells; c0 += NT * 4) {
-      const uint32_t g = wp.cell_off + c0;
-      const uint32_t r = *reinterpret_cast<const uint32_t*>(d.res + g);
-      const uint32_t wl = *reinterpret_cast<const uint32_t*>(d.wall + g);
-      const uint32_t ag = *reinterpret_cast<const uint32_t*>(s_agent + c0);
-      uint32_t v = 0;
+  // 5. the draft of the statistics record (the block scan's barrier is behind every sum)
+  StepDraft* dr = d.draft + w;
+  if (tid >= 64 && tid < 64 + kSlotPart) dr->count[tid - 64] = cnt[tid - 64];
+  if (wave == 0) {   // lane i < NW holds wave i's sums
+    const bool on = lane < NW;
+    const uint32_t n_i = on ? live_red[lane] : 0u;
+    const double mean_i = on ? mean_red[lane] : 0.0;
+    const uint32_t N = lane_value(wave_scan(n_i), 63);
+    const double mean = N ? lane_value(wave_scan((double)n_i * mean_i), 63) / (double)N : 0.0;
+    const double M2 = wave_scan((on ? m2_red[lane] : 0.0) + (double)n_i * (mean_i - mean) * (mean_i - mean));
+    const unsigned long long E = wave_scan(on ? red64[lane] : 0ull);
+    unsigned long long carried[3] = {0, 0, 0};
+    if constexpr (ECO) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        v |= (((ag >> (8 * j)) & 0xFFu) | cell_sense(wp, (r >> (8 * j)) & 0xFFu, (wl >> (8 * j)) & 0xFFu)) << (8 * j);
-      if (c0 + 4 <= cells) {
-        *reinterpret_cast<uint32_t*>(d.sense + g) = v;
-      } else {
-        for (uint32_t j = 0; c0 + j < cells; ++j) d.sense[g + j] = (uint8_t)(v >> (8 * j));
-      }
+      for (int q = 0; q < 3; ++q) carried[q] = wave_scan(on ? eco_red[q][lane] : 0ull);
     }
-  } else if (ECO) {
-    cell_ecology_tile(d, wp, Tile{w, 0u, cells, 0u}, 1, s_col);   // with terrain, the flowed water copied back first
-  } else {
-    cell_render_tile(d, Tile{w, 0u, cells, 0u}, s_col);
+    if (lane == 63) {
+      dr->regrown = ccnt[0];
+      dr->resource_total = ccnt[1];
+      dr->water = ECO ? ccnt[2] + carried[0] : 0ull;
+      dr->biomass = ECO ? ccnt[3] + carried[1] : 0ull;
+      dr->hp = carried[2];
+      dr->energy = (long long)E;
+      dr->mean = mean;
+      dr->m2 = M2;
+      dr->n0 = N;
+      WorldVar& v = d.wv[w];
+      dr->step = v.step;
+      dr->uid_next = v.uid_next;
+      v.n_win = Wn;
+      v.n_free = F;
+    }
   }
 }
 
@@ -1882,8 +2337,7 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, Layout L, uint32_t n
 __global__ __launch_bounds__(256) void k_render(Dev d, const Tile* __restrict__ tiles, int only_world) {
   const Tile ct = tiles[blockIdx.x];
   if ((int)ct.world != only_world) return;
-  if (d.ep) cell_ecology_tile(d, d.wp[ct.world], ct, 0);
-  else cell_render_tile(d, ct);
+  window_cells(d, ct);
 }
 
 // Terrain: each cell's way down, the lowest 4-neighbour if strictly lower (the
@@ -2164,11 +2618,11 @@ __global__ __launch_bounds__(512) void k_stream_read(const probe_u32x4* __restri
 
 // ---------------------------------------------------------------------------
 // Static scratch of the allocation-free step (eco_world_step_static): the tile
-// partials, birth lists and step counters of one object live in this array
+// partials, birth lists and statistics drafts of one object live in this array
 // instead of the object's own buffers.  Each GPU the library runs on holds one
 // copy until the process ends; every call on that GPU shares it.
 // ---------------------------------------------------------------------------
-constexpr size_t kStaticScratchBytes = size_t(16) << 20;
+constexpr size_t kStaticScratchBytes = (size_t(16) << 20) + ECO_MAX_WORLDS * sizeof(StepDraft) + ECO_MAX_PARTS * sizeof(double);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 // This GPU's address of the array (the array's name in host code is only a host
@@ -2198,22 +2652,28 @@ hipError_t static_scratch(void** ptr, size_t* bytes) {
 // ---------------------------------------------------------------------------
 #define ECO_CHECK_LAUNCH() return hipGetLastError()
 
-hipError_t launch_move(hipStream_t s, const Dev& d, const TileScratch& ts) {
+hipError_t launch_move(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t H) {
   if (ts.n_slot_tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_move, dim3(ts.n_slot_tiles), dim3(kSlotTile), 0, s, d, ts.slot_tiles, ts.part_slot);
+  hipLaunchKernelGGL(k_move, dim3(ts.n_slot_tiles + d.n_worlds), dim3(kSlotTile), 0, s, d, ts, H);
   ECO_CHECK_LAUNCH();
 }
-hipError_t launch_birth_claim_regrow(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A) {
+// After a call's last step.
+hipError_t launch_settle(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t H, uint32_t small) {
+  hipLaunchKernelGGL(k_settle, dim3(d.n_worlds), dim3(256), 0, s, d, ts, H, small);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || d.n_worlds == 1) return e;
+  hipLaunchKernelGGL(k_settled, dim3((d.n_worlds + 255) / 256), dim3(256), 0, s, d);
+  ECO_CHECK_LAUNCH();
+}
+hipError_t launch_claim_cells(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A) {
   const uint32_t nb = ts.n_slot_tiles + ts.n_cell_tiles;
   if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_birth_claim_regrow, dim3(nb), dim3(256), 0, s, d, ts, A);
+  hipLaunchKernelGGL(k_claim_cells, dim3(nb), dim3(256), 0, s, d, ts, A);
   ECO_CHECK_LAUNCH();
 }
 hipError_t launch_birth_rank(hipStream_t s, const Dev& d, const TileScratch& ts) {
-  hipLaunchKernelGGL(k_birth_rank_count, dim3(ts.n_slot_tiles), dim3(kSlotTile), 0, s, d, ts);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_birth_rank_write, dim3(ts.n_slot_tiles), dim3(kSlotTile), 0, s, d, ts);
+  const uint32_t nb = ts.n_slot_tiles + d.n_worlds + (d.rock ? ts.n_cell_tiles : 0u);
+  hipLaunchKernelGGL(k_birth_rank, dim3(nb), dim3(kSlotTile), 0, s, d, ts);
   ECO_CHECK_LAUNCH();
 }
 // Resident blocks per CU of the birth-commit kernel for this layout (its register
@@ -2230,42 +2690,40 @@ hipError_t birth_commit_blocks_per_cu(const Layout& L, int* blocks) {
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, f, 256, 0);
 }
 
+hipError_t launch_step_small(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A, uint32_t H) {
+  if (d.ep) hipLaunchKernelGGL(k_step_small<true>, dim3(2), dim3(1024), 0, s, d, ts, A, H);
+  else hipLaunchKernelGGL(k_step_small<false>, dim3(2), dim3(1024), 0, s, d, ts, A, H);
+  ECO_CHECK_LAUNCH();
+}
+// roles: 1 births, 2 live list and records, 3 both in one launch.
+template <int WDT, int H>
+void launch_birth_commit_wh(hipStream_t s, const Dev& d, const Layout& L, const TileScratch& ts, uint32_t births,
+                            uint32_t ranked, int roles) {
+  const uint32_t rest = ts.n_slot_tiles + d.n_worlds;
+  const uint32_t base = (roles & 2) ? 0u : rest, end = rest + ((roles & 1) ? births : 0u);
+  hipLaunchKernelGGL((k_birth_commit<WDT, H>), dim3(end - base), dim3(256), 0, s,
+                     (CommitArgs{d, L, ts, base, births, ranked}));
+}
 template <int WDT>
-void launch_birth_commit_w(hipStream_t s, const Dev& d, const Layout& L, uint32_t blocks) {
-  if (L.H1 == 32) hipLaunchKernelGGL((k_birth_commit<WDT, 32>), dim3(blocks), dim3(256), 0, s, d, L);
-  else if (L.H1 == 64) hipLaunchKernelGGL((k_birth_commit<WDT, 64>), dim3(blocks), dim3(256), 0, s, d, L);
-  else hipLaunchKernelGGL((k_birth_commit<WDT, 128>), dim3(blocks), dim3(256), 0, s, d, L);
+void launch_birth_commit_w(hipStream_t s, const Dev& d, const Layout& L, const TileScratch& ts, uint32_t births,
+                           uint32_t ranked, int roles) {
+  if (L.H1 == 32) launch_birth_commit_wh<WDT, 32>(s, d, L, ts, births, ranked, roles);
+  else if (L.H1 == 64) launch_birth_commit_wh<WDT, 64>(s, d, L, ts, births, ranked, roles);
+  else launch_birth_commit_wh<WDT, 128>(s, d, L, ts, births, ranked, roles);
 }
-hipError_t launch_step_small(hipStream_t s, const Dev& d, const Layout& L) {
+hipError_t launch_birth_commit(hipStream_t s, const Dev& d, const Layout& L, const TileScratch& ts, uint32_t births,
+                               uint32_t ranked, int roles) {
   if (L.H1 != L.H2 || (L.H1 != 32 && L.H1 != 64 && L.H1 != 128)) return hipErrorInvalidValue;
-#define ECO_SMALL(WW, E)                                                                                          \
-  if (L.H1 == 32) hipLaunchKernelGGL((k_step_small<WW, 32, E>), dim3(1), dim3(1024), 0, s, d, L, L.A);           \
-  else if (L.H1 == 64) hipLaunchKernelGGL((k_step_small<WW, 64, E>), dim3(1), dim3(1024), 0, s, d, L, L.A);      \
-  else hipLaunchKernelGGL((k_step_small<WW, 128, E>), dim3(1), dim3(1024), 0, s, d, L, L.A);
-  if (d.ep) {
-    if (L.wdtype == 0) { ECO_SMALL(0, true) }
-    else if (L.wdtype == 1) { ECO_SMALL(1, true) }
-    else { ECO_SMALL(2, true) }
-  } else {
-    if (L.wdtype == 0) { ECO_SMALL(0, false) }
-    else if (L.wdtype == 1) { ECO_SMALL(1, false) }
-    else { ECO_SMALL(2, false) }
-  }
-#undef ECO_SMALL
+  if (L.wdtype == 0) launch_birth_commit_w<0>(s, d, L, ts, births, ranked, roles);
+  else if (L.wdtype == 1) launch_birth_commit_w<1>(s, d, L, ts, births, ranked, roles);
+  else launch_birth_commit_w<2>(s, d, L, ts, births, ranked, roles);
   ECO_CHECK_LAUNCH();
 }
-hipError_t launch_birth_commit(hipStream_t s, const Dev& d, const Layout& L, uint32_t blocks) {
-  if (L.H1 != L.H2 || (L.H1 != 32 && L.H1 != 64 && L.H1 != 128)) return hipErrorInvalidValue;
-  if (L.wdtype == 0) launch_birth_commit_w<0>(s, d, L, blocks);
-  else if (L.wdtype == 1) launch_birth_commit_w<1>(s, d, L, blocks);
-  else launch_birth_commit_w<2>(s, d, L, blocks);
-  ECO_CHECK_LAUNCH();
-}
-hipError_t launch_compact(hipStream_t s, const Dev& d, const TileScratch& ts, int init, int only_world) {
+hipError_t launch_compact(hipStream_t s, const Dev& d, const TileScratch& ts, int only_world) {
   hipLaunchKernelGGL(k_compact_count, dim3(ts.n_slot_tiles), dim3(kSlotTile), 0, s, d, ts, only_world);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_compact_write, dim3(ts.n_slot_tiles + ts.n_cell_tiles), dim3(kSlotTile), 0, s, d, ts, init,
+  hipLaunchKernelGGL(k_compact_write, dim3(ts.n_slot_tiles + ts.n_cell_tiles), dim3(kSlotTile), 0, s, d, ts,
                      only_world);
   ECO_CHECK_LAUNCH();
 }
