@@ -414,18 +414,27 @@ __device__ __forceinline__ T world_param(uint32_t w, uint32_t offset) {
 }
 #define WORLD_PARAM(w, field) world_param<decltype(WorldParams::field)>(w, offsetof(WorldParams, field))
 
-// Agent g of the step's live list (woff in LDS: exclusive world offsets); w is a
-// world index not past g's world.
-__device__ __forceinline__ AgentCtx load_agent(const uint32_t* woff, uint32_t g, uint32_t w) {
+// World and local slot of agent g of the step's live list (woff in LDS: exclusive
+// world offsets); w is a world index not past g's world.  An object of one world (its
+// slots and cells start at 0) has no offsets in LDS: entry g of the one list.
+struct AgentId {
+  uint32_t w, local;
+};
+__device__ __forceinline__ AgentId find_agent(const uint32_t* woff, bool one, uint32_t g, uint32_t w) {
+  if (one) return AgentId{0u, (uint32_t)sload(DEV_ARG(live) + g)};
   while (g >= uni(woff[w + 1])) ++w;
+  return AgentId{w, (uint32_t)sload(DEV_ARG(live) + WORLD_PARAM(w, slot_off) + (g - uni(woff[w])))};
+}
+
+__device__ __forceinline__ AgentCtx load_agent(const AgentId id, uint32_t slot) {
+  const uint32_t w = id.w;
   AgentCtx c;
   c.w = w;
-  const uint32_t slot_off = WORLD_PARAM(w, slot_off);
   c.W = WORLD_PARAM(w, W);
   c.H = WORLD_PARAM(w, H);
   c.cell_off = WORLD_PARAM(w, cell_off);
-  c.local = (uint32_t)sload(DEV_ARG(live) + slot_off + (g - uni(woff[w])));
-  c.slot = slot_off + c.local;
+  c.local = id.local;
+  c.slot = slot;
   c.step = (uint32_t)sload(&DEV_ARG(wv)[w].step);
   c.pos = sload(DEV_ARG(pos) + c.slot);
   c.energy = sload(DEV_ARG(energy) + c.slot);
@@ -561,7 +570,13 @@ void k_forward(Dev d, Layout L) {
   constexpr int VPL = WTraits<WDT>::VPL;
   extern __shared__ __align__(16) float smem[];
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  // Made uniform for the compiler, and with it every agent's number, slot and context:
+  // these are then scalar registers and scalar loads.  (As vector values they took
+  // some thirty of the registers that hold weights in flight: 92 -> 68 for FP32 with a
+  // ring of four, five -> seven waves a SIMD.  Policy kernel, this and the agents'
+  // order below, before / after: 16,345 FP8 agents of 37 KB 111 / 99 us, 4,213 BF16
+  // agents of 45 KB 34 / 30 us, 61,003 FP8 agents 364 / 348 us.)
+  const int wave = (int)uni(threadIdx.x >> 6);
   const int wpb = blockDim.x >> 6;
   uint32_t* woff = reinterpret_cast<uint32_t*>(smem);
   const uint32_t woff_words = (d.n_worlds + 1 + 3) & ~3u;
@@ -570,25 +585,40 @@ void k_forward(Dev d, Layout L) {
   float* h2s = h1s + 128;
 
   for (uint32_t i = L.D + lane; i < L.Dpad; i += 64) xs[i] = 0.0f;  // padding stays zero
-  world_offsets(d.wv, d.n_worlds, woff);
-  const uint32_t total = woff[d.n_worlds];
+  // Agents g, g + n_waves, ... with g counted over the first waves of all blocks, then
+  // the second, ...: every wave has the same number of agents up to one, and a
+  // population smaller than the waves is spread over all compute units.  (One
+  // contiguous run of ceil(total / n_waves) agents a wave left waves idle: 4,213 agents
+  // on 4,096 waves took two agents on 2,107 of them.)  The first agent is known before
+  // the live count is, so its slot is fetched with it (any entry below total_slots is
+  // inside the list).
   const uint32_t n_waves = gridDim.x * wpb;
-  const uint32_t gw = blockIdx.x * wpb + wave;
-  const uint32_t chunk = (total + n_waves - 1) / n_waves;
-  const uint32_t g_lo = gw * chunk, g_hi = min(g_lo + chunk, total);
-  if (g_lo >= g_hi) return;
+  const uint32_t g_lo = wave * gridDim.x + blockIdx.x;
+  const bool one = d.n_worlds == 1;
+  AgentId id{0u, 0u};
+  uint32_t total;
+  if (one) {
+    id = find_agent(woff, true, min(g_lo, d.total_slots - 1u), 0u);
+    total = sload(&d.wv[0].n_live);
+  } else {
+    world_offsets(d.wv, d.n_worlds, woff);
+    total = uni(woff[d.n_worlds]);
+  }
+  if (g_lo >= total) return;
+  if (!one) id = find_agent(woff, false, g_lo, find_world(woff, d.n_worlds, g_lo));
+  const uint32_t slot0 = one ? id.local : WORLD_PARAM(id.w, slot_off) + id.local;
 
   static_assert(WORDS || !NINE, "a ninth action needs the ecology's window words");
   constexpr int NA = NINE ? 9 : 8;   // the most actions this instantiation samples from
 
-  AgentCtx cur = load_agent(woff, g_lo, find_world(woff, d.n_worlds, g_lo));
-  uint32_t sv[kMaxWindowCellsPerLane];
-  gather_sense<WORDS>(L, cur, lane, sv);
   const int KB2 = (int)L.H1 / VPL;   // layer-2 k-blocks (H1 == H; a run-time value, so the compiler keeps the stream a loop)
   // the weight stream: layer 1 and layer 2 of each agent in turn, U blocks in flight
   u32x4 ring[U];
-  ring_start<H, U>(ring, make_seg<H>(d.store + (uint64_t)cur.slot * L.sstride, L.s_w1, (int)L.KBv), lane);
-  for (uint32_t g = g_lo; g < g_hi; ++g) {
+  ring_start<H, U>(ring, make_seg<H>(d.store + (uint64_t)slot0 * L.sstride, L.s_w1, (int)L.KBv), lane);
+  AgentCtx cur = load_agent(id, slot0);
+  uint32_t sv[kMaxWindowCellsPerLane];
+  gather_sense<WORDS>(L, cur, lane, sv);
+  for (uint32_t g = g_lo; g < total; g += n_waves) {
     const AgentCtx& wp = cur;   // the world's grid
     // Window cell ahead of the agent (row ahead0 - 1, column R), when the window has
     // one: the move claim reads its agent and wall channels from the observation
@@ -599,11 +629,12 @@ void k_forward(Dev d, Layout L) {
     write_observation<WORDS>(L, cur, lane, sv, xs);
     const uint32_t front_word = (WORDS && front >= 0) ? window_word(sv, front) : 0u;
     // the next agent's context and window bytes, in flight while this agent streams
-    const bool has_next = g + 1 < g_hi;
+    const bool has_next = g + n_waves < total;
     AgentCtx nxt = cur;
     uint32_t sn[kMaxWindowCellsPerLane];
     if (has_next) {
-      nxt = load_agent(woff, g + 1, cur.w);
+      const AgentId ni = find_agent(woff, one, g + n_waves, cur.w);
+      nxt = load_agent(ni, WORLD_PARAM(ni.w, slot_off) + ni.local);
       gather_sense<WORDS>(L, nxt, lane, sn);
     }
 
