@@ -146,7 +146,7 @@ struct Dev {
   int32_t* freel;               // [total_slots] free slots (local) ascending
   float* logits;                // [total_slots][lgs]
   uint32_t lgs;                 // logits per slot in that buffer: 8, or 16 with a ninth action
-  const double2* trig;          // [256] cos, sin of 2 pi a / 256 (the Box-Muller angle table)
+  const double2* trig;          // [512] the Box-Muller tables: cos, sin of 2 pi a / 256, then the logarithm's
   unsigned long long* cellkeys; // init scratch: [total_cells] (key << 32 | local cell)
   unsigned long long* sorted;   // init scratch
   uint32_t n_worlds;
@@ -215,44 +215,41 @@ __device__ __forceinline__ uint32_t draw32(const WP& w, uint32_t a, uint32_t ste
 // z = sqrt(-2 ln u1) (cos 2 pi u2, sin 2 pi u2), evaluated in FP64, so that a
 // mutated FP32 parameter is the correctly rounded parent + sigma z up to the
 // last bits of the FP64 evaluation.  u1 and u2 are 24-bit dyadic fractions,
-// which the two functions below use: the logarithm of an integer times a power
+// which the functions below use: the logarithm of an integer times a power
 // of two, and the angle split at a table of 256 exact multiples of 2 pi / 256.
-// ln(m 2^-24) for an integer 1 <= m <= 2^24, in FP64 to about an ulp: m = 2^e f
-// with f in [sqrt(1/2), sqrt(2)], so ln(m 2^-24) = (e - 24) ln 2 + ln f with
-// ln f = 2 atanh(s), s = (f - 1) / (f + 1), |s| <= 0.1716, from the odd series
-// 2 (s + s^3/3 + ... + s^19/19), whose next term is below 2^-55 relative; ln 2
-// in two parts, the first with trailing zeros so that (e - 24) times it is exact.
-__device__ __forceinline__ double ln_u24(uint32_t m) {
-  int e = 31 - __builtin_clz(m);
-  double f = ldexp((double)m, -e);   // exact, in [1, 2)
-  if (f > 1.4142135623730951) {
-    f *= 0.5;
-    ++e;
-  }
-  // s = (f - 1) / (f + 1) (both exact; the divisor lies in [1.7, 2.5]): the
-  // hardware reciprocal refined by two Newton steps, then one correction of the
-  // quotient by its residual
-  const double num = f - 1.0, den = f + 1.0;
-  double rc = __builtin_amdgcn_rcp(den);
-  rc = __builtin_fma(rc, __builtin_fma(-den, rc, 1.0), rc);
-  rc = __builtin_fma(rc, __builtin_fma(-den, rc, 1.0), rc);
-  double s = num * rc;
-  s = __builtin_fma(rc, __builtin_fma(-den, s, num), s);
-  const double s2 = s * s;
-  double q = 1.0 / 19.0;
-  q = __builtin_fma(q, s2, 1.0 / 17.0);
-  q = __builtin_fma(q, s2, 1.0 / 15.0);
-  q = __builtin_fma(q, s2, 1.0 / 13.0);
-  q = __builtin_fma(q, s2, 1.0 / 11.0);
-  q = __builtin_fma(q, s2, 1.0 / 9.0);
-  q = __builtin_fma(q, s2, 1.0 / 7.0);
-  q = __builtin_fma(q, s2, 1.0 / 5.0);
-  q = __builtin_fma(q, s2, 1.0 / 3.0);
-  const double two_s = 2.0 * s;
-  const double lnf = __builtin_fma(two_s * s2, q, two_s);
-  const double k = (double)(e - 24);
+//
+// -2 ln(m 2^-24) for an integer 1 <= m <= 2^24, in FP64 to about an ulp: m = 2^e f
+// with f in [1, 2), and the top eight bits of f below its leading one name a table
+// entry {1/c, -2 ln c} with c near f.  1/c has at most 29 significant bits and f 24,
+// so r = f / c - 1 is exact in one multiply-add; |r| < 2^-8, and ln(1 + r) is its
+// series through r^7 (the next term is below 2^-58 relative).  Entries from sqrt(2) on
+// stand for c / 2 with e + 1, so that nothing cancels next to m = 2^24; there and at
+// f = 1, c is 1 (or 2) itself with ln c = 0, and the result keeps its relative
+// accuracy down to the exact 0.  2 ln 2 in two parts, the first with trailing zeros so
+// that k times it is exact.  (The odd atanh series with its division, used before,
+// took 26 FP64 instructions and a reciprocal where this takes 11: with it, the shorter
+// square root and the BF16 conversion instruction the births of a 65,536-agent BF16
+// world, 8,640 a step, went from 659 to 599 us, the rate of a device copy.  Largest
+// error of sqrt(-2 ln u) over all 2^24 u: 1.65 x 2^-53 relative, before 1.93.)
+constexpr int kLogTable = 256;
+constexpr int kLogFold = 106;   // entries from here on (f >= 1.4140625) stand for c / 2
+
+__device__ __forceinline__ double neg2_ln_u24(uint32_t m, const double2* __restrict__ tab) {
+  const uint32_t lz = (uint32_t)__builtin_clz(m);
+  const uint32_t v = m << lz;                        // leading one at bit 31
+  const uint32_t i = (v >> 23) & (kLogTable - 1);
+  const double f = __hiloint2double((int)(0x3FF00000u | ((v >> 11) & 0xFFFFFu)), (int)(v << 21));
+  const double2 t = tab[i];
+  const double r = __builtin_fma(f, t.x, -1.0);
+  double q = __builtin_fma(r, 1.0 / 7.0, -1.0 / 6.0);
+  q = __builtin_fma(r, q, 1.0 / 5.0);
+  q = __builtin_fma(r, q, -1.0 / 4.0);
+  q = __builtin_fma(r, q, 1.0 / 3.0);
+  q = __builtin_fma(r, q, -1.0 / 2.0);
+  const double l1p = __builtin_fma(r * r, q, r);
+  const double k = (double)((int)(7u - lz) + (i >= (uint32_t)kLogFold ? 1 : 0));   // e - 24, e = 31 - lz
   constexpr double ln2_hi = 0x1.62e42fefa38p-1, ln2_lo = 0x1.ef35793c7673p-45;
-  return __builtin_fma(k, ln2_hi, __builtin_fma(k, ln2_lo, lnf));
+  return __builtin_fma(k, -2.0 * ln2_hi, __builtin_fma(k, -2.0 * ln2_lo, __builtin_fma(-2.0, l1p, t.y)));
 }
 
 // cos and sin of 2 pi j 2^-24 for a 24-bit integer j, in FP64 to a few ulps of
@@ -280,30 +277,32 @@ __device__ __forceinline__ void cossin_2pi_u24(uint32_t j, const double2* __rest
   s = __builtin_fma(t.y, cp, t.x * sp);
 }
 
-// sqrt(y) for 0 <= y < 2^10 in FP64, to about an ulp: Goldschmidt's iteration
-// (g -> sqrt(y), h -> 1 / (2 sqrt(y))) from the hardware reciprocal square root,
-// twice, then one correction by the residual y - g^2.  y = 0 gives 0.
+// sqrt(y) for 0 <= y < 2^10 in FP64, to about an ulp: one step of Goldschmidt's
+// iteration (g -> sqrt(y), h -> 1 / (2 sqrt(y))) from the hardware reciprocal square
+// root (2^-24 or better, so g is then good to 2^-46), then one correction by the
+// residual y - g^2, which squares that again.  y = 0 gives 2^-500 (the reciprocal
+// needs a positive argument), which any normal drawn from it rounds to a zero of the
+// same sign.
 __device__ __forceinline__ double sqrt_small(double y) {
+  y = __builtin_fmax(y, 0x1p-1000);
   const double r0 = __builtin_amdgcn_rsq(y);
-  double g = y * r0, h = 0.5 * r0;
-  double e = __builtin_fma(-g, h, 0.5);
-  g = __builtin_fma(g, e, g);
-  h = __builtin_fma(h, e, h);
-  e = __builtin_fma(-g, h, 0.5);
-  g = __builtin_fma(g, e, g);
-  h = __builtin_fma(h, e, h);
-  g = __builtin_fma(__builtin_fma(-g, g, y), h, g);
-  return y > 0.0 ? g : 0.0;
+  double g = y * r0;
+  const double h = 0.5 * r0;
+  g = __builtin_fma(g, __builtin_fma(-g, h, 0.5), g);
+  return __builtin_fma(__builtin_fma(-g, g, y), h, g);
 }
 
-// Four standard normals from one Philox block (tab: the angle table above, in LDS).
+// The angle table, then the logarithm table, in LDS and behind Dev::trig.
+constexpr int kNoiseTable = kTrigTable + kLogTable;
+
+// Four standard normals from one Philox block (tab: the two tables, in LDS).
 __device__ __forceinline__ void gauss4k(uint32_t key0, uint32_t key1, uint32_t a, uint32_t step, uint32_t stream,
                                         uint32_t blk, const double2* __restrict__ tab, double z[4]) {
   const uint4 x = philox10(a, step, stream, blk, key0, key1);
   const uint32_t xs[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
-    const double r = sqrt_small(-2.0 * ln_u24((xs[2 * p] >> 8) + 1u));   // u1 = ((x >> 8) + 1) 2^-24
+    const double r = sqrt_small(neg2_ln_u24((xs[2 * p] >> 8) + 1u, tab + kTrigTable));   // u1 = ((x >> 8) + 1) 2^-24
     double s, c;
     cossin_2pi_u24(xs[2 * p + 1] >> 8, tab, c, s);                 // u2 = (x >> 8) 2^-24
     z[2 * p] = r * c;
@@ -316,9 +315,9 @@ __device__ __forceinline__ void gauss4(const WorldParams& w, uint32_t a, uint32_
   gauss4k(w.key0, w.key1, a, step, stream, blk, tab, z);
 }
 
-// The angle table into LDS (all threads of the block take part).
+// The tables into LDS (all threads of the block take part).
 __device__ __forceinline__ void load_trig(const double2* __restrict__ src, double2* dst) {
-  for (int i = threadIdx.x; i < kTrigTable; i += blockDim.x) dst[i] = src[i];
+  for (int i = threadIdx.x; i < kNoiseTable; i += blockDim.x) dst[i] = src[i];
   __syncthreads();
 }
 

@@ -341,6 +341,38 @@ std::vector<double2> angle_table() {
   return t;
 }
 
+// The logarithm table: entry i stands for f in [1 + i / 256, 1 + (i + 1) / 256) with
+// {1/c, -2 ln c}, 1/c of 28 bits behind the point for c in the middle (c = 1 and 2 at
+// the ends), and the logarithm that of c / 2 from kLogFold on.  Of the 1/c next to the
+// middle's the one whose logarithm lies nearest to a double is taken, so that the
+// table adds no rounding of its own.
+std::vector<double2> log_table() {
+  std::vector<double2> t(kLogTable);
+  for (int i = 0; i < kLogTable; ++i) {
+    const long double fold = i >= kLogFold ? 2.0L : 1.0L;
+    const double c = i == 0 ? 1.0 : (i == kLogTable - 1 ? 2.0 : 1.0 + (i + 0.5) / kLogTable);
+    const int span = (i == 0 || i == kLogTable - 1) ? 0 : 64;
+    long double best = 1.0L;
+    for (int n = -span; n <= span; ++n) {
+      const double ic = (std::nearbyint(0x1p28 / c) + n) * 0x1p-28;
+      const long double l = 2.0L * std::log((long double)ic * fold);
+      const long double off = l == 0.0L ? 0.0L : std::fabs(((long double)(double)l - l) / l);
+      if (off < best) {
+        best = off;
+        t[i] = make_double2(ic, (double)l);
+      }
+    }
+  }
+  return t;
+}
+
+// Both, as the kernels hold them.
+std::vector<double2> noise_tables() {
+  std::vector<double2> t = angle_table(), l = log_table();
+  t.insert(t.end(), l.begin(), l.end());
+  return t;
+}
+
 void upload_world_params(eco_world* w) {
   for (uint32_t i = 0; i < w->n_worlds; ++i) {
     w->wp[i].key0 = (uint32_t)(w->descs[i].seed & 0xFFFFFFFFu);
@@ -863,7 +895,7 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   d.freel = (int32_t*)A(4 * TS);
   d.lgs = w->L.R3;
   d.logits = (float*)A(4ull * d.lgs * TS);
-  d.trig = (const double2*)A(sizeof(double2) * kTrigTable);
+  d.trig = (const double2*)A(sizeof(double2) * kNoiseTable);
   d.cellkeys = (unsigned long long*)A(8 * TC);
   d.sorted = (unsigned long long*)A(8 * TC);
   d.store = (uint8_t*)A(w->L.sstride * TS);
@@ -955,9 +987,9 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   chk(hipMemcpyAsync(w->place_info, w->place_info_h.data(), 4 * w->place_info_h.size(), hipMemcpyHostToDevice, s),
       "upload placement table");
   {
-    static const std::vector<double2> trig = angle_table();
-    chk(hipMemcpyAsync((void*)d.trig, trig.data(), sizeof(double2) * kTrigTable, hipMemcpyHostToDevice, s),
-        "upload angle table");
+    static const std::vector<double2> trig = noise_tables();
+    chk(hipMemcpyAsync((void*)d.trig, trig.data(), sizeof(double2) * kNoiseTable, hipMemcpyHostToDevice, s),
+        "upload noise tables");
   }
   chk(hipMemsetAsync(d.store, 0, w->L.sstride * TS, s), "clear weights");
   if (d.master != d.store) chk(hipMemsetAsync(d.master, 0, w->L.mstride * TS, s), "clear master");

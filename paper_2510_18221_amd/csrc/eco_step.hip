@@ -256,11 +256,12 @@ __device__ __forceinline__ UnitInfo unit_info(const Layout& L, uint32_t u) {
   return r;
 }
 
-// Round-to-nearest-even FP32 -> BF16 of a finite value.
-__device__ __forceinline__ uint32_t bf16_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
+// Round-to-nearest-even FP32 -> BF16 of two finite values, a in the low half (one
+// gfx950 instruction; equal to rounding the bit pattern for every FP32 but NaN).
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
 // FP32 -> OCP FP8 E4M3FN, round to nearest even, saturating at 448; values
@@ -341,8 +342,8 @@ __device__ void emit_agent(const Dev& d, const Layout& L, const WorldParams& wp,
     for (int i = 0; i < 4; ++i) tsum += (double)v[i] * (double)v[i];
 
     if (WDT == 1) {
-      const uint32_t lo = bf16_rne(v[0]) | (bf16_rne(v[1]) << 16);
-      const uint32_t hi = bf16_rne(v[2]) | (bf16_rne(v[3]) << 16);
+      const uint32_t lo = bf16_pair(v[0], v[1]);
+      const uint32_t hi = bf16_pair(v[2], v[3]);
       uint64_t off;
       if (ui.layer == 0) off = L.s_w1 + ((uint64_t)(ui.kb >> 1) * L.H1 + ui.row) * 16 + (ui.kb & 1) * 8;
       else if (ui.layer == 1) off = L.s_w2 + ((uint64_t)(ui.kb >> 1) * L.H2 + ui.row) * 16 + (ui.kb & 1) * 8;
@@ -1441,8 +1442,8 @@ template <int WDT, int H>
 __device__ __forceinline__ void store_unit(const Layout& L, uint8_t* sc, int layer, uint32_t row, uint32_t kb,
                                            const float (&v)[4], uint32_t* s_amax) {
   if (WDT == 1) {
-    const uint32_t lo = bf16_rne(v[0]) | (bf16_rne(v[1]) << 16);
-    const uint32_t hi = bf16_rne(v[2]) | (bf16_rne(v[3]) << 16);
+    const uint32_t lo = bf16_pair(v[0], v[1]);
+    const uint32_t hi = bf16_pair(v[2], v[3]);
     uint64_t off;
     if (layer == 0) off = L.s_w1 + ((uint64_t)(kb >> 1) * H + row) * 16 + (kb & 1) * 8;
     else if (layer == 1) off = L.s_w2 + ((uint64_t)(kb >> 1) * H + row) * 16 + (kb & 1) * 8;
@@ -1617,8 +1618,8 @@ __device__ double mutate_part(uint32_t child, uint32_t parent, float wsigma, uin
 #pragma unroll
       for (int i = 0; i < 4; ++i) tsum += (double)va[i] * (double)va[i] + (double)vb[i] * (double)vb[i];
       typedef unsigned int u32x4s __attribute__((ext_vector_type(4)));
-      const u32x4s blk = {bf16_rne(va[0]) | (bf16_rne(va[1]) << 16), bf16_rne(va[2]) | (bf16_rne(va[3]) << 16),
-                          bf16_rne(vb[0]) | (bf16_rne(vb[1]) << 16), bf16_rne(vb[2]) | (bf16_rne(vb[3]) << 16)};
+      const u32x4s blk = {bf16_pair(va[0], va[1]), bf16_pair(va[2], va[3]),
+                          bf16_pair(vb[0], vb[1]), bf16_pair(vb[2], vb[3])};
       __builtin_nontemporal_store(blk, reinterpret_cast<u32x4s*>(sc + s_w1 + ((uint64_t)j * H + row) * 16));
     }
   } else {
@@ -1842,8 +1843,8 @@ void k_birth_commit(CommitArgs by_value) {
   __shared__ uint32_t red[4];
   __shared__ uint32_t s_amax[128 + 128 + 16];
   __shared__ double s_red[4];
-  __shared__ double2 tab[kTrigTable];
-  static_assert(kTrigTable == 256, "one table entry per thread");
+  __shared__ double2 tab[kNoiseTable];
+  static_assert(kNoiseTable == 512, "two table entries per thread");
   uint32_t first = blockIdx.x, lgp = 0;
   {
     const CommitArgs& a = args();
@@ -1879,6 +1880,7 @@ void k_birth_commit(CommitArgs by_value) {
     if (first >= (total << lgp) + (total + 255) / 256) return;   // nothing for this block (no block, without births)
     run_win[threadIdx.x] = before + inc - own;
     tab[threadIdx.x] = a.d.trig[threadIdx.x];
+    tab[256 + threadIdx.x] = a.d.trig[256 + threadIdx.x];
     if (threadIdx.x == 255) {
       run_win[256] = all;
       if (summed) {
@@ -2571,7 +2573,7 @@ __global__ __launch_bounds__(256) void k_emit_list(Dev d, Layout L, const uint32
                                                    int mode, double std1, double std2, double std3) {
   __shared__ uint32_t s_amax[128 + 128 + 16];
   __shared__ double s_red[4];
-  __shared__ double2 tab[kTrigTable];
+  __shared__ double2 tab[kNoiseTable];
   load_trig(d.trig, tab);
   for (uint32_t e = blockIdx.x; e < n; e += gridDim.x) {
     const uint32_t w = list[2 * e], j = list[2 * e + 1];
