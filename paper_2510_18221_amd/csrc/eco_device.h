@@ -59,7 +59,9 @@ struct WorldVar {
   uint32_t n0;          // survivors of the last step, and their trait mean and sum of squared deviations
   uint32_t pad;
   double mean, m2;
+  uint64_t pad2;
 };
+static_assert(sizeof(WorldVar) == 64, "whole 16-byte units");
 
 // Per-slot-tile counters of one step (index in the tile's row of part_slot).
 constexpr int kSlotPart = 16;    // u32 counters per slot tile
@@ -160,6 +162,18 @@ struct Dev {
 // Tile of one world's slot or cell range, for per-slot / per-cell kernels.
 struct Tile {
   uint32_t world, start, count, pad;
+};
+
+// Pieces of device memory gathered into, or scattered from, the pinned host buffer of
+// an object (each at a multiple of 16 bytes there and on the device).
+struct Segment {
+  void* dev;
+  uint32_t at;      // place in the host buffer, in 16-byte units
+  uint32_t bytes;
+};
+constexpr int kMaxSegments = 24;
+struct Segments {
+  Segment s[kMaxSegments];
 };
 
 // Per-tile scratch of the multi-block passes (slot tiles of 256 slots, cell
