@@ -21,7 +21,7 @@
  *    eco_allocator when one is given, else hipMalloc) and released by
  *    eco_world_destroy.  Host buffers passed in stay owned by the caller.
  *  - The calls that move state, statistics, logits or actions between host and
- *    device use one pinned host buffer of 2 MiB per object, allocated by the first of
+ *    device use one pinned host buffer of 1 MiB per object, allocated by the first of
  *    them and released by eco_world_destroy (copies do without it if that fails).
  *  - All work is enqueued on the stream given at create (NULL = the null
  *    stream).  eco_world_step is asynchronous; calls that return data to the

@@ -394,7 +394,8 @@ eco_status sync(eco_world* w) {
 // copy's fixed cost, 10 - 17 us, is then small beside its bytes).  The state of the
 // 64 x 64 world, 152 KB in 13 arrays, takes 20 us where copies took 240, that of a
 // 1024 x 1024 world, 10.4 MB, 580 where they took 700.
-constexpr size_t kHostBytes = size_t(2) << 20, kSegmentBytes = size_t(256) << 10;
+// Allocating the buffer takes 20 - 50 us at 1 MiB and up to 330 at 2 MiB.
+constexpr size_t kHostBytes = size_t(1) << 20, kSegmentBytes = size_t(256) << 10;
 
 bool host_buffer(eco_world* w) {
   if (!w->host && hipHostMalloc((void**)&w->host, kHostBytes, hipHostMallocDefault) != hipSuccess) {
