@@ -45,10 +45,10 @@ hipError_t launch_render(hipStream_t s, const Dev& d, const TileScratch& ts, int
 hipError_t launch_flowdir(hipStream_t s, const Dev& d, const TileScratch& ts, int world);
 hipError_t launch_init_cells(hipStream_t s, const Dev& d, const Tile* tiles, uint32_t nt);
 hipError_t launch_init_agents(hipStream_t s, const Dev& d, const Tile* tiles, uint32_t nt);
-hipError_t launch_emit_list(hipStream_t s, const Dev& d, const Layout& L, const uint32_t* list, uint32_t n, int mode,
-                            double std1, double std2, double std3, uint32_t blocks);
+hipError_t launch_init_weights(hipStream_t s, const Dev& d, const Layout& L, const uint32_t* list, uint32_t n,
+                               bool requant, double std1, double std2, double std3, uint32_t n_cus);
 hipError_t launch_placement(hipStream_t s, const Dev& d, const Tile* cell_tiles, uint32_t nt, const void* pinfo,
-                            uint32_t* cnt, uint32_t* start);
+                            uint32_t* cnt, uint32_t* sums, uint32_t* start, uint32_t most_buckets);
 }  // namespace eco
 
 using namespace eco;
@@ -57,7 +57,6 @@ namespace {
 
 constexpr uint32_t kSlotTileH = 256;
 constexpr uint32_t kCellTileH = 1024;
-enum { EMIT_INIT = 0, EMIT_REQUANT = 2 };
 
 thread_local std::string g_err;
 
@@ -103,8 +102,9 @@ struct eco_world {
   // bucket counts and starts
   void* place_info = nullptr;
   uint32_t* place_cnt = nullptr;
+  uint32_t* place_sums = nullptr;
   uint32_t* place_start = nullptr;
-  uint32_t n_buckets = 0;
+  uint32_t n_buckets = 0, most_buckets = 0;   // of all worlds, of one
   std::vector<uint32_t> place_info_h;
   uint32_t* emit_list = nullptr;
   int n_cus = 256;
@@ -439,7 +439,6 @@ class Transfer {
   uint32_t count_ = 0, most_ = 0;
 };
 
-uint32_t emit_blocks(eco_world* w) { return (uint32_t)std::max(1, w->n_cus * 4); }
 // Birth commit: one 256-thread block per birth, persistent, as many blocks as
 // can be resident at once (the kernel is bound by its noise arithmetic; more
 // resident waves hide the parent reads, and a grid beyond residency would start
@@ -452,32 +451,17 @@ eco_status run_init(eco_world* w) {
   Dev& d = w->d;
   HIPCHK(w, hipMemcpyAsync((void*)d.wp, w->wp.data(), sizeof(WorldParams) * w->n_worlds, hipMemcpyHostToDevice, s),
          "upload world params");
-  std::vector<WorldVar> wv(w->n_worlds);
-  for (uint32_t i = 0; i < w->n_worlds; ++i) {
-    wv[i] = WorldVar{};
-    wv[i].uid_next = w->descs[i].n_agents_init;
-  }
-  HIPCHK(w, hipMemcpyAsync(d.wv, wv.data(), sizeof(WorldVar) * w->n_worlds, hipMemcpyHostToDevice, s), "upload vars");
-  HIPCHK(w, hipMemsetAsync(d.flags, 0, w->total_slots, s), "clear flags");
   HIPCHK(w, hipMemsetAsync(d.ring, 0, sizeof(eco_stats) * kStatsRing * w->n_worlds, s), "clear stats");
   HIPCHK(w, launch_init_cells(s, d, w->cell_tiles, w->n_cell_tiles), "init cells");
   HIPCHK(w, launch_flowdir(s, d, w->ts, -1), "flow directions");
   HIPCHK(w, hipMemsetAsync(w->place_cnt, 0, 4ull * w->n_buckets, s), "clear placement counts");
-  HIPCHK(w, launch_placement(s, d, w->cell_tiles, w->n_cell_tiles, w->place_info, w->place_cnt, w->place_start),
-         "placement");
+  HIPCHK(w, launch_placement(s, d, w->cell_tiles, w->n_cell_tiles, w->place_info, w->place_cnt, w->place_sums,
+                             w->place_start, w->most_buckets), "placement");
   HIPCHK(w, launch_init_agents(s, d, w->slot_tiles, w->n_slot_tiles), "init agents");
-  std::vector<uint32_t> list;
-  for (uint32_t i = 0; i < w->n_worlds; ++i)
-    for (uint32_t j = 0; j < w->descs[i].n_agents_init; ++j) {
-      list.push_back(i);
-      list.push_back(j);
-    }
-  const uint32_t n = (uint32_t)(list.size() / 2);
-  if (n) {
-    HIPCHK(w, hipMemcpyAsync(w->emit_list, list.data(), list.size() * 4, hipMemcpyHostToDevice, s), "upload list");
-    HIPCHK(w, launch_emit_list(s, d, w->L, w->emit_list, n, EMIT_INIT, w->std1, w->std2, w->std3, emit_blocks(w)),
-           "init weights");
-  }
+  uint64_t n = 0;
+  for (const auto& de : w->descs) n += de.n_agents_init;
+  HIPCHK(w, launch_init_weights(s, d, w->L, nullptr, (uint32_t)n, false, w->std1, w->std2, w->std3, (uint32_t)w->n_cus),
+         "init weights");
   HIPCHK(w, launch_compact(s, d, w->ts, -1), "compact");
   HIPCHK(w, launch_resource_total(s, d, -1), "resource total");
   eco_status st = sync(w);
@@ -988,12 +972,14 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
       pinfo.push_back(nb);
       pinfo.push_back(32 - k);
       nb += 1u << k;
+      w->most_buckets = std::max(w->most_buckets, 1u << k);
     }
     pinfo.push_back(nb);
     pinfo.push_back(32);
     w->n_buckets = nb;
     w->place_info = A(4 * pinfo.size());
     w->place_cnt = (uint32_t*)A(4ull * nb);
+    w->place_sums = (uint32_t*)A(4ull * (nb / 4096 + n_worlds + 1));
     w->place_start = (uint32_t*)A(4ull * (nb + n_worlds));
     w->place_info_h = pinfo;
   }
@@ -1045,9 +1031,7 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
     chk(hipMemcpyAsync((void*)d.trig, trig.data(), sizeof(double2) * kNoiseTable, hipMemcpyHostToDevice, s),
         "upload noise tables");
   }
-  chk(hipMemsetAsync(d.store, 0, w->L.sstride * TS, s), "clear weights");
-  if (d.master != d.store) chk(hipMemsetAsync(d.master, 0, w->L.mstride * TS, s), "clear master");
-  chk(hipMemsetAsync(d.trait, 0, 8 * TS, s), "clear trait");
+  chk(hipMemsetAsync(d.flags, 0, TS, s), "clear flags");   // (those between the worlds' ranges stay as they are here)
   chk(hipMemsetAsync(d.sampled, 0xFF, TS, s), "clear sampled");
   chk(hipMemsetAsync(d.act_in, 0, TS, s), "clear act_in");
   chk(hipMemsetAsync(w->part_slot, 0, 4ull * kSlotPart * std::max(1u, w->n_slot_tiles), s), "clear partials");
@@ -1229,12 +1213,7 @@ eco_status eco_world_reset(eco_world* w, const uint64_t* seeds) {
   if (seeds)
     for (uint32_t i = 0; i < w->n_worlds; ++i) w->descs[i].seed = seeds[i];
   upload_world_params(w);
-  hipStream_t s = w->stream;
-  Dev& d = w->d;
   w->broken = false;
-  HIPCHK(w, hipMemsetAsync(d.store, 0, w->L.sstride * (uint64_t)w->total_slots, s), "clear weights");
-  if (d.master != d.store) HIPCHK(w, hipMemsetAsync(d.master, 0, w->L.mstride * (uint64_t)w->total_slots, s), "clear master");
-  HIPCHK(w, hipMemsetAsync(d.trait, 0, 8ull * w->total_slots, s), "clear trait");
   return run_init(w);
 }
 
@@ -1632,8 +1611,8 @@ eco_status eco_world_write_state(eco_world* w, uint32_t world, const void* buf, 
     }
   if (!list.empty()) {
     HIPCHK(w, hipMemcpyAsync(w->emit_list, list.data(), list.size() * 4, hipMemcpyHostToDevice, s), "upload list");
-    HIPCHK(w, launch_emit_list(s, w->d, w->L, w->emit_list, (uint32_t)(list.size() / 2), EMIT_INIT, w->std1, w->std2,
-                               w->std3, emit_blocks(w)), "init weights");
+    HIPCHK(w, launch_init_weights(s, w->d, w->L, w->emit_list, (uint32_t)(list.size() / 2), false, w->std1, w->std2,
+                                  w->std3, (uint32_t)w->n_cus), "init weights");
   }
   HIPCHK(w, launch_compact(s, w->d, w->ts, (int)world), "compact");
   HIPCHK(w, launch_resource_total(s, w->d, (int)world), "resource total");
@@ -1753,8 +1732,11 @@ eco_status eco_world_read_weights(eco_world* w, uint32_t world, uint32_t slot, i
   std::vector<uint8_t> blk(master ? L.mstride : L.sstride);
   HIPCHK(w, hipMemcpyAsync(blk.data(), (master ? w->d.master + g * L.mstride : w->d.store + g * L.sstride), blk.size(),
                            hipMemcpyDeviceToHost, w->stream), "read weights");
+  double trait = 0.0;   // |theta|^2: 0 in a slot that never had weights, whose bytes are the allocation's
+  HIPCHK(w, hipMemcpyAsync(&trait, w->d.trait + g, 8, hipMemcpyDeviceToHost, w->stream), "read trait");
   st = sync(w);
   if (st != ECO_OK) return st;
+  if (trait == 0.0) std::fill(blk.begin(), blk.end(), (uint8_t)0);
   for (uint32_t u = 0; u < L.u_end; ++u) {
     const HostUnit hu = host_unit(L, u);
     for (uint32_t i = 0; i < hu.nvalid; ++i) {
@@ -1815,7 +1797,7 @@ eco_status eco_world_write_weights(eco_world* w, uint32_t world, uint32_t slot, 
          "write master");
   const uint32_t list[2] = {world, slot};
   HIPCHK(w, hipMemcpyAsync(w->emit_list, list, 8, hipMemcpyHostToDevice, s), "upload list");
-  HIPCHK(w, launch_emit_list(s, w->d, L, w->emit_list, 1, EMIT_REQUANT, 0, 0, 0, 1), "requantise");
+  HIPCHK(w, launch_init_weights(s, w->d, L, w->emit_list, 1, true, 0, 0, 0, 1), "requantise");
   st = sync(w);
   if (st != ECO_OK) return st;
   return ECO_OK;

@@ -217,45 +217,9 @@ __device__ __forceinline__ uint32_t end_slot_tile(const TileScratch& ts, uint32_
 }
 
 // ---------------------------------------------------------------------------
-// Weight emission (init, mutation, re-quantisation) for one agent, one block.
+// Weight storage formats.
 // A "unit" is 4 consecutive logical parameters = one 16-byte FP32 master block.
 // ---------------------------------------------------------------------------
-struct UnitInfo {
-  uint32_t p;      // logical index of the first parameter
-  uint32_t nvalid; // parameters of the unit that exist (0..4)
-  int layer;       // 0,1,2 weights; 3,4,5 biases of layer 0,1,2
-  uint32_t row;    // output row (weights) / first row (biases)
-  uint32_t kb;     // k-block (weights of layers 0,1) or column quad (layer 2)
-};
-
-__device__ __forceinline__ UnitInfo unit_info(const Layout& L, uint32_t u) {
-  UnitInfo r;
-  if (u < L.u_b1) {                 // W1 [kb][j]
-    r.layer = 0; r.kb = u / L.H1; r.row = u % L.H1;
-    r.p = L.p_w1 + r.row * L.D + 4 * r.kb; r.nvalid = 4;
-  } else if (u < L.u_w2) {          // b1
-    r.layer = 3; r.row = 4 * (u - L.u_b1); r.kb = 0;
-    r.p = L.p_b1 + r.row; r.nvalid = 4;
-  } else if (u < L.u_b2) {          // W2 [kb][i]
-    const uint32_t e = u - L.u_w2;
-    r.layer = 1; r.kb = e / L.H2; r.row = e % L.H2;
-    r.p = L.p_w2 + r.row * L.H1 + 4 * r.kb; r.nvalid = 4;
-  } else if (u < L.u_w3) {          // b2
-    r.layer = 4; r.row = 4 * (u - L.u_b2); r.kb = 0;
-    r.p = L.p_b2 + r.row; r.nvalid = 4;
-  } else if (u < L.u_b3) {          // W3 [a][H2], 4 columns per unit
-    const uint32_t e = u - L.u_w3, per = L.H2 / 4;
-    r.layer = 2; r.row = e / per; r.kb = e % per;
-    r.p = L.p_w3 + r.row * L.H2 + 4 * r.kb; r.nvalid = (r.row < L.A) ? 4 : 0;
-  } else {                          // b3 (R3 padded), then the log temperature in slot A when it evolves
-    const uint32_t e = u - L.u_b3, n3 = L.A + L.temp;
-    r.layer = 5; r.row = 4 * e; r.kb = 0;
-    r.p = L.p_b3 + r.row;
-    r.nvalid = (r.row < n3) ? min(4u, n3 - r.row) : 0;
-  }
-  return r;
-}
-
 // Round-to-nearest-even FP32 -> BF16 of two finite values, a in the low half (one
 // gfx950 instruction; equal to rounding the bit pattern for every FP32 but NaN).
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
@@ -291,110 +255,6 @@ __device__ __forceinline__ uint32_t fp8_rne_sat(float x) {
   }
   if (q == 0) return 0u;
   return sign | q;
-}
-
-__device__ __forceinline__ float fp8_value(uint32_t q) {
-  const uint32_t e = (q >> 3) & 15u, m = q & 7u;
-  float v = (e == 0) ? (float)m * 0x1p-9f : ldexpf(1.0f + (float)m * 0.125f, (int)e - 7);
-  return (q & 0x80u) ? -v : v;
-}
-
-enum EmitMode { EMIT_INIT = 0, EMIT_REQUANT = 2 };
-
-// Writes the FP32 master of global slot `child` and its storage copy, and the
-// trait |theta|^2 (init and weight writes; births go through mutate_child).
-// INIT: N(0, 1/fan_in) weights from (rng_slot, step 0, WINIT), zero biases.
-// REQUANT: master already written.
-template <int WDT>
-__device__ void emit_agent(const Dev& d, const Layout& L, const WorldParams& wp, uint32_t child, int mode,
-                           uint32_t rng_slot, double std1, double std2, double std3, const double2* tab,
-                           uint32_t* s_amax, double* s_red) {
-  const int tid = threadIdx.x;
-  float* mc = reinterpret_cast<float*>(d.master + (uint64_t)child * L.mstride);
-  uint8_t* sc = d.store + (uint64_t)child * L.sstride;
-  const uint32_t nrows = L.H1 + L.H2 + L.R3;
-  if (WDT == 2) {
-    for (uint32_t i = tid; i < nrows; i += blockDim.x) s_amax[i] = 0u;
-    __syncthreads();
-  }
-  if (L.colour && tid == 0 && mode == EMIT_INIT) {
-    // colour trait: U[0,1) per channel
-    const uint4 x = philox10(rng_slot, 0u, ST_COLOUR_INIT, 0u, wp.key0, wp.key1);
-    d.colour[child] = make_float4((float)(x.x >> 8) * 0x1p-24f, (float)(x.y >> 8) * 0x1p-24f,
-                                  (float)(x.z >> 8) * 0x1p-24f, 0.0f);
-  }
-  double tsum = 0.0;
-  for (uint32_t u = tid; u < L.u_end; u += blockDim.x) {
-    const UnitInfo ui = unit_info(L, u);
-    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (mode == EMIT_REQUANT) {
-      const float4 m4 = reinterpret_cast<const float4*>(mc)[u];
-      v[0] = m4.x; v[1] = m4.y; v[2] = m4.z; v[3] = m4.w;
-    } else if (ui.nvalid > 0 && ui.layer < 3) {
-      double z[4];
-      gauss4(wp, rng_slot, 0u, ST_WINIT, ui.p >> 2, tab, z);
-      const double sd = ui.layer == 0 ? std1 : (ui.layer == 1 ? std2 : std3);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = (float)(z[i] * sd);
-    }
-    if (mode != EMIT_REQUANT) reinterpret_cast<float4*>(mc)[u] = make_float4(v[0], v[1], v[2], v[3]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) tsum += (double)v[i] * (double)v[i];
-
-    if (WDT == 1) {
-      const uint32_t lo = bf16_pair(v[0], v[1]);
-      const uint32_t hi = bf16_pair(v[2], v[3]);
-      uint64_t off;
-      if (ui.layer == 0) off = L.s_w1 + ((uint64_t)(ui.kb >> 1) * L.H1 + ui.row) * 16 + (ui.kb & 1) * 8;
-      else if (ui.layer == 1) off = L.s_w2 + ((uint64_t)(ui.kb >> 1) * L.H2 + ui.row) * 16 + (ui.kb & 1) * 8;
-      else if (ui.layer == 2) off = L.s_w3 + ((uint64_t)ui.row * L.H2 + 4 * ui.kb) * 2;
-      else if (ui.layer == 3) off = L.s_b1 + (uint64_t)ui.row * 2;
-      else if (ui.layer == 4) off = L.s_b2 + (uint64_t)ui.row * 2;
-      else off = L.s_b3 + (uint64_t)ui.row * 2;
-      *reinterpret_cast<uint2*>(sc + off) = make_uint2(lo, hi);
-    } else if (WDT == 2) {
-      if (ui.layer < 3) {
-        const uint32_t r = ui.layer == 0 ? ui.row : (ui.layer == 1 ? L.H1 + ui.row : L.H1 + L.H2 + ui.row);
-        float mx = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) mx = fmaxf(mx, fabsf(v[i]));
-        atomicMax(&s_amax[r], __float_as_uint(mx));
-      } else {
-        const uint64_t off = (ui.layer == 3 ? L.s_b1 : (ui.layer == 4 ? L.s_b2 : L.s_b3)) + (uint64_t)ui.row * 4;
-        *reinterpret_cast<float4*>(sc + off) = make_float4(v[0], v[1], v[2], v[3]);
-      }
-    }
-  }
-  if (WDT == 2) {
-    __syncthreads();
-    // scales, then a second pass over the same units (each thread re-reads its own writes)
-    for (uint32_t r = tid; r < nrows; r += blockDim.x) {
-      const float amax = __uint_as_float(s_amax[r]);
-      const float scale = amax > 0.0f ? amax / 448.0f : 1.0f;
-      uint64_t off;
-      if (r < L.H1) off = L.s_sc1 + (uint64_t)r * 4;
-      else if (r < L.H1 + L.H2) off = L.s_sc2 + (uint64_t)(r - L.H1) * 4;
-      else off = L.s_sc3 + (uint64_t)(r - L.H1 - L.H2) * 4;
-      *reinterpret_cast<float*>(sc + off) = scale;
-    }
-    for (uint32_t u = tid; u < L.u_end; u += blockDim.x) {
-      const UnitInfo ui = unit_info(L, u);
-      if (ui.layer >= 3) continue;
-      const uint32_t r = ui.layer == 0 ? ui.row : (ui.layer == 1 ? L.H1 + ui.row : L.H1 + L.H2 + ui.row);
-      const float amax = __uint_as_float(s_amax[r]);
-      const float scale = amax > 0.0f ? amax / 448.0f : 1.0f;
-      const float4 m4 = reinterpret_cast<const float4*>(mc)[u];
-      const uint32_t q = fp8_rne_sat(m4.x / scale) | (fp8_rne_sat(m4.y / scale) << 8) |
-                         (fp8_rne_sat(m4.z / scale) << 16) | (fp8_rne_sat(m4.w / scale) << 24);
-      uint64_t off;
-      if (ui.layer == 0) off = L.s_w1 + ((uint64_t)(ui.kb >> 2) * L.H1 + ui.row) * 16 + (ui.kb & 3) * 4;
-      else if (ui.layer == 1) off = L.s_w2 + ((uint64_t)(ui.kb >> 2) * L.H2 + ui.row) * 16 + (ui.kb & 3) * 4;
-      else off = L.s_w3 + (uint64_t)ui.row * L.H2 + 4 * ui.kb;
-      *reinterpret_cast<uint32_t*>(sc + off) = q;
-    }
-  }
-  const double t = block_sum_f64<256>(tsum, s_red);
-  if (tid == 0) d.trait[child] = t;
 }
 
 // ---------------------------------------------------------------------------
@@ -1555,29 +1415,52 @@ __device__ __forceinline__ void fp8_finish(const Layout& L, const float4* __rest
 // the rest of the kernel push that loop's own constants and keys out (its body grew
 // from 243 to 321 instructions, and the births of a 65,536-agent world with 840 of
 // them a step from 79 to 116 us).
+struct WeightArgs {   // the first members of both kernels' arguments that write weights
+  Dev d;
+  Layout L;
+};
 struct CommitArgs {
   Dev d;
   Layout L;
   TileScratch ts;
   uint32_t base, n_birth_blocks, ranked;
 };
-__device__ __forceinline__ const CommitArgs& args() {
-  typedef const __attribute__((address_space(4))) CommitArgs* seg_ptr;
+template <typename A = CommitArgs>
+__device__ __forceinline__ const A& args() {
+  typedef const __attribute__((address_space(4))) A* seg_ptr;
   seg_ptr p = (seg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(p));
-  return *(const CommitArgs*)p;
+  return *(const A*)p;
 }
 
-// One part of a child: master = parent master + sigma z (Sec. 3.3 mutation of every
-// parameter), z standard normal from the parent's Philox stream (parent slot, step,
-// MUTATE, block); the storage copy re-quantised from it.  Returns the part's share of
-// the child's |theta|^2 (valid in thread 0).
-template <int WDT, int H, int NT>
-__device__ double mutate_part(uint32_t child, uint32_t parent, float wsigma, uint32_t key0, uint32_t key1,
-                              uint32_t rng_slot, uint32_t step, const PartRows<H> pr, const double2* tab,
-                              uint32_t* s_amax, double* s_red) {
-  const uint32_t tid = threadIdx.x;
-  const CommitArgs& a0 = args();
+// One part of an agent's weights, the storage copy quantised from the master.
+//  BIRTH: master = parent master + sigma z (Sec. 3.3 mutation of every parameter), z
+//    standard normal from the parent's Philox stream (parent slot, step, MUTATE, block).
+//  INIT: N(0, sd^2) weights with the layer's sd, from (slot, step 0, WINIT), zero biases.
+//  REQUANT: the master is there already.
+// Returns the part's share of the agent's |theta|^2 (valid in thread 0).
+enum WeightMode { W_BIRTH, W_INIT, W_REQUANT };
+struct Noise {
+  double sd[3];   // sigma, or the three layers' standard deviations
+  uint32_t key0, key1, slot, step;
+};
+template <int WDT, int H, int NT, int MODE>
+__device__ double write_weights(uint32_t child, uint32_t parent, const Noise nz, const PartRows<H> pr,
+                                const double2* tab, uint32_t* s_amax, double* s_red) {
+  constexpr uint32_t stream = MODE == W_BIRTH ? ST_MUTATE : ST_WINIT;
+  const uint32_t tid = threadIdx.x, key0 = nz.key0, key1 = nz.key1, rng_slot = nz.slot, step = nz.step;
+  const WeightArgs& a0 = args<WeightArgs>();
+  // the parameter from its normal and its parent's (or present) value
+  auto param = [](double z, double sd, float from) {
+    return MODE == W_BIRTH ? (float)__builtin_fma(sd, z, (double)from) : (MODE == W_INIT ? (float)(z * sd) : from);
+  };
+  auto from4 = [&](const float4* p) { return MODE == W_INIT ? make_float4(0.0f, 0.0f, 0.0f, 0.0f) : stream_load4(p); };
+  auto normals = [&](uint32_t blk, double z[4]) {
+    if (MODE != W_REQUANT) gauss4k(key0, key1, rng_slot, step, stream, blk, tab, z);
+  };
+  auto put = [&](float4* p, const float (&v)[4]) {
+    if (MODE != W_REQUANT) stream_store4<WDT>(p, v[0], v[1], v[2], v[3]);
+  };
   const float4* __restrict__ mp = reinterpret_cast<const float4*>(a0.d.master + (uint64_t)parent * a0.L.mstride);
   float4* __restrict__ mc = reinterpret_cast<float4*>(a0.d.master + (uint64_t)child * a0.L.mstride);
   uint8_t* sc = a0.d.store + (uint64_t)child * a0.L.sstride;
@@ -1585,7 +1468,7 @@ __device__ double mutate_part(uint32_t child, uint32_t parent, float wsigma, uin
     for (uint32_t i = tid; i < 2 * H + a0.L.R3; i += NT) s_amax[i] = 0u;
     __syncthreads();
   }
-  const double sigma = (double)wsigma;
+  const double sd1 = nz.sd[0];
   double tsum = 0.0;
   // W1 (most of the units) without the layer decode, then the other layers
   const uint32_t KB1 = a0.L.KB1, s_w1 = a0.L.s_w1, lgr = pr.lgr, row0 = pr.row0, rmask = (1u << lgr) - 1u;
@@ -1600,21 +1483,21 @@ __device__ double mutate_part(uint32_t child, uint32_t parent, float wsigma, uin
       const uint32_t row = row0 + (q & rmask), j = q >> lgr, kb0 = 2 * j;
       const bool two = kb0 + 1 < KB1;
       const uint32_t u0 = kb0 * H + row, u1 = u0 + H;
-      const float4 a = stream_load4(mp + u0);
-      const float4 b = two ? stream_load4(mp + u1) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      const float4 a = from4(mp + u0);
+      const float4 b = two ? from4(mp + u1) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       const float pa[4] = {a.x, a.y, a.z, a.w}, pb[4] = {b.x, b.y, b.z, b.w};
       float va[4], vb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      double z[4];
-      gauss4k(key0, key1, rng_slot, step, ST_MUTATE, row * KB1 + kb0, tab, z);
+      double z[4] = {0.0, 0.0, 0.0, 0.0};
+      normals(row * KB1 + kb0, z);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) va[i] = (float)__builtin_fma(sigma, z[i], (double)pa[i]);
+      for (int i = 0; i < 4; ++i) va[i] = param(z[i], sd1, pa[i]);
       if (two) {
-        gauss4k(key0, key1, rng_slot, step, ST_MUTATE, row * KB1 + kb0 + 1, tab, z);
+        normals(row * KB1 + kb0 + 1, z);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) vb[i] = (float)__builtin_fma(sigma, z[i], (double)pb[i]);
-        stream_store4<WDT>(mc + u1, vb[0], vb[1], vb[2], vb[3]);
+        for (int i = 0; i < 4; ++i) vb[i] = param(z[i], sd1, pb[i]);
+        put(mc + u1, vb);
       }
-      stream_store4<WDT>(mc + u0, va[0], va[1], va[2], va[3]);
+      put(mc + u0, va);
 #pragma unroll
       for (int i = 0; i < 4; ++i) tsum += (double)va[i] * (double)va[i] + (double)vb[i] * (double)vb[i];
       typedef unsigned int u32x4s __attribute__((ext_vector_type(4)));
@@ -1625,40 +1508,41 @@ __device__ double mutate_part(uint32_t child, uint32_t parent, float wsigma, uin
   } else {
     const uint32_t n1 = KB1 << lgr;
     auto unit_of = [&](uint32_t q) { return (q >> lgr) * H + row0 + (q & rmask); };
-    float4 next = tid < n1 ? stream_load4(mp + unit_of(tid)) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float4 next = tid < n1 ? from4(mp + unit_of(tid)) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll 1
     for (uint32_t q = tid; q < n1; q += NT) {
       const float4 p4 = next;   // this unit's parent values, loaded one unit ahead
-      if (q + NT < n1) next = stream_load4(mp + unit_of(q + NT));
+      if (q + NT < n1) next = from4(mp + unit_of(q + NT));
       const uint32_t row = row0 + (q & rmask), kb = q >> lgr;
       const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
-      double z[4];
-      gauss4k(key0, key1, rng_slot, step, ST_MUTATE, row * KB1 + kb, tab, z);
+      double z[4] = {0.0, 0.0, 0.0, 0.0};
+      normals(row * KB1 + kb, z);
       float v[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = (float)__builtin_fma(sigma, z[i], (double)pv[i]);
-      stream_store4<WDT>(mc + kb * H + row, v[0], v[1], v[2], v[3]);
+      for (int i = 0; i < 4; ++i) v[i] = param(z[i], sd1, pv[i]);
+      put(mc + kb * H + row, v);
 #pragma unroll
       for (int i = 0; i < 4; ++i) tsum += (double)v[i] * (double)v[i];
       store_unit<WDT, H>(a0.L, sc, 0, row, kb, v, s_amax);
     }
   }
-  const Layout& L = args().L;
+  const Layout& L = args<WeightArgs>().L;
   const uint32_t n2 = (H / 4) << lgr, nrest = n2 + part_rest_count<H>(L, pr);
 #pragma unroll 1
   for (uint32_t q = tid; q < nrest; q += NT) {
     const uint32_t u = q < n2 ? part_w2_unit<H>(L, pr, q) : part_rest_unit<H>(L, pr, q - n2);
     const UnitPos up = unit_pos<H>(L, u);
     float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (up.nvalid > 0) {
-      const float4 p4 = stream_load4(mp + u);
+    if (up.nvalid > 0 && !(MODE == W_INIT && up.layer >= 3)) {
+      const float4 p4 = from4(mp + u);
       const float pv[4] = {p4.x, p4.y, p4.z, p4.w};
-      double z[4];
-      gauss4k(key0, key1, rng_slot, step, ST_MUTATE, up.blk, tab, z);
+      double z[4] = {0.0, 0.0, 0.0, 0.0};
+      normals(up.blk, z);
+      const double sd = MODE == W_INIT ? (up.layer == 1 ? nz.sd[1] : nz.sd[2]) : sd1;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = (i < (int)up.nvalid) ? (float)__builtin_fma(sigma, z[i], (double)pv[i]) : 0.0f;
+      for (int i = 0; i < 4; ++i) v[i] = (i < (int)up.nvalid) ? param(z[i], sd, pv[i]) : 0.0f;
     }
-    stream_store4<WDT>(mc + u, v[0], v[1], v[2], v[3]);
+    put(mc + u, v);
 #pragma unroll
     for (int i = 0; i < 4; ++i) tsum += (double)v[i] * (double)v[i];
     store_unit<WDT, H>(L, sc, up.layer, up.row, up.kb, v, s_amax);
@@ -1924,8 +1808,9 @@ void k_birth_commit(CommitArgs by_value) {
     const WorldParams& wp = d.wp[w];
     const uint32_t slot_off = wp.slot_off, child = slot_off + uniform((uint32_t)d.freel[slot_off + k]);
     const uint32_t p_local = uniform(parent_of(a, slot_off, k, uniform(off_win[w]) + k));
-    const double t = mutate_part<WDT, H, 256>(child, slot_off + p_local, wp.sigma, wp.key0, wp.key1, p_local,
-                                              (uint32_t)d.draft[w].step, part_rows<H>(part, lgp), tab, s_amax, s_red);
+    const Noise nz{{(double)wp.sigma, 0.0, 0.0}, wp.key0, wp.key1, p_local, (uint32_t)d.draft[w].step};
+    const double t = write_weights<WDT, H, 256, W_BIRTH>(child, slot_off + p_local, nz, part_rows<H>(part, lgp), tab,
+                                                         s_amax, s_red);
     if (threadIdx.x == 0) {
       const CommitArgs& b = args();
       if (lgp || b.ranked) b.ts.parts[j] = t;
@@ -2359,42 +2244,46 @@ __global__ __launch_bounds__(256) void k_flowdir(Dev d, const Tile* __restrict__
   }
 }
 
-// Resource total of each world (init / after state writes): one block per world.
-__global__ __launch_bounds__(kScanThreads) void k_resource_total(Dev d, int only_world) {
-  __shared__ unsigned long long red64[kScanThreads / 64];
-  const uint32_t w = blockIdx.x;
+// Grid totals of the records of init and state writes, whose record has just been
+// written with zeros there: blockIdx.y is the world, its blocks add their shares.
+__global__ __launch_bounds__(256) void k_resource_total(Dev d, int only_world) {
+  __shared__ unsigned long long cnt[3];
+  const uint32_t w = blockIdx.y;
   if (only_world >= 0 && (int)w != only_world) return;
+  if (threadIdx.x < 3) cnt[threadIdx.x] = 0;
+  __syncthreads();
   const WorldParams wp = d.wp[w];
-  unsigned long long s = 0;
-  eco_stats* rec = &d.ring[(uint64_t)w * kStatsRing + (d.wv[w].step % kStatsRing)];
+  unsigned long long s = 0, sw = 0, sb = 0;
+  const uint32_t first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
   if (d.ep) {   // ecology: energy on the grid; water and biomass on the grid and in live agents
-    unsigned long long sw = 0, sb = 0;
-    for (uint32_t c = threadIdx.x; c < wp.cells; c += blockDim.x) {
+    for (uint32_t c = first; c < wp.cells; c += stride) {
       const uint32_t g = wp.cell_off + c;
       s += (unsigned long long)d.ce[g];
       sw += (unsigned long long)d.cw[g];
       sb += (unsigned long long)d.cb[g];
     }
-    for (uint32_t j = threadIdx.x; j < wp.cap; j += blockDim.x) {
+    for (uint32_t j = first; j < wp.cap; j += stride) {
       const uint32_t g = wp.slot_off + j;
       if (d.flags[g] & kAlive) {
         sw += (unsigned long long)d.water[g];
         sb += (unsigned long long)d.biomass[g];
       }
     }
-    const unsigned long long t = block_sum_u64<kScanThreads>(s, red64);
-    const unsigned long long tw = block_sum_u64<kScanThreads>(sw, red64);
-    const unsigned long long tb = block_sum_u64<kScanThreads>(sb, red64);
-    if (threadIdx.x == 0) {
-      rec->resource_total = t;
-      rec->water_total = tw;
-      rec->biomass_total = tb;
+  } else {
+    for (uint32_t c = 4 * first; c < wp.cells; c += 4 * stride) {   // (the bytes past a ragged end: not counted)
+      const uint32_t v = *reinterpret_cast<const uint32_t*>(d.res + wp.cell_off + c);
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j)
+        if (c + j < wp.cells) s += (v >> (8 * j)) & 0xFFu;
     }
-    return;
   }
-  for (uint32_t c = threadIdx.x; c < wp.cells; c += blockDim.x) s += d.res[wp.cell_off + c];
-  const unsigned long long t = block_sum_u64<kScanThreads>(s, red64);
-  if (threadIdx.x == 0) rec->resource_total = t;
+  wave_add_u64(s, &cnt[0]);
+  wave_add_u64(sw, &cnt[1]);
+  wave_add_u64(sb, &cnt[2]);
+  __syncthreads();
+  eco_stats* rec = &d.ring[(uint64_t)w * kStatsRing + (d.wv[w].step % kStatsRing)];
+  uint64_t* to = threadIdx.x == 0 ? &rec->resource_total : (threadIdx.x == 1 ? &rec->water_total : &rec->biomass_total);
+  if (threadIdx.x < 3 && cnt[threadIdx.x]) atomicAdd(reinterpret_cast<unsigned long long*>(to), cnt[threadIdx.x]);
 }
 
 // ---------------------------------------------------------------------------
@@ -2479,28 +2368,58 @@ __global__ __launch_bounds__(256) void k_place_count(Dev d, const Tile* __restri
     atomicAdd(&cnt[place_bucket(pi, d.cellkeys[wp.cell_off + tl.start + i])], 1u);
 }
 
-// Per world (one block each): start[b] = exclusive prefix of the counts over the
-// world's buckets (start of world w's buckets at boff + w, one extra entry per
-// world holding its total), and the counts cleared for the scatter's cursors.
-__global__ __launch_bounds__(kScanThreads) void k_place_scan(const PlaceInfo* __restrict__ pinfo, uint32_t* cnt,
-                                                             uint32_t* start) {
-  __shared__ uint32_t red[kScanThreads / 64 + 1];
-  const uint32_t w = blockIdx.x;
+// start[b] = exclusive prefix of the counts over the world's buckets (start of world
+// w's buckets at boff + w, one extra entry per world holding its total), and the
+// counts cleared for the scatter's cursors.  Blocks (tile, world) of 4,096 buckets:
+// first each tile's sum (at boff / 4,096 + w + tile, apart for every world), then each
+// tile from the sums before it.  (One block for a whole world took 600 us at 262,144
+// buckets.)
+constexpr uint32_t kPlaceTile = 4096;
+__device__ __forceinline__ uint32_t place_sum_at(const PlaceInfo& pi, uint32_t w) { return pi.boff / kPlaceTile + w; }
+
+__device__ __forceinline__ uint4 place_counts(const uint32_t* cnt, uint32_t b, uint32_t hi) {
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (b < hi) v.x = cnt[b];
+  if (b + 1 < hi) v.y = cnt[b + 1];
+  if (b + 2 < hi) v.z = cnt[b + 2];
+  if (b + 3 < hi) v.w = cnt[b + 3];
+  return v;
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_place_sums(const PlaceInfo* __restrict__ pinfo, const uint32_t* cnt,
+                                                             uint32_t* sums) {
+  __shared__ unsigned long long red[kScanThreads / 64];
+  const uint32_t w = blockIdx.y;
   const PlaceInfo pi = pinfo[w];
   const uint32_t nb = pinfo[w + 1].boff - pi.boff;
-  const uint32_t per = (nb + kScanThreads - 1) / kScanThreads;
-  const uint32_t lo = pi.boff + threadIdx.x * per, hi = min(lo + per, pi.boff + nb);
-  uint32_t own = 0;
-  for (uint32_t b = lo; b < hi; ++b) own += cnt[b];
-  uint32_t total;
-  uint32_t run = block_exscan<kScanThreads>(own, red, &total);
-  for (uint32_t b = lo; b < hi; ++b) {
-    const uint32_t c = cnt[b];
-    start[b + w] = run;
-    run += c;
-    cnt[b] = 0;
-  }
-  if (threadIdx.x == 0) start[pi.boff + nb + w] = total;
+  if (blockIdx.x * kPlaceTile >= nb) return;
+  const uint4 v = place_counts(cnt, pi.boff + blockIdx.x * kPlaceTile + 4 * threadIdx.x, pi.boff + nb);
+  const unsigned long long t = block_sum_u64<kScanThreads>(v.x + v.y + v.z + v.w, red);
+  if (threadIdx.x == 0) sums[place_sum_at(pi, w) + blockIdx.x] = (uint32_t)t;
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_place_scan(const PlaceInfo* __restrict__ pinfo, uint32_t* cnt,
+                                                             const uint32_t* __restrict__ sums, uint32_t* start) {
+  __shared__ uint32_t red[kScanThreads / 64 + 1];
+  const uint32_t w = blockIdx.y;
+  const PlaceInfo pi = pinfo[w];
+  const uint32_t nb = pinfo[w + 1].boff - pi.boff, hi = pi.boff + nb;
+  if (blockIdx.x * kPlaceTile >= nb) return;
+  const uint32_t b = pi.boff + blockIdx.x * kPlaceTile + 4 * threadIdx.x;
+  const uint4 v = place_counts(cnt, b, hi);
+  uint32_t before = 0, total;
+  for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kScanThreads) before += sums[place_sum_at(pi, w) + t];
+  block_exscan<kScanThreads>(before, red, &before);   // (its total: the earlier tiles' sum)
+  uint32_t run = before + block_exscan<kScanThreads>(v.x + v.y + v.z + v.w, red, &total);
+  const uint32_t c[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (uint32_t j = 0; j < 4; ++j)
+    if (b + j < hi) {
+      start[b + j + w] = run;
+      run += c[j];
+      cnt[b + j] = 0;
+    }
+  if (threadIdx.x == 0 && (blockIdx.x + 1) * kPlaceTile >= nb) start[hi + w] = before + total;
 }
 
 // Each cell into its bucket (unordered within the bucket) of sorted[].
@@ -2559,27 +2478,77 @@ __global__ __launch_bounds__(kSlotTile) void k_init_agents(Dev d, const Tile* __
     }
     d.uid[g] = j;
     d.puid[g] = ~0ull;
-  } else {
+  } else {   // a free slot: no field is left as the allocation had it (a state read back is written as a whole)
     d.flags[g] = 0;
     d.trait[g] = 0.0;
+    d.pos[g] = 0;
+    d.facing[g] = 0;
+    d.energy[g] = 0;
+    d.age[g] = 0;
+    if (d.ep) d.water[g] = d.biomass[g] = d.hp[g] = 0;
+    d.uid[g] = 0;
+    d.puid[g] = 0;
+  }
+  if (j == 0) {
+    WorldVar v{};
+    v.uid_next = wp.n_init;
+    d.wv[tl.world] = v;
   }
 }
 
-// Initial weights of a list of (world, local slot) pairs, one block per entry
-// (persistent).  list == nullptr: every slot j < n_init of every world, with
-// entries enumerated through the per-world init counts.
-template <int WDT>
-__global__ __launch_bounds__(256) void k_emit_list(Dev d, Layout L, const uint32_t* __restrict__ list, uint32_t n,
-                                                   int mode, double std1, double std2, double std3) {
+// Weights of n agents, one block per agent (persistent): of every world's initial
+// agents in turn (list null), or of the list's (world, local slot) pairs; MODE W_INIT
+// (with the colour trait) or W_REQUANT.  Bound by the arithmetic of the noise, as the
+// births, whose writer it shares; nothing is cleared beforehand, since every byte that
+// is read is written here or by a birth.  With that clearing and one unit per thread
+// and turn, the row found by division and the quantised weights taken in a second
+// pass, a reset of 65,536 agents (64 wide layers) took 9.4 ms in FP32 and 11.6 in
+// BF16, now 3.7 and 4.2; FP8, 61,000 agents: 12.5, now 6.2.
+struct InitArgs {
+  Dev d;
+  Layout L;
+  const uint32_t* list;
+  uint32_t n;
+  double sd[3];
+};
+template <int WDT, int H, int MODE>
+__global__ __launch_bounds__(256) void k_init_weights(InitArgs by_value) {
+  __shared__ uint32_t off[kMaxWorlds + 1];
   __shared__ uint32_t s_amax[128 + 128 + 16];
   __shared__ double s_red[4];
   __shared__ double2 tab[kNoiseTable];
-  load_trig(d.trig, tab);
-  for (uint32_t e = blockIdx.x; e < n; e += gridDim.x) {
-    const uint32_t w = list[2 * e], j = list[2 * e + 1];
-    const WorldParams wp = d.wp[w];
+  {
+    const InitArgs& a = args<InitArgs>();
+    if (!a.list && threadIdx.x < 64) {   // prefix of the worlds' initial populations
+      const uint32_t n = a.d.n_worlds, per = (n + 63) / 64, lo = min(threadIdx.x * per, n), hi = min(lo + per, n);
+      uint32_t own = 0;
+      for (uint32_t i = lo; i < hi; ++i) own += a.d.wp[i].n_init;
+      const uint32_t inc = wave_scan(own);
+      uint32_t run = inc - own;
+      for (uint32_t i = lo; i < hi; ++i) {
+        off[i] = run;
+        run += a.d.wp[i].n_init;
+      }
+      if (threadIdx.x == 63) off[n] = inc;
+    }
+    load_trig(a.d.trig, tab);
+  }
+  auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  for (uint32_t e = blockIdx.x; e < args<InitArgs>().n; e += gridDim.x) {
+    const InitArgs& a = args<InitArgs>();
+    const Dev& d = a.d;
+    const uint32_t w = uniform(a.list ? a.list[2 * e] : find_world(off, d.n_worlds, e));
+    const uint32_t j = uniform(a.list ? a.list[2 * e + 1] : e - off[w]);
+    const WorldParams& wp = d.wp[w];
     const uint32_t g = wp.slot_off + j;
-    emit_agent<WDT>(d, L, wp, g, mode, j, std1, std2, std3, tab, s_amax, s_red);
+    if (MODE == W_INIT && d.colour && threadIdx.x == 0) {   // colour trait: U[0,1) per channel
+      const uint4 x = philox10(j, 0u, ST_COLOUR_INIT, 0u, wp.key0, wp.key1);
+      d.colour[g] = make_float4((float)(x.x >> 8) * 0x1p-24f, (float)(x.y >> 8) * 0x1p-24f,
+                                (float)(x.z >> 8) * 0x1p-24f, 0.0f);
+    }
+    const Noise nz{{a.sd[0], a.sd[1], a.sd[2]}, wp.key0, wp.key1, j, 0u};
+    const double t = write_weights<WDT, H, 256, MODE>(g, g, nz, part_rows<H>(0u, 0u), tab, s_amax, s_red);
+    if (threadIdx.x == 0) args<InitArgs>().d.trait[g] = t;
     __syncthreads();
   }
 }
@@ -2787,7 +2756,8 @@ hipError_t launch_render(hipStream_t s, const Dev& d, const TileScratch& ts, int
   ECO_CHECK_LAUNCH();
 }
 hipError_t launch_resource_total(hipStream_t s, const Dev& d, int only_world) {
-  hipLaunchKernelGGL(k_resource_total, dim3(d.n_worlds), dim3(kScanThreads), 0, s, d, only_world);
+  const uint32_t blocks = std::min<uint32_t>(64u, std::max<uint32_t>(1u, d.total_cells / 16384u));
+  hipLaunchKernelGGL(k_resource_total, dim3(blocks, d.n_worlds), dim3(256), 0, s, d, only_world);
   ECO_CHECK_LAUNCH();
 }
 hipError_t launch_init_cells(hipStream_t s, const Dev& d, const Tile* tiles, uint32_t nt) {
@@ -2796,13 +2766,16 @@ hipError_t launch_init_cells(hipStream_t s, const Dev& d, const Tile* tiles, uin
   ECO_CHECK_LAUNCH();
 }
 hipError_t launch_placement(hipStream_t s, const Dev& d, const Tile* cell_tiles, uint32_t nt, const void* pinfo,
-                            uint32_t* cnt, uint32_t* start) {
+                            uint32_t* cnt, uint32_t* sums, uint32_t* start, uint32_t most_buckets) {
   if (nt == 0) return hipSuccess;
   const PlaceInfo* pi = reinterpret_cast<const PlaceInfo*>(pinfo);
   hipLaunchKernelGGL(k_place_count, dim3(nt), dim3(256), 0, s, d, cell_tiles, pi, cnt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_place_scan, dim3(d.n_worlds), dim3(kScanThreads), 0, s, pi, cnt, start);
+  const dim3 tiles((most_buckets + kPlaceTile - 1) / kPlaceTile, d.n_worlds);
+  hipLaunchKernelGGL(k_place_sums, tiles, dim3(kScanThreads), 0, s, pi, cnt, sums);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_place_scan, tiles, dim3(kScanThreads), 0, s, pi, cnt, sums, start);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(k_place_scatter, dim3(nt), dim3(256), 0, s, d, cell_tiles, pi, cnt, start);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -2814,16 +2787,32 @@ hipError_t launch_init_agents(hipStream_t s, const Dev& d, const Tile* tiles, ui
   hipLaunchKernelGGL(k_init_agents, dim3(nt), dim3(kSlotTile), 0, s, d, tiles);
   ECO_CHECK_LAUNCH();
 }
-hipError_t launch_emit_list(hipStream_t s, const Dev& d, const Layout& L, const uint32_t* list, uint32_t n, int mode,
-                            double std1, double std2, double std3, uint32_t blocks) {
-  if (n == 0) return hipSuccess;
-  if (L.wdtype == 0)
-    hipLaunchKernelGGL(k_emit_list<0>, dim3(blocks), dim3(256), 0, s, d, L, list, n, mode, std1, std2, std3);
-  else if (L.wdtype == 1)
-    hipLaunchKernelGGL(k_emit_list<1>, dim3(blocks), dim3(256), 0, s, d, L, list, n, mode, std1, std2, std3);
-  else
-    hipLaunchKernelGGL(k_emit_list<2>, dim3(blocks), dim3(256), 0, s, d, L, list, n, mode, std1, std2, std3);
+template <int WDT, int H>
+hipError_t launch_init_weights_wh(hipStream_t s, const InitArgs& a, uint32_t n_cus, bool requant) {
+  int per_cu = 1;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &per_cu, reinterpret_cast<const void*>(&k_init_weights<WDT, H, W_INIT>), 256, 0);
+  if (e != hipSuccess) return e;
+  const dim3 grid(std::min<uint32_t>(a.n, n_cus * (uint32_t)std::max(1, per_cu)));
+  if (requant) hipLaunchKernelGGL((k_init_weights<WDT, H, W_REQUANT>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_init_weights<WDT, H, W_INIT>), grid, dim3(256), 0, s, a);
   ECO_CHECK_LAUNCH();
+}
+// Initial (or, requant, re-quantised) weights of n agents: the list's, or without one
+// every world's initial agents.
+hipError_t launch_init_weights(hipStream_t s, const Dev& d, const Layout& L, const uint32_t* list, uint32_t n,
+                               bool requant, double std1, double std2, double std3, uint32_t n_cus) {
+  if (n == 0) return hipSuccess;
+  if (L.H1 != L.H2 || (L.H1 != 32 && L.H1 != 64 && L.H1 != 128)) return hipErrorInvalidValue;
+  const InitArgs a{d, L, list, n, {std1, std2, std3}};
+#define ECO_INIT(WW)                                                              \
+  if (L.H1 == 32) return launch_init_weights_wh<WW, 32>(s, a, n_cus, requant);    \
+  else if (L.H1 == 64) return launch_init_weights_wh<WW, 64>(s, a, n_cus, requant); \
+  else return launch_init_weights_wh<WW, 128>(s, a, n_cus, requant);
+  if (L.wdtype == 0) { ECO_INIT(0) }
+  if (L.wdtype == 1) { ECO_INIT(1) }
+  ECO_INIT(2)
+#undef ECO_INIT
 }
 
 }  // namespace eco

@@ -1,0 +1,73 @@
+"""Initial worlds: weights, placement and records of several worlds in one object
+against the oracle, again after a reset with other seeds, and of slots that a written
+state brings to life.  D = 40 gives an even and D = 44 an odd number of four-input
+blocks a row; 90,000 cells rank their placement keys over several tiles of buckets.
+"""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2510_18221_amd import workloads as wl
+
+from gpu_util import assert_stats_match, assert_weights_close, compare_world, need_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def eco():
+    need_gpu()
+    from paper_2510_18221_amd import eco as m
+    m.lib()
+    return m
+
+
+def worlds(wdtype, hidden, n_scalars, ecology=False):
+    mk = wl.ecology_desc if ecology else wl.desc
+    kw = dict(window=3, n_scalars=n_scalars, hidden1=hidden, hidden2=hidden, wdtype=wdtype, resource_density=0.15)
+    if not ecology:
+        kw["n_actions"] = 7
+    return [mk(width=300, height=300, n_agents_init=400, capacity=1001, seed=3, **kw),
+            mk(width=9, height=7, n_agents_init=0, capacity=1, seed=4, **kw),
+            mk(width=51, height=49, n_agents_init=77, capacity=77, seed=5, **kw),
+            mk(width=16, height=16, n_agents_init=1, capacity=300, seed=6, **kw)]
+
+
+@pytest.mark.parametrize("hidden", [32, 64, 128])
+@pytest.mark.parametrize("wdtype", [wl.FP32, wl.BF16, wl.FP8])
+@pytest.mark.parametrize("n_scalars", [4, 8])
+def test_initial_worlds_match_oracle(eco, wdtype, hidden, n_scalars):
+    cfgs = worlds(wdtype, hidden, n_scalars)
+    gw = eco.World(cfgs)
+    for seeds in (None, [11, 12, 13, 14]):
+        if seeds:
+            gw.step(3)   # deaths and births leave their traces in the slots
+            gw.reset(seeds)
+            cfgs = [dict(c, seed=s) for c, s in zip(cfgs, seeds)]
+        stats = gw.stats()
+        for i, cfg in enumerate(cfgs):
+            ow = orc.OracleWorld(cfg)
+            compare_world(gw, ow, f"world {i} seeds {seeds}", i, weights_slots=60)
+            assert_stats_match(stats[i], ow.stats(), f"world {i} seeds {seeds}")
+            for master in (False, True):   # a slot no agent has had
+                if cfg["capacity"] > cfg["n_agents_init"]:
+                    assert not gw.read_weights(cfg["capacity"] - 1, i, master=master).any()
+    gw.close()
+
+
+@pytest.mark.parametrize("ecology", [False, True])
+@pytest.mark.parametrize("wdtype", [wl.FP32, wl.BF16, wl.FP8])
+def test_revived_slots_have_their_initial_weights(eco, wdtype, ecology):
+    cfgs = worlds(wdtype, 32, 8, ecology)
+    gw = eco.World(cfgs)
+    full = dict(cfgs[3], n_agents_init=200)   # the same seed: slots 0 - 199 have their initial weights here
+    ow = orc.OracleWorld(full)
+    st = gw.read_state(3)
+    gw.write_state(st, 3)                     # as it was read, free slots included
+    src = ow.state()
+    for k in src:
+        st[k] = src[k]
+    gw.write_state(st, 3)
+    compare_world(gw, ow, "revived", 3, weights_slots=200)
+    assert_stats_match(gw.stats()[3], ow.stats(), "revived")
+    gw.close()

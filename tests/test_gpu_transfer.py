@@ -42,7 +42,7 @@ def random_state(eco, cfg, rng, ecology):
 
 
 # slots and cells of the written world: a few, odd, arrays around 256 KiB (65,536 int32),
-# and together above the 2 MiB buffer
+# and together above the 1 MiB buffer
 @pytest.mark.parametrize("cap,w,h", [(1, 3, 3), (37, 9, 7), (1001, 51, 49), (65536, 256, 256), (65537, 257, 256),
                                      (140001, 401, 399)])
 @pytest.mark.parametrize("ecology", [False, True])
