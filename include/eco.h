@@ -222,9 +222,9 @@ typedef struct {
 } eco_info;
 
 /* Per-kernel GPU time accumulated while ECO_RT_TIME_KERNELS is set.  The cell pass
-   (REGROW, SENSE) runs in the BIRTH_CLAIM launch; both stay at zero.  BIRTH_COMMIT
-   (births) and COMPACT (live list and records) are two roles of one launch, made
-   apart in eager timed steps. */
+   (REGROW, SENSE) runs in the BIRTH_CLAIM launch; both stay at zero.  BIRTH_SCAN
+   (records), BIRTH_COMMIT (births) and COMPACT (live list) are roles of one launch,
+   made apart in eager timed steps. */
 enum { ECO_K_FORWARD = 0, ECO_K_MOVE = 1, ECO_K_BIRTH_CLAIM = 2, ECO_K_BIRTH_SCAN = 3,
        ECO_K_BIRTH_COMMIT = 4, ECO_K_REGROW = 5, ECO_K_COMPACT = 6, ECO_K_SENSE = 7, ECO_K_COUNT = 8 };
 typedef struct {

@@ -24,7 +24,7 @@ namespace eco {
 constexpr int kStatsRing = 1024;
 constexpr int ECO_MAX_WORLDS = 1024;   // worlds of one object at most
 constexpr uint32_t ECO_MAX_PARTS = 8192;   // blocks sharing children in one birth launch at most
-constexpr uint8_t kAlive = 1, kBirthClaim = 2, kBirthWon = 4;
+constexpr uint8_t kAlive = 1;
 enum Action : uint8_t { REST = 0, TURN_L = 1, TURN_R = 2, FORWARD = 3, EAT = 4, REPRODUCE = 5, ATTACK = 6 };
 // The ecology's eight actions: EAT (4) takes energy, then water, biomass, reproduce;
 // with attacks a ninth, attack.
@@ -67,7 +67,7 @@ static_assert(sizeof(WorldVar) == 64, "whole 16-byte units");
 constexpr int kSlotPart = 16;    // u32 counters per slot tile
 constexpr int kCellPart = 4;     // u64 counters per cell tile
 enum { PC_HIST = 0, PC_MOVES_OK = 9, PC_MOVES_BLOCKED = 10, PC_EATEN = 11, PC_DEATHS = 12, PC_BB_CELL = 13,
-       PC_KILLED = 14, PC_CLAIMS = 15 };
+       PC_KILLED = 14 };
 
 // What one world's statistics record needs besides its births: summed once the
 // moves, the birth claims and the cell pass of the step are done, completed by the

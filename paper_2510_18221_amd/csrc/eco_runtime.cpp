@@ -28,7 +28,6 @@ hipError_t launch_forward_w2(int H, int U, dim3 grid, dim3 block, size_t shmem, 
 hipError_t launch_move(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t H);
 hipError_t launch_settle(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t H, uint32_t small);
 hipError_t launch_claim_cells(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A);
-hipError_t launch_birth_rank(hipStream_t s, const Dev& d, const TileScratch& ts);
 hipError_t launch_birth_commit(hipStream_t s, const Dev& d, const Layout& L, const TileScratch& ts, uint32_t births,
                                uint32_t ranked, int roles);
 hipError_t launch_step_small(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A, uint32_t H);
@@ -503,21 +502,21 @@ const char* group_name(int k) {
     case ECO_K_FORWARD: return "forward kernel";
     case ECO_K_MOVE: return "move kernel";
     case ECO_K_BIRTH_CLAIM: return "birth claim / cell kernel";
-    case ECO_K_BIRTH_SCAN: return "birth ranking kernel";
+    case ECO_K_BIRTH_SCAN: return "record kernel";
     case ECO_K_BIRTH_COMMIT: return "birth commit kernel";
     default: return "live list kernel";
   }
 }
-// The births and the live list with the records are two roles of one launch, made
-// apart only to be timed apart.
+// The records, the births and the live list are roles of one launch, made apart only
+// to be timed apart.
 hipError_t launch_group(eco_world* w, hipStream_t s, const Dev& d, const TileScratch& ts, int k, bool timed) {
   switch (k) {
     case ECO_K_FORWARD: return launch_forward(w, s, d, w->launch);
     case ECO_K_MOVE: return launch_move(s, d, ts, w->L.H1);
     case ECO_K_BIRTH_CLAIM: return launch_claim_cells(s, d, ts, w->L.A);
-    case ECO_K_BIRTH_SCAN: return launch_birth_rank(s, d, ts);
+    case ECO_K_BIRTH_SCAN: return launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 0, 4);
     case ECO_K_BIRTH_COMMIT: return launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 0, 1);
-    default: return launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 0, timed ? 2 : 3);
+    default: return launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 0, timed ? 2 : 7);
   }
 }
 
@@ -554,7 +553,7 @@ eco_status enqueue_step(eco_world* w, hipStream_t s, const Dev& d, const TileScr
         HIPCHK(w, launch_forward(w, s, d, w->launch), "forward kernel");
       } else {
         HIPCHK(w, launch_step_small(s, d, ts, w->L.A, w->L.H1), "small-world step kernel");
-        HIPCHK(w, launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 1, 3), "birth commit kernel");
+        HIPCHK(w, launch_birth_commit(s, d, w->L, ts, birth_blocks(w), 1, 7), "birth commit kernel");
       }
       if (timed) {
         HIPCHK(w, hipEventRecord(b, s), "event record");
@@ -564,7 +563,7 @@ eco_status enqueue_step(eco_world* w, hipStream_t s, const Dev& d, const TileScr
     return ECO_OK;
   }
   for (int k : kStepGroups) {
-    if (!timed && k == ECO_K_BIRTH_COMMIT) continue;   // with the live list, below
+    if (!timed && (k == ECO_K_BIRTH_SCAN || k == ECO_K_BIRTH_COMMIT)) continue;   // with the live list, below
     hipEvent_t a = nullptr, b = nullptr;
     if (timed) {
       a = take_event(w);
@@ -1150,8 +1149,8 @@ eco_status eco_world_step_static(eco_world* w, uint32_t n_steps) {
   ts.tm2 = reinterpret_cast<double*>(b + o_tm2);
   ts.ecosum = w->L.ecology ? reinterpret_cast<unsigned long long*>(b + o_ecosum) : nullptr;
   // every part is written by the step before it is read (the tile counters by
-  // the move, claim and compaction passes, the birth lists and counters by the
-  // ranking pass), so nothing needs clearing between calls
+  // the move and claim passes, the birth lists and counters by the claim pass), so
+  // nothing needs clearing between calls
   for (uint32_t i = 0; i < n_steps; ++i) {
     st = enqueue_step(w, w->stream, d, ts, false);
     if (st != ECO_OK) return st;

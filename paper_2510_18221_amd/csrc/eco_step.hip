@@ -5,26 +5,24 @@
 //   k_move         winners move; EAT; step cost; death at energy <= 0; age
 //                  (Sec. 3.2 "Resources and Agent Health", "Actions")
 //   k_claim_cells  slot tiles: eligible parents claim the empty cell behind them
-//                  (Sec. 3.2 "Actions": child placed directly behind the parent),
-//                  the free slots are listed in ascending order (the recycled-slot
+//                  (Sec. 3.2 "Actions": child placed directly behind the parent) and
+//                  the winners are listed in slot order, the free slots are listed in ascending order (the recycled-slot
 //                  free list), the survivors' sums; cell tiles: each empty cell
 //                  regrows one unit with probability p (Sec. 3.2: energy slowly
 //                  grows back) and the window channels of the next step
-//   k_birth_rank   claim winners of each slot tile in slot order; one block per
-//                  world drafts its statistics
 //   k_birth_commit births: child state + child weights = parent + sigma * N(0,1)
 //                  (Sec. 3.3 mutation) into the recycled slot; slot tiles: the
 //                  live list of the next step; the statistics record (App. E
 //                  measurement interface) and the clock
-// Each launch needs what the one before it wrote anywhere in the world, so four is
+// Each launch needs what the one before it wrote anywhere in the world, so three is
 // the least without a barrier across the grid, and a launch of this size costs its
 // chain of dependent loads (2 - 4 us, next to 1.7 us for an empty one) whatever
 // little it does: the step after the policy kernel of the 256 x 256 ecology world
 // with 4,213 agents took 35 us in seven launches (moves, claims + regrowth, two
-// ranking passes, births, two compaction passes with the cell pass) and takes
-// 24 us in four.
-// Every contended write is an atomicMin on a claim word; every other write goes
-// to a unique slot or cell, so the integer state is independent of scheduling.
+// ranking passes, births, two compaction passes with the cell pass), 22 in four
+// (a ranking pass between the claims and the births) and takes 20 us in three.
+// Every contended write of a move is an atomicMin on a claim word; every other write
+// goes to a unique slot or cell, so the integer state is independent of scheduling.
 #include <algorithm>
 #include <mutex>
 
@@ -205,9 +203,6 @@ __device__ __forceinline__ Tile cell_tile(const TileScratch& ts, uint32_t i) {
 // World w's slot and cell offsets (zero without a load where it is the only one).
 __device__ __forceinline__ uint32_t slot_offset(const Dev& d, const TileScratch& ts, uint32_t w) {
   return ts.cap0 ? 0u : d.wp[w].slot_off;
-}
-__device__ __forceinline__ uint32_t cell_offset(const Dev& d, const TileScratch& ts, uint32_t w) {
-  return ts.cap0 ? 0u : d.wp[w].cell_off;
 }
 __device__ __forceinline__ uint32_t first_slot_tile(const TileScratch& ts, uint32_t w) {
   return ts.cap0 ? 0u : ts.tile_rng[4 * w];
@@ -527,7 +522,7 @@ __global__ __launch_bounds__(kSlotTile) void k_move(Dev d, TileScratch ts, uint3
   const uint64_t fm = __ballot(in && !alive);
   if ((threadIdx.x & 63u) == 0) s_free[threadIdx.x >> 6] = (uint32_t)__builtin_popcountll(fm);
   __syncthreads();
-  if (threadIdx.x < kSlotPart && threadIdx.x != PC_BB_CELL && threadIdx.x != PC_CLAIMS)   // these two: the birth claims
+  if (threadIdx.x < kSlotPart && threadIdx.x != PC_BB_CELL)   // that one: the birth claims
     ts.part_slot[blockIdx.x * kSlotPart + threadIdx.x] = cnt[threadIdx.x];
   if (threadIdx.x == 0) {
     uint32_t f = 0;
@@ -538,29 +533,53 @@ __global__ __launch_bounds__(kSlotTile) void k_move(Dev d, TileScratch ts, uint3
   }
 }
 
-// One live agent's birth claim after the moves: an eligible parent claims the empty
-// cell directly behind it (lowest slot wins, atomicMin) and 1 is returned; 2 when
-// that cell is taken or walled (a blocked parent), else 0.  water, biomass: what it
-// carries, in the ecology.
-__device__ __forceinline__ int birth_claim_agent(const Dev& d, const WorldParams& wp, uint32_t w, uint32_t slot,
-                                                 uint32_t n_actions, uint8_t fl, int act, int pos, int facing, int energy,
-                                                 int water, int biomass) {
-  bool eligible = energy >= wp.e_repro && (n_actions == 5 || act == REPRODUCE);
+// Whether a live agent can be a parent this step (water, biomass: what it carries, in
+// the ecology).
+__device__ __forceinline__ bool may_bear(const Dev& d, const WorldParams& wp, uint32_t w, uint32_t n_actions, int act,
+                                         int energy, int water, int biomass) {
   if (d.ep) {   // ecology: the eighth action, and spare biomass and water to give the child
     const eco_ecology& e = d.ep[w];
-    eligible = act == REPRODUCE_ECO && energy >= wp.e_repro && water >= e.w_child && biomass >= e.b_repro;
+    return act == REPRODUCE_ECO && energy >= wp.e_repro && water >= e.w_child && biomass >= e.b_repro;
   }
-  if (!eligible) return 0;
-  const uint32_t t = neighbour(wp, (uint32_t)pos, facing, -1);
-  const bool walled = wp.has_walls && d.wall[wp.cell_off + t];
-  if (d.occ[wp.cell_off + t] != -1 || walled) return 2;
-  atomicMin(&d.claim[wp.cell_off + t], slot);
-  d.tgt[slot] = (int)t;
-  d.flags[slot] = fl | kBirthClaim;
-  return 1;
+  return energy >= wp.e_repro && (n_actions == 5 || act == REPRODUCE);
 }
 
-// Birth claims of one slot tile, the free list of the tile (its free slots at
+// One live agent's birth claim after the moves: a parent claims the cell directly
+// behind it, which must be empty, and the lowest slot of its claimants wins.  The
+// others can only be the agents on the cell's other three sides that face away from it,
+// so each claimant looks at them itself: nothing in this pass changes what it reads.
+// (An atomic minimum on a word per cell, read by the next launch, cost 2 - 3 us of this
+// launch and that launch.)
+enum ClaimResult { CLAIM_NONE, CLAIM_WON, CLAIM_BLOCKED };
+__device__ __forceinline__ int birth_claim_agent(const Dev& d, const WorldParams& wp, uint32_t w, uint32_t slot,
+                                                 uint32_t n_actions, int act, int pos, int facing, int energy,
+                                                 int water, int biomass) {
+  if (!may_bear(d, wp, w, n_actions, act, energy, water, biomass)) return CLAIM_NONE;
+  const uint32_t t = neighbour(wp, (uint32_t)pos, facing, -1);
+  const bool walled = wp.has_walls && d.wall[wp.cell_off + t];
+  const int on = d.occ[wp.cell_off + t];
+  int o[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) o[k] = d.occ[wp.cell_off + neighbour(wp, t, (facing + k + 1) & 3, +1)];
+  if (on != -1 || walled) return CLAIM_BLOCKED;
+  bool lost = false;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint32_t other = wp.slot_off + (uint32_t)o[k];
+    if (o[k] < 0 || other >= slot) continue;
+    const int f = d.facing[other], a = d.act[other], e = d.energy[other];
+    const int cw = d.ep ? d.water[other] : 0, cb = d.ep ? d.biomass[other] : 0;
+    lost |= f == ((facing + k + 1) & 3) && may_bear(d, wp, w, n_actions, a, e, cw, cb);
+  }
+  if (lost) return CLAIM_BLOCKED;
+  d.tgt[slot] = (int)t;
+  return CLAIM_WON;
+}
+
+// Birth claims of one slot tile (its winners in slot order, as places in the tile, and
+// their number to scan[0], with several worlds also to the world's n_win; one world's
+// births are summed from scan[0], since the additions of some hundred tiles to one word
+// cost 3 us), the free list of the tile (its free slots at
 // their ranks among the world's, the earlier tiles' counts summed here) and the
 // survivors' sums: count, energy, trait mean and squared deviations from it, and in
 // the ecology what they carry (births move these from parent to child, so they
@@ -568,7 +587,7 @@ __device__ __forceinline__ int birth_claim_agent(const Dev& d, const WorldParams
 // slots, then every wave reads the four waves' results.
 __device__ __forceinline__ void claim_tile(const Dev& d, const TileScratch& ts, uint32_t tile, uint32_t n_actions) {
   constexpr int NW = kSlotTile / 64;
-  __shared__ uint32_t s_alive[NW], s_free[NW], s_before[NW], s_claims[NW], s_blocked[NW];
+  __shared__ uint32_t s_alive[NW], s_free[NW], s_before[NW], s_won[NW], s_blocked[NW];
   __shared__ unsigned long long s_e[NW], s_eco[3][NW];
   __shared__ double s_mean[NW], s_m2[NW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -596,10 +615,10 @@ __device__ __forceinline__ void claim_tile(const Dev& d, const TileScratch& ts, 
   uint32_t before = 0;   // free slots of the world's earlier tiles
   for (uint32_t t = first_slot_tile(ts, w) + threadIdx.x; t < tile; t += kSlotTile) before += ts.scan[t * 4 + 1];
   const bool alive = (fl & kAlive) != 0;
-  int claim = 0;
-  if (alive) claim = birth_claim_agent(d, wp, w, slot, n_actions, fl, act, pos, facing, energy, water, biomass);
+  int claim = CLAIM_NONE;
+  if (alive) claim = birth_claim_agent(d, wp, w, slot, n_actions, act, pos, facing, energy, water, biomass);
   const uint64_t am = __ballot(alive), fm = __ballot(in && !alive);
-  const uint64_t cm = __ballot(claim == 1), bm = __ballot(claim == 2);
+  const uint64_t wm = __ballot(claim == CLAIM_WON), bm = __ballot(claim == CLAIM_BLOCKED);
   const uint32_t n = (uint32_t)__builtin_popcountll(am);
   const unsigned long long es = wave_scan(alive ? (unsigned long long)(long long)energy : 0ull);
   const double mean = n ? lane_value(wave_scan(alive ? trait : 0.0), 63) / (double)n : 0.0;
@@ -615,7 +634,7 @@ __device__ __forceinline__ void claim_tile(const Dev& d, const TileScratch& ts, 
     s_alive[wave] = n;
     s_free[wave] = (uint32_t)__builtin_popcountll(fm);
     s_before[wave] = before;
-    s_claims[wave] = (uint32_t)__builtin_popcountll(cm);
+    s_won[wave] = (uint32_t)__builtin_popcountll(wm);
     s_blocked[wave] = (uint32_t)__builtin_popcountll(bm);
     s_e[wave] = es;
     s_mean[wave] = mean;
@@ -624,22 +643,26 @@ __device__ __forceinline__ void claim_tile(const Dev& d, const TileScratch& ts, 
     for (int k = 0; k < 3; ++k) s_eco[k][wave] = carried[k];
   }
   __syncthreads();
-  uint32_t first = 0, tot_before = 0;   // free rank of the wave's first free slot
+  uint32_t first = 0, tot_before = 0, won_before = 0;   // free rank of the wave's first free slot
 #pragma unroll
   for (int i = 0; i < NW; ++i) {
     tot_before += s_before[i];
-    if (i < wave) first += s_free[i];
+    if (i < wave) {
+      first += s_free[i];
+      won_before += s_won[i];
+    }
   }
+  if (claim == CLAIM_WON) d.bparent[slot_off + tl.start + won_before + lanes_before(wm)] = (int)threadIdx.x;
   if (in && !alive) d.freel[slot_off + tot_before + first + lanes_before(fm)] = (int)local;
   if (threadIdx.x == 0) {
-    uint32_t N = 0, F = 0, C = 0, B = 0;
+    uint32_t N = 0, F = 0, won = 0, B = 0;
     unsigned long long E = 0, cw = 0, cb = 0, ch = 0;
     double sum = 0.0, M2 = 0.0;
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       N += s_alive[i];
       F += s_free[i];
-      C += s_claims[i];
+      won += s_won[i];
       B += s_blocked[i];
       E += s_e[i];
       cw += s_eco[0][i];
@@ -651,7 +674,8 @@ __device__ __forceinline__ void claim_tile(const Dev& d, const TileScratch& ts, 
 #pragma unroll
     for (int i = 0; i < NW; ++i) M2 += s_m2[i] + (double)s_alive[i] * (s_mean[i] - mu) * (s_mean[i] - mu);
     ts.part_slot[tile * kSlotPart + PC_BB_CELL] = B;
-    ts.part_slot[tile * kSlotPart + PC_CLAIMS] = C;
+    ts.scan[tile * 4] = won;
+    if (won && !ts.cap0) atomicAdd(&d.wv[w].n_win, won);
     ts.scan[tile * 4 + 2] = tot_before;
     ts.esum[tile] = (long long)E;
     ts.tmean[tile] = mu;
@@ -661,7 +685,11 @@ __device__ __forceinline__ void claim_tile(const Dev& d, const TileScratch& ts, 
       ts.ecosum[3 * tile + 1] = cb;
       ts.ecosum[3 * tile + 2] = ch;
     }
-    if (tile + 1 == end_slot_tile(ts, w)) d.wv[w].n_free = tot_before + F;
+    if (tile + 1 == end_slot_tile(ts, w)) {   // what the births need, beside the record that advances the clock
+      d.wv[w].n_free = tot_before + F;
+      d.draft[w].step = d.wv[w].step;
+      d.draft[w].uid_next = d.wv[w].uid_next;
+    }
   }
 }
 
@@ -846,7 +874,7 @@ __device__ __forceinline__ uint32_t sat255(int v) { return (uint32_t)min(max(v, 
 // GROW (a step): each empty cell regrows one unit with probability p, and the
 // regrown cells and the resource total go to cnt[0], cnt[1] (LDS).  Then the
 // cell's window channels, from the resources just grown and the occupants after the
-// moves (a birth adds its own, patch_birth_cells), so the grid is read once a step.  agent,
+// moves (a birth adds its own, place_child), so the grid is read once a step.  agent,
 // col: the occupants' sense bits by cell and colour words by slot, where the caller
 // has them in LDS; else they are read through the occupancy.
 template <bool GROW>
@@ -1058,7 +1086,7 @@ __global__ __launch_bounds__(256) void k_claim_cells(Dev d, TileScratch ts, uint
 // deviations about it: M2 = sum (M2_i + n_i (mean_i - mean)^2); the slot tiles of a
 // world hold 256 slots each but the last).
 template <int NT>
-__device__ void world_draft(const Dev& d, const TileScratch& ts, uint32_t w) {
+__device__ __forceinline__ void world_draft(const Dev& d, const TileScratch& ts, uint32_t w, StepDraft* dr) {
   constexpr int NW = NT / 64;
   __shared__ uint32_t s_cnt[kSlotPart + 1][NW];
   __shared__ unsigned long long s_sum[kCellPart + 4][NW];
@@ -1132,7 +1160,6 @@ __device__ void world_draft(const Dev& d, const TileScratch& ts, uint32_t w) {
   m2 = wave_scan(m2);
   if (lane == 63) s_m2[wave] = m2;
   __syncthreads();
-  StepDraft* dr = d.draft + w;
   if (threadIdx.x < kSlotPart) {
     uint32_t v = 0;
 #pragma unroll
@@ -1162,51 +1189,7 @@ __device__ void world_draft(const Dev& d, const TileScratch& ts, uint32_t w) {
     dr->step = d.wv[w].step;
     dr->uid_next = d.wv[w].uid_next;
   }
-}
-
-// Birth ranking.  Slot tiles: the tile's claim winners (their claim word holds
-// their slot), in slot order, as places in the tile; their number to scan[0], and with
-// several worlds to the world's n_win (one world's births are summed from scan[0]:
-// the additions of some hundred tiles to one word cost 3 us).  Then one block per world drafts its statistics, and with
-// terrain a block per cell tile settles the water.
-__global__ __launch_bounds__(kSlotTile) void k_birth_rank(Dev d, TileScratch ts) {
-  __shared__ uint32_t s_win[kSlotTile / 64];
-  if (blockIdx.x >= ts.n_slot_tiles) {
-    const uint32_t b = blockIdx.x - ts.n_slot_tiles;
-    if (b < d.n_worlds) {
-      world_draft<kSlotTile>(d, ts, b);
-    } else {
-      const Tile ct = cell_tile(ts, b - d.n_worlds);
-      settle_water(d, d.wp[ct.world], ct);
-    }
-    return;
-  }
-  const Tile tl = slot_tile(ts, blockIdx.x);
-  const uint32_t slot_off = slot_offset(d, ts, tl.world), cell_off = cell_offset(d, ts, tl.world);
-  const bool in = threadIdx.x < tl.count;
-  const uint32_t first = slot_off + tl.start, slot = first + threadIdx.x;
-  uint8_t fl = 0;
-  int t = 0;
-  if (in) {
-    fl = d.flags[slot];
-    t = d.tgt[slot];
-  }
-  const bool won = (fl & kBirthClaim) && d.claim[cell_off + t] == slot;
-  const uint64_t wm = __ballot(won);
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63u) == 0) s_win[wave] = (uint32_t)__builtin_popcountll(wm);
   __syncthreads();
-  uint32_t before = 0, total = 0;
-#pragma unroll
-  for (int i = 0; i < kSlotTile / 64; ++i) {
-    if (i < wave) before += s_win[i];
-    total += s_win[i];
-  }
-  if (won) d.bparent[first + before + lanes_before(wm)] = (int)threadIdx.x;
-  if (threadIdx.x == 0) {
-    ts.scan[blockIdx.x * 4] = total;
-    if (total && !ts.cap0) atomicAdd(&d.wv[tl.world].n_win, total);
-  }
 }
 
 // Births of a world this step: its winners, as far as free slots go (an object of
@@ -1423,7 +1406,7 @@ struct CommitArgs {
   Dev d;
   Layout L;
   TileScratch ts;
-  uint32_t base, n_birth_blocks, ranked;
+  uint32_t base, first_birth, n_birth_blocks, ranked;   // first_birth: the first birth block's number
 };
 template <typename A = CommitArgs>
 __device__ __forceinline__ const A& args() {
@@ -1603,12 +1586,14 @@ __device__ __forceinline__ void place_child(const Dev& d, uint32_t w, uint32_t k
   }
 }
 
-// World w's statistics record and the clock advance (one block): its draft
-// completed by the births.  With births, the trait moments follow once
+// World w's statistics record and the clock advance (one block): its draft (made here,
+// or by the small-world kernel) completed by the births.  With births, the trait moments follow once
 // the children are written (settle_record).
 __device__ __forceinline__ void world_record(const Dev& d, const TileScratch& ts, uint32_t w, bool ranked) {
   __shared__ uint32_t s_win[kSlotTile / 64];
-  const StepDraft dr = d.draft[w];
+  __shared__ StepDraft drafted;
+  if (!ranked) world_draft<kSlotTile>(d, ts, w, &drafted);
+  const StepDraft& dr = ranked ? d.draft[w] : drafted;
   WorldVar& v = d.wv[w];
   uint32_t nw = v.n_win;
   const uint32_t n_free = v.n_free;
@@ -1641,7 +1626,7 @@ __device__ __forceinline__ void world_record(const Dev& d, const TileScratch& ts
   st.regrown = dr.regrown;
   st.moves_ok = dr.count[PC_MOVES_OK];
   st.moves_blocked = dr.count[PC_MOVES_BLOCKED];
-  st.births_blocked_cell = dr.count[PC_CLAIMS] - nw + dr.count[PC_BB_CELL];
+  st.births_blocked_cell = dr.count[PC_BB_CELL];
   st.births_blocked_capacity = nw - nb;
   st.resource_total = dr.resource_total;
   for (int a = 0; a < 9; ++a) st.action_hist[a] = dr.count[PC_HIST + a];
@@ -1659,14 +1644,14 @@ __device__ __forceinline__ void world_record(const Dev& d, const TileScratch& ts
 // The next step's live list of one slot tile: the survivors and the free slots
 // whose rank is below the world's births, in slot order (the live slots before the
 // tile are the slots that were not free there and the births among those that
-// were); the tile's flags, and its claim words released.
+// were), and the tile's flags.
 __device__ __forceinline__ void live_tile(const Dev& d, const TileScratch& ts, uint32_t tile, bool ranked) {
   constexpr int NW = kSlotTile / 64;
   __shared__ uint32_t s_live[NW], s_free[NW], s_win[NW];
   const int wave = threadIdx.x >> 6;
   const Tile tl = slot_tile(ts, tile);
   const uint32_t w = tl.world;
-  const uint32_t slot_off = slot_offset(d, ts, w), cell_off = cell_offset(d, ts, w);
+  const uint32_t slot_off = slot_offset(d, ts, w);
   const uint32_t free_before = ts.scan[tile * 4 + 2], n_free = d.wv[w].n_free, n_win = d.wv[w].n_win;
   const bool summed = ts.cap0 && !ranked;
   uint32_t win = 0;
@@ -1674,12 +1659,7 @@ __device__ __forceinline__ void live_tile(const Dev& d, const TileScratch& ts, u
     for (uint32_t i = threadIdx.x; i < ts.n_slot_tiles; i += kSlotTile) win += ts.scan[i * 4];
   const bool in = threadIdx.x < tl.count;
   const uint32_t local = tl.start + threadIdx.x, slot = slot_off + local;
-  uint8_t fl = 0;
-  int t = 0;
-  if (in) {
-    fl = d.flags[slot];
-    t = d.tgt[slot];
-  }
+  const uint8_t fl = in ? d.flags[slot] : (uint8_t)0;
   const bool survivor = (fl & kAlive) != 0;
   const uint64_t am = __ballot(survivor), fm = __ballot(in && !survivor);
   win = wave_scan(win);
@@ -1705,11 +1685,11 @@ __device__ __forceinline__ void live_tile(const Dev& d, const TileScratch& ts, u
   if (alive) d.live[slot_off + (tl.start - free_before) + surv + min(fr, nb)] = (int)local;
   const uint8_t nf = alive ? kAlive : (uint8_t)0;
   if (in && fl != nf) d.flags[slot] = nf;
-  if (fl & kBirthClaim) d.claim[cell_off + t] = 0xFFFFFFFFu;
 }
 
 // The last launch of a step.  The first blocks: the live list of a slot tile each,
-// then the record of a world each.  The other n_birth_blocks: births (persistent over all
+// the record of a world each, and with terrain the settled water of a cell tile each
+// (small worlds: k_step_small has settled it).  The other n_birth_blocks: births (persistent over all
 // worlds' births), as many blocks as are resident at once.  One block per child where
 // there are enough children to fill the chip, else 2^lgp blocks share a child, each a
 // part of its rows (child_split), so that few births do not take as long as one child
@@ -1718,7 +1698,7 @@ __device__ __forceinline__ void live_tile(const Dev& d, const TileScratch& ts, u
 // weights, a thread a birth.  A birth's parent is found from the tiles' winner counts
 // (prefix sums over 256 runs of tiles in LDS, then the tiles of the run), or
 // read from bparent where the small-world kernel has ranked the winners.
-// base: the first block's number (the two roles can be launched apart).
+// base: the first block's number (the roles can be launched apart).
 template <int WDT, int H>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WDT == 0 ? 6 : 5)))
 void k_birth_commit(CommitArgs by_value) {
@@ -1741,7 +1721,12 @@ void k_birth_commit(CommitArgs by_value) {
       world_record(a.d, a.ts, block - T, a.ranked);
       return;
     }
-    first = block - T - a.d.n_worlds;
+    if (block < a.first_birth) {
+      const Tile ct = cell_tile(a.ts, block - T - a.d.n_worlds);
+      settle_water(a.d, a.d.wp[ct.world], ct);
+      return;
+    }
+    first = block - a.first_birth;
     if (a.ranked && births_of(a.d.wv[0]) == 0) return;
     // the winners before each run of tiles, and the worlds' births
     const bool summed = a.ts.cap0 && !a.ranked;
@@ -1998,10 +1983,10 @@ __global__ __launch_bounds__(kSlotTile) void k_compact_write(Dev d, TileScratch 
 
 // ---------------------------------------------------------------------------
 // The moves, claims, cell pass and ranking of a step for an object of one small
-// world, in one block: the phases of k_move, k_claim_cells and k_birth_rank with the
+// world, in one block: the phases of k_move and k_claim_cells with the
 // world's scans done inside the block, before the same last launch (k_birth_commit:
 // births, live list, record).  A small world's step is bound by the latency of its
-// launches, and this replaces three dependent launches by one.  A thread scans a
+// launches, and this replaces two dependent launches by one.  A thread scans a
 // contiguous range of slots, so every scan is one block-wide exclusive sum.  ECO: the
 // world has the ecology (d.ep set); the single-resource instantiation carries none of
 // the ecology's phases (behind a run-time test they made its step measurably slower).
@@ -2019,7 +2004,6 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
   }
   __shared__ uint32_t cnt[kSlotPart];              // step counters (PC_*)
   __shared__ unsigned long long ccnt[kCellPart];   // regrown units, resource total (the ecology: grid energy), grid water, biomass
-  __shared__ uint32_t any_claim;
   __shared__ unsigned long long rank_red[NW];        // the ranking scan's wave totals
   __shared__ uint32_t live_red[NW];                  // the waves' survivors
   __shared__ unsigned long long red64[NW];           // the waves' energy sums
@@ -2039,7 +2023,6 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
   const int32_t live_tid = d.live[min(tid, d.total_slots - 1u)];
   if (tid < kSlotPart) cnt[tid] = 0;
   if (tid < kCellPart) ccnt[tid] = 0;
-  if (tid == 0) any_claim = 0;
   constexpr uint32_t w = 0;
   const WorldParams wp = d.wp[w];
   const uint32_t step = (uint32_t)d.wv[w].step, n_live = d.wv[w].n_live, cap = wp.cap, cells = wp.cells;
@@ -2059,13 +2042,21 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
     for (uint32_t k = tid; k < n_children; k += NT)
       d.trait[wp.slot_off + (uint32_t)d.freel[wp.slot_off + k]] = child_trait(d, ts, lgp, true, k, 0u);
   }
-  // 1. moves, eating, costs and deaths of the step's live agents
+  // 1. moves, eating, costs and deaths of the step's live agents (what the thread's
+  // first one is afterwards stays in registers for the next phase)
+  Moved held{0, 0, false};
+  int held_act = 0, held_facing = 0;
   for (uint32_t i = l0; i < l1; ++i) {
     const uint32_t local = (uint32_t)(i == tid ? live_tid : live[i]), slot = wp.slot_off + local;
-    const int a = d.act[slot], pos = d.pos[slot], t = d.tgt[slot], E = d.energy[slot];
+    const int a = d.act[slot], pos = d.pos[slot], t = d.tgt[slot], E = d.energy[slot], facing = d.facing[slot];
     float4 cv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (d.colour) cv = d.colour[slot];
     const Moved m = move_agent(d, wp, w, slot, local, step + 1u, a, pos, t, E, cnt);
+    if (i == l0) {
+      held = m;
+      held_act = a;
+      held_facing = facing;
+    }
     if (m.alive) {
       if (sense_bytes) s_agent[m.cell] = (uint8_t)agent_sense(wp, m.energy);   // one agent per cell
       if (d.colour) s_col[local] = colour_word(cv);
@@ -2075,17 +2066,25 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
   // 2. birth claims of the agents still alive with their sums (count, energy, what they
   // carry, and the trait mean and sum of squared deviations by Welford's update), and
   // the cell pass
-  uint32_t nc = 0, nblk = 0, n_t = 0;
+  static_assert(CH * NP <= 32, "a bit per agent of a thread");
+  uint32_t wins = 0, nblk = 0, n_t = 0;   // wins: bit i - l0
   long long es = 0;
   double mean_t = 0.0, m2_t = 0.0;
   unsigned long long eco_w[3] = {0, 0, 0};
   for (uint32_t i = l0; i < l1; ++i) {
     const uint32_t slot = wp.slot_off + (uint32_t)(i == tid ? live_tid : live[i]);
-    const uint8_t fl = d.flags[slot];
-    const int act = d.act[slot], pos = d.pos[slot], facing = d.facing[slot], energy = d.energy[slot];
+    bool alive = held.alive;
+    int act = held_act, pos = held.cell, facing = held_facing, energy = held.energy;
+    if (i != l0) {
+      alive = (d.flags[slot] & kAlive) != 0;
+      act = d.act[slot];
+      pos = d.pos[slot];
+      facing = d.facing[slot];
+      energy = d.energy[slot];
+    }
     const int water = ECO ? d.water[slot] : 0, biomass = ECO ? d.biomass[slot] : 0, hp = ECO ? d.hp[slot] : 0;
     const double trait = d.trait[slot];
-    if (!(fl & kAlive)) continue;
+    if (!alive) continue;
     ++n_t;
     es += energy;
     const double dv = trait - mean_t;
@@ -2100,16 +2099,12 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
       eco_w[1] += (unsigned long long)biomass;
       eco_w[2] += (unsigned long long)hp;
     }
-    const int r = birth_claim_agent(d, wp, w, slot, n_actions, fl, act, pos, facing, energy, water, biomass);
-    nc += r == 1 ? 1u : 0u;
-    nblk += r == 2 ? 1u : 0u;
+    const int r = birth_claim_agent(d, wp, w, slot, n_actions, act, pos, facing, energy, water, biomass);
+    if (r == CLAIM_WON) wins |= 1u << (i - l0);
+    nblk += r == CLAIM_BLOCKED ? 1u : 0u;
   }
-  if (nc) any_claim = 1u;   // the same value from every claimant
-  const uint32_t both = wave_scan(nc | nblk << 16);   // at most 8,192 each
-  if (lane == 63 && both) {
-    atomicAdd(&cnt[PC_CLAIMS], both & 0xFFFFu);
-    atomicAdd(&cnt[PC_BB_CELL], both >> 16);
-  }
+  nblk = wave_scan(nblk);
+  if (lane == 63 && nblk) atomicAdd(&cnt[PC_BB_CELL], nblk);
   const Tile all{w, 0u, cells, 0u};
   if constexpr (ECO) ecology_cells<true>(d, wp, d.ep[w], all, step, ccnt, s_col);
   else plain_cells<true>(d, wp, all, step, ccnt, s_agent, s_col);
@@ -2158,12 +2153,7 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
   // are used), both ranked by one block scan of 16-bit counts packed in a u64
   // (winners, free slots of each pass; no field carries into the next: every total is
   // at most 8,192).
-  uint32_t nw = 0;
-  if (any_claim)   // the same in every thread (written before the barrier above)
-    for (uint32_t i = l0; i < l1; ++i) {
-      const uint32_t slot = wp.slot_off + (uint32_t)live[i];
-      if ((d.flags[slot] & kBirthClaim) && d.claim[wp.cell_off + d.tgt[slot]] == slot) ++nw;
-    }
+  const uint32_t nw = (uint32_t)__builtin_popcount(wins);
   static_assert(NP == 2, "the packed ranking scan holds two passes of free slots");
   unsigned long long rtot;
   const unsigned long long rex =
@@ -2172,9 +2162,9 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
                            rank_red, &rtot);
   const uint32_t Wn = (uint32_t)(rtot & 0xFFFFu);
   uint32_t k = (uint32_t)(rex & 0xFFFFu);
-  for (uint32_t i = l0; i < l1 && nw; ++i) {
-    const uint32_t local = (uint32_t)live[i], slot = wp.slot_off + local;
-    if ((d.flags[slot] & kBirthClaim) && d.claim[wp.cell_off + d.tgt[slot]] == slot) d.bparent[wp.slot_off + k++] = (int)local;
+  for (uint32_t m = wins; m; m &= m - 1) {
+    const uint32_t i = l0 + (uint32_t)__builtin_ctz(m);
+    d.bparent[wp.slot_off + k++] = i == tid ? live_tid : live[i];
   }
   uint32_t F = 0;
 #pragma unroll
@@ -2669,11 +2659,6 @@ hipError_t launch_claim_cells(hipStream_t s, const Dev& d, const TileScratch& ts
   hipLaunchKernelGGL(k_claim_cells, dim3(nb), dim3(256), 0, s, d, ts, A);
   ECO_CHECK_LAUNCH();
 }
-hipError_t launch_birth_rank(hipStream_t s, const Dev& d, const TileScratch& ts) {
-  const uint32_t nb = ts.n_slot_tiles + d.n_worlds + (d.rock ? ts.n_cell_tiles : 0u);
-  hipLaunchKernelGGL(k_birth_rank, dim3(nb), dim3(kSlotTile), 0, s, d, ts);
-  ECO_CHECK_LAUNCH();
-}
 // Resident blocks per CU of the birth-commit kernel for this layout (its register
 // and LDS use), so that the persistent grid is exactly one wave of resident blocks.
 template <int WDT>
@@ -2693,14 +2678,15 @@ hipError_t launch_step_small(hipStream_t s, const Dev& d, const TileScratch& ts,
   else hipLaunchKernelGGL(k_step_small<false>, dim3(2), dim3(1024), 0, s, d, ts, A, H);
   ECO_CHECK_LAUNCH();
 }
-// roles: 1 births, 2 live list and records, 3 both in one launch.
+// roles: 1 births, 2 live list, 4 records and water; 7 all in one launch, or one of them.
 template <int WDT, int H>
 void launch_birth_commit_wh(hipStream_t s, const Dev& d, const Layout& L, const TileScratch& ts, uint32_t births,
                             uint32_t ranked, int roles) {
-  const uint32_t rest = ts.n_slot_tiles + d.n_worlds;
-  const uint32_t base = (roles & 2) ? 0u : rest, end = rest + ((roles & 1) ? births : 0u);
+  const uint32_t rest = ts.n_slot_tiles + d.n_worlds + (d.rock && !ranked ? ts.n_cell_tiles : 0u);
+  const uint32_t base = (roles & 2) ? 0u : ((roles & 4) ? ts.n_slot_tiles : rest);
+  const uint32_t end = (roles & 1) ? rest + births : ((roles & 4) ? rest : ts.n_slot_tiles);
   hipLaunchKernelGGL((k_birth_commit<WDT, H>), dim3(end - base), dim3(256), 0, s,
-                     (CommitArgs{d, L, ts, base, births, ranked}));
+                     (CommitArgs{d, L, ts, base, rest, births, ranked}));
 }
 template <int WDT>
 void launch_birth_commit_w(hipStream_t s, const Dev& d, const Layout& L, const TileScratch& ts, uint32_t births,

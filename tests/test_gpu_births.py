@@ -76,3 +76,32 @@ def test_records_inside_a_call(eco, worlds, side):
                     assert v == y[k], (w, k, v, y[k])
     a.close()
     b.close()
+
+
+# every agent claims at every step, so most empty cells have two to four claimants;
+# grids one or two cells wide have the same cell on several sides
+@pytest.mark.parametrize("w,h,n", [(1, 1, 1), (1, 9, 4), (9, 1, 4), (2, 2, 2), (2, 40, 30), (3, 3, 5), (64, 64, 1600),
+                                   (150, 101, 6000)])
+@pytest.mark.parametrize("ecology", [False, True])
+@pytest.mark.parametrize("split", [False, True])
+def test_contended_claims_match_oracle(eco, w, h, n, ecology, split):
+    kw = dict(width=w, height=h, n_agents_init=n, capacity=w * h + 3, mutation_sigma=0.05,
+              window=3 if min(w, h) > 2 else 1, n_scalars=8, hidden1=32, hidden2=32, wdtype=wl.BF16, e_cost=0, e_init=9000, e_repro=50, seed=w * h)
+    if ecology:
+        cfg = wl.ecology_desc(eco=dict(b_repro=1, w_child=1, w_init=5000, b_init=90), **kw)
+    else:
+        cfg = wl.desc(n_actions=7, resource_density=0.3, **kw)
+    ow, gw = orc.OracleWorld(cfg), eco.World(cfg)
+    if split:
+        gw.set_flags(eco.RT_USE_GRAPH | eco.RT_SPLIT_STEP)
+    rng = np.random.default_rng([w, h])
+    for t in range(4):
+        acts = np.where(rng.random(cfg["capacity"]) < 0.8, 7 if ecology else 5, rng.integers(0, 3, cfg["capacity"]))
+        ow.step(actions=acts.astype(np.uint8))
+        gw.step_with_actions(acts.astype(np.uint8))
+        compare_world(gw, ow, f"{w} x {h} step {t}", weights_slots=3)
+        st = gw.stats()[0]
+        assert_stats_match(st, ow.stats(), f"{w} x {h} step {t}")
+        if n > 1000 and t == 0:
+            assert st["births"] > 400 and st["births_blocked_cell"] > 400
+    gw.close()
