@@ -242,12 +242,12 @@ typedef struct {
                                    ECO_RT_USE_GRAPH, event-record nodes around the policy kernel
                                    only, in a graph of the n steps of each eco_world_step call (one
                                    graph kept per n).  The call synchronises to read the times. */
-#define ECO_RT_SPLIT_STEP 8u    /* an object of one small world (at most 8,192 slots, and 12,288
-                                   cells or 8,192 in the ecology) runs the step after the policy
-                                   kernel as one single-block launch before the birth launch
-                                   (timed together as ECO_K_MOVE); this flag runs the separate
-                                   kernels instead.  Same integer state and statistics either way
-                                   (the trait moments to rounding). */
+#define ECO_RT_SPLIT_STEP 8u    /* an object of one small world (at most 8,192 slots and 4,096
+                                   cells) runs the step after the policy kernel as one
+                                   single-block launch before the birth launch (timed together as
+                                   ECO_K_MOVE); this flag runs the separate kernels instead.  Same
+                                   integer state and statistics either way (the trait moments to
+                                   rounding). */
 /* The single-block launch's limits: the most slots and cells it could hold (each
  * world's ranges rounded up to 64). */
 #define ECO_SMALL_STEP_MAX_SLOTS 8192u

@@ -23,6 +23,13 @@ namespace eco {
 
 constexpr int kStatsRing = 1024;
 constexpr int ECO_MAX_WORLDS = 1024;   // worlds of one object at most
+// Cells per cell tile (one block of the cell pass): four per thread, and the few cells of
+// a small object one per thread, since a wave's instructions for four (a lone wave issues
+// one in 2.4 ns) are then longer than the launch.  us per step with four / one cell per
+// thread: 128^2 with terrain and colours 30.5 / 27.7, 256^2 50.3 / 47.8; twelve worlds of
+// 128^2 even; 512^2 ecology 116.3 / 117.5, and 1.1 million cells 385.8 / 387.8.
+constexpr uint32_t ECO_CELL_TILE = 1024, ECO_SMALL_CELL_TILE = 256, ECO_SMALL_CELLS = 131072;
+constexpr uint32_t ECO_SMALL_CELL_TILES = ECO_SMALL_CELLS / ECO_SMALL_CELL_TILE + ECO_MAX_WORLDS;   // of such an object at most
 constexpr uint32_t ECO_MAX_PARTS = 8192;   // blocks sharing children in one birth launch at most
 constexpr uint8_t kAlive = 1;
 enum Action : uint8_t { REST = 0, TURN_L = 1, TURN_R = 2, FORWARD = 3, EAT = 4, REPRODUCE = 5, ATTACK = 6 };
@@ -185,6 +192,7 @@ struct TileScratch {
   const uint32_t* tile_rng;
   uint32_t n_slot_tiles, n_cell_tiles;
   uint32_t split_below;   // fewer births than this in a step: several blocks share a child (ECO_MAX_PARTS / 2 at most)
+  uint32_t cell_tile;   // cells per cell tile
   uint32_t cap0, cells0;  // an object of one world: its capacity and cells (its tiles need no table); else 0
   uint32_t* part_slot;   // [slot tiles][16] step counters (PC_*)
   unsigned long long* part_cell;   // [cell tiles][4] regrown, resource total (ecology: energy), water, biomass

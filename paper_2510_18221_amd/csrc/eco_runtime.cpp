@@ -55,7 +55,6 @@ using namespace eco;
 namespace {
 
 constexpr uint32_t kSlotTileH = 256;
-constexpr uint32_t kCellTileH = 1024;
 
 thread_local std::string g_err;
 
@@ -522,17 +521,18 @@ hipError_t launch_group(eco_world* w, hipStream_t s, const Dev& d, const TileScr
 
 // An object of one small world steps with the policy kernel, one single-block launch
 // (k_step_small) and the birth launch, unless ECO_RT_SPLIT_STEP asks for the separate
-// kernels: its step is bound by the latency of its launches, and one block spares two of
-// them; a larger world's cells keep one block longer than the two launches take.  The
-// line lies where the passes of the block over the cells (4,096 each) make it even.
-// Measured, one block / separate kernels, us per step: single resource 64^2 17.5 / 22.2,
-// 96^2 19.7 / 22.7, 128^2 25.2 / 23.3; the ecology 64^2 22.3 / 25.5, 80^2 24.2 / 25.4,
-// 96^2 26.9 / 25.9, 128^2 37.6 / 28.8 (with terrain and colours 96^2 32.2 / 30.6).
-constexpr uint32_t kSmallSlots = ECO_SMALL_STEP_MAX_SLOTS, kSmallCells = 3 * 4096, kSmallEcologyCells = 2 * 4096;
+// kernels: its step is bound by the latency of its launches, and one block spares one of
+// them; the line lies where the block's threads take one group of four cells each, since
+// a second pass keeps it longer than the launch it spares.
+// Measured, one block / separate kernels, us per step: single resource without births 64^2
+// 16.7 / 19.1, 80^2 17.7 / 18.8, with three births a step 64^2 21.2 / 20.8, 80^2 22.8 / 21.1,
+// 96^2 23.8 / 21.3; the ecology 48^2 21.4 / 22.4, 64^2 21.9 / 22.8, 80^2 23.8 / 23.0 (with
+// terrain and colours 48^2 24.2 / 25.3, 64^2 25.4 / 25.1, 80^2 28.5 / 25.5).
+constexpr uint32_t kSmallSlots = ECO_SMALL_STEP_MAX_SLOTS, kSmallCells = 4096;
 static_assert(kSmallCells <= ECO_SMALL_STEP_MAX_CELLS, "inside what the kernel holds");
 bool small_step(const eco_world* w) {
-  return w->n_worlds == 1 && w->total_slots <= kSmallSlots &&
-         w->total_cells <= (w->L.ecology ? kSmallEcologyCells : kSmallCells) && !(w->rt_flags & ECO_RT_SPLIT_STEP);
+  return w->n_worlds == 1 && w->total_slots <= kSmallSlots && w->total_cells <= kSmallCells &&
+         !(w->rt_flags & ECO_RT_SPLIT_STEP);
 }
 
 // Enqueue one step's kernels.  timed: bracket each kernel group with events.
@@ -833,6 +833,9 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   }
   // world tables: slot and cell ranges aligned to 64
   uint64_t so = 0, co = 0;
+  for (uint32_t i = 0; i < n_worlds; ++i) co += round_up((uint64_t)descs[i].width * descs[i].height, 64);
+  const uint32_t cell_tile = co <= ECO_SMALL_CELLS ? ECO_SMALL_CELL_TILE : ECO_CELL_TILE;
+  co = 0;
   w->wp.resize(n_worlds);
   bool any_attack = false;
   for (uint32_t i = 0; i < n_worlds; ++i) {
@@ -864,8 +867,8 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
     }
     w->tile_rng_h.push_back(w->n_slot_tiles);
     w->tile_rng_h.push_back(w->n_cell_tiles);
-    for (uint32_t c = 0; c < p.cells; c += kCellTileH) {
-      w->cell_tiles_h.push_back(Tile{i, c, std::min(kCellTileH, p.cells - c), 0});
+    for (uint32_t c = 0; c < p.cells; c += cell_tile) {
+      w->cell_tiles_h.push_back(Tile{i, c, std::min(cell_tile, p.cells - c), 0});
       ++w->n_cell_tiles;
     }
     w->tile_rng_h.push_back(w->n_cell_tiles);
@@ -950,6 +953,7 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
     ts.tile_rng = w->tile_rng;
     ts.n_slot_tiles = w->n_slot_tiles;
     ts.n_cell_tiles = w->n_cell_tiles;
+    ts.cell_tile = cell_tile;
     ts.cap0 = n_worlds == 1 ? w->wp[0].cap : 0u;
     ts.cells0 = n_worlds == 1 ? w->wp[0].cells : 0u;
     ts.part_slot = w->part_slot;
@@ -1108,7 +1112,9 @@ eco_status eco_world_step_static(eco_world* w, uint32_t n_steps) {
   if (st != ECO_OK) return st;
   if (n_steps == 0) return ECO_OK;
   // the step's scratch, laid out in the static array (each part 256-aligned)
-  const uint64_t T = std::max(1u, w->n_slot_tiles), C = std::max(1u, w->n_cell_tiles);
+  const uint64_t T = std::max(1u, w->n_slot_tiles);
+  uint64_t C = 0;   // tiles of 1,024 cells (the smaller ones of a small object have their own place)
+  for (const auto& p : w->wp) C += (p.cells + ECO_CELL_TILE - 1) / ECO_CELL_TILE;
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
     const uint64_t o = off;
@@ -1123,8 +1129,10 @@ eco_status eco_world_step_static(eco_world* w, uint32_t n_steps) {
   void* base = nullptr;
   size_t cap = 0;
   HIPCHK(w, static_scratch(&base, &cap), "static scratch address");
-  // the limit: 16 MiB for all of this but the drafts and the parts (which lie behind it)
-  cap -= sizeof(StepDraft) * ECO_MAX_WORLDS + sizeof(double) * ECO_MAX_PARTS;
+  // the limit: 16 MiB for all of this but the drafts, the parts and a small object's
+  // cell tiles (which lie behind it)
+  const uint64_t draft_bytes = sizeof(StepDraft) * ECO_MAX_WORLDS, parts_bytes = sizeof(double) * ECO_MAX_PARTS;
+  cap -= draft_bytes + parts_bytes + 8ull * kCellPart * ECO_SMALL_CELL_TILES;
   if (off > cap) {
     char buf[200];
     snprintf(buf, sizeof buf, "eco_world_step_static: the object needs %llu bytes of scratch, above the static "
@@ -1140,9 +1148,10 @@ eco_status eco_world_step_static(eco_world* w, uint32_t n_steps) {
   d.freel = reinterpret_cast<int32_t*>(b + o_freel);
   d.draft = reinterpret_cast<StepDraft*>(b + cap);
   TileScratch ts = w->ts;
-  ts.parts = reinterpret_cast<double*>(b + cap + sizeof(StepDraft) * ECO_MAX_WORLDS);
+  ts.parts = reinterpret_cast<double*>(b + cap + draft_bytes);
   ts.part_slot = reinterpret_cast<uint32_t*>(b + o_part_slot);
-  ts.part_cell = reinterpret_cast<unsigned long long*>(b + o_part_cell);
+  ts.part_cell = reinterpret_cast<unsigned long long*>(
+      b + (ts.cell_tile == ECO_CELL_TILE ? o_part_cell : cap + draft_bytes + parts_bytes));
   ts.scan = reinterpret_cast<uint32_t*>(b + o_scan);
   ts.esum = reinterpret_cast<long long*>(b + o_esum);
   ts.tmean = reinterpret_cast<double*>(b + o_tmean);

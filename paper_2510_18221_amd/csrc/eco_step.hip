@@ -31,7 +31,6 @@
 namespace eco {
 
 constexpr int kSlotTile = 256;   // slots per block in per-slot kernels
-constexpr int kCellTile = 1024;  // cells per block in per-cell kernels
 constexpr int kScanThreads = 1024;
 
 // ---------------------------------------------------------------------------
@@ -197,7 +196,7 @@ __device__ __forceinline__ Tile slot_tile(const TileScratch& ts, uint32_t i) {
   return ts.slot_tiles[i];
 }
 __device__ __forceinline__ Tile cell_tile(const TileScratch& ts, uint32_t i) {
-  if (ts.cap0) return Tile{0u, i * kCellTile, min((uint32_t)kCellTile, ts.cells0 - i * kCellTile), 0u};
+  if (ts.cap0) return Tile{0u, i * ts.cell_tile, min(ts.cell_tile, ts.cells0 - i * ts.cell_tile), 0u};
   return ts.cell_tiles[i];
 }
 // World w's slot and cell offsets (zero without a load where it is the only one).
@@ -720,47 +719,70 @@ __device__ __forceinline__ uint32_t word_of(const uint4& x, int j) {
   return j == 0 ? x.x : (j == 1 ? x.y : (j == 2 ? x.z : x.w));
 }
 
-// One regrowth pass over the resource bytes of local cells c0 .. c0 + n - 1 (c0 a
-// multiple of 4, n <= 4) held in the word v: each empty cell regrows one unit
+// One regrowth pass over the resource bytes of local cells c0 .. c0 + n - 1 (n <= V,
+// which divides 4, and c0 a multiple of V) held in the word v: each empty cell regrows one unit
 // with probability p (its draw against floor(p 2^32)).  Returns the new word;
 // adds the regrown cells and the resource total to grown and total.
+template <int V>
 __device__ __forceinline__ uint32_t regrow_word(const WorldParams& wp, uint32_t c0, uint32_t n, uint32_t v,
                                                 uint32_t step, unsigned long long& grown, unsigned long long& total) {
   bool any = false;
 #pragma unroll
-  for (uint32_t j = 0; j < 4; ++j) any |= j < n && ((v >> (8 * j)) & 0xFFu) == 0;
+  for (uint32_t j = 0; j < V; ++j) any |= j < n && ((v >> (8 * j)) & 0xFFu) == 0;
   uint32_t nv = v;
   if (any) {
     const uint4 x = regrow_draws(wp, c0 >> 2, step);
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j)
-      if (j < n && ((v >> (8 * j)) & 0xFFu) == 0 && (uint64_t)word_of(x, (int)j) < wp.regrow_thr) {
+    for (uint32_t j = 0; j < V; ++j)
+      if (j < n && ((v >> (8 * j)) & 0xFFu) == 0 && (uint64_t)word_of(x, V == 4 ? (int)j : (int)(c0 & 3u)) < wp.regrow_thr) {
         nv |= 1u << (8 * j);
         ++grown;
       }
   }
 #pragma unroll
-  for (uint32_t j = 0; j < 4; ++j)
+  for (uint32_t j = 0; j < V; ++j)
     if (j < n) total += (nv >> (8 * j)) & 0xFFu;
   return nv;
 }
 
-// Four consecutive int32 cells from g (g a multiple of 4; the cell allocation ends
-// at a multiple of 64, so the vector stays inside it even for a ragged tail) and
-// their store, whole for n = 4, else cell by cell.
-__device__ __forceinline__ void load_cells4(const int32_t* p, int v[4]) {
-  const int4 x = *reinterpret_cast<const int4*>(p);
-  v[0] = x.x;
-  v[1] = x.y;
-  v[2] = x.z;
-  v[3] = x.w;
+// V consecutive int32 cells from local cell c (four: c a multiple of 4; the cell
+// allocation ends at a multiple of 64, so a ragged last group reads inside it), the
+// first n of them stored, and V byte cells as the bytes of a word.
+template <int V>
+__device__ __forceinline__ void load_cells(const int32_t* p, int (&v)[V]) {
+  if constexpr (V == 4) {
+    const int4 x = *reinterpret_cast<const int4*>(p);
+    v[0] = x.x;
+    v[1] = x.y;
+    v[2] = x.z;
+    v[3] = x.w;
+  } else {
+    v[0] = p[0];
+  }
 }
 
-__device__ __forceinline__ void store_cells4(int32_t* p, uint32_t n, const int v[4]) {
-  if (n == 4) {
-    *reinterpret_cast<int4*>(p) = make_int4(v[0], v[1], v[2], v[3]);
+template <int V>
+__device__ __forceinline__ void store_cells(int32_t* p, uint32_t n, const int (&v)[V]) {
+  if (V == 4 && n == 4) {
+    if constexpr (V == 4) *reinterpret_cast<int4*>(p) = make_int4(v[0], v[1], v[2], v[3]);
   } else {
     for (uint32_t j = 0; j < n; ++j) p[j] = v[j];
+  }
+}
+
+template <int V, typename T>
+__device__ __forceinline__ uint32_t load_bytes(const T* p) {
+  static_assert(sizeof(T) == 1, "byte cells");
+  if constexpr (V == 4) return *reinterpret_cast<const uint32_t*>(p);
+  else return (uint32_t)(uint8_t)p[0];
+}
+
+template <int V>
+__device__ __forceinline__ void store_bytes(uint8_t* p, uint32_t n, uint32_t v) {
+  if (V == 4 && n == 4) {
+    *reinterpret_cast<uint32_t*>(p) = v;
+  } else {
+    for (uint32_t j = 0; j < n; ++j) p[j] = (uint8_t)(v >> (8 * j));
   }
 }
 
@@ -769,27 +791,29 @@ __device__ __forceinline__ int byte_of(uint32_t v, int j) { return (int)(int8_t)
 // Terrain: the water on local cells c0 .. c0 + n - 1 after the flow (each cell's
 // water moves one cell downhill, every cell at once): a cell keeps its own water if
 // it has no way down, and takes that of each neighbour whose way down leads to it.
-// own[] holds the cells' water before the flow, fd their four direction bytes.
-// With W a multiple of 4 a whole group lies in one row, and the neighbours above
-// and below are whole aligned groups: flow_rows_load reads them (and the cells
-// left and right of the group) so that the caller can issue these loads with its
-// own, and returns false where the group takes the per-cell path instead.
+// own[] holds the cells' water before the flow, fd their direction bytes.  A group of
+// one cell, or of four with W a multiple of 4, lies in one row, and the neighbours above
+// and below are whole groups: flow_rows_load reads them (and the cells left and right
+// of the group) so that the caller can issue these loads with its own, and returns
+// false where the group takes the per-cell path instead.
+template <int V>
 struct FlowRows {
-  int wu[4], wd[4];   // water of the cells above and below
+  int wu[V], wd[V];   // water of the cells above and below
   uint32_t fu, fdn;   // their direction bytes
   int wl, wr, fl, fr;   // water and direction of the cells left and right of the group
 };
 
+template <int V>
 __device__ __forceinline__ bool flow_rows_load(const Dev& d, const WorldParams& wp, uint32_t c0, uint32_t n,
-                                               FlowRows& r) {
-  if ((wp.W & 3u) != 0 || n != 4) return false;
+                                               FlowRows<V>& r) {
+  if (V > 1 && ((wp.W & 3u) != 0 || n != V)) return false;
   const uint32_t off = wp.cell_off, W = wp.W, y0 = c0 / W, x0 = c0 - y0 * W, row = y0 * W;
   const uint32_t up = (y0 == 0 ? wp.H - 1 : y0 - 1) * W + x0, dn = (y0 + 1 == wp.H ? 0u : y0 + 1) * W + x0;
-  const uint32_t lf = row + (x0 == 0 ? W - 1 : x0 - 1), rt = row + (x0 + 4 == W ? 0u : x0 + 4);
-  load_cells4(d.cw + off + up, r.wu);
-  load_cells4(d.cw + off + dn, r.wd);
-  r.fu = *reinterpret_cast<const uint32_t*>(d.flowdir + off + up);
-  r.fdn = *reinterpret_cast<const uint32_t*>(d.flowdir + off + dn);
+  const uint32_t lf = row + (x0 == 0 ? W - 1 : x0 - 1), rt = row + (x0 + V == W ? 0u : x0 + V);
+  load_cells(d.cw + off + up, r.wu);
+  load_cells(d.cw + off + dn, r.wd);
+  r.fu = load_bytes<V>(d.flowdir + off + up);
+  r.fdn = load_bytes<V>(d.flowdir + off + dn);
   r.wl = d.cw[off + lf];
   r.wr = d.cw[off + rt];
   r.fl = d.flowdir[off + lf];
@@ -797,20 +821,21 @@ __device__ __forceinline__ bool flow_rows_load(const Dev& d, const WorldParams& 
   return true;
 }
 
-__device__ __forceinline__ void flow_gather4(const Dev& d, const WorldParams& wp, uint32_t c0, uint32_t n,
-                                             const int own[4], uint32_t fd, bool rows, const FlowRows& r,
-                                             int out[4]) {
+template <int V>
+__device__ __forceinline__ void flow_gather(const Dev& d, const WorldParams& wp, uint32_t c0, uint32_t n,
+                                            const int (&own)[V], uint32_t fd, bool rows, const FlowRows<V>& r,
+                                            int (&out)[V]) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) out[j] = byte_of(fd, j) < 0 ? own[j] : 0;
-  if (rows) {
+  for (int j = 0; j < V; ++j) out[j] = byte_of(fd, j) < 0 ? own[j] : 0;
+  if (V == 1 || rows) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < V; ++j) {
       // the neighbour above (facing 0) leads here if it flows down (2), the one to
       // the right (1) if it flows left (3), below (2) if up (0), left (3) if right (1)
       if (byte_of(r.fu, j) == 2) out[j] += r.wu[j];
-      if ((j < 3 ? byte_of(fd, j + 1) : r.fr) == 3) out[j] += j < 3 ? own[j + 1] : r.wr;
+      if ((j < V - 1 ? byte_of(fd, j + 1) : r.fr) == 3) out[j] += j < V - 1 ? own[j + 1 < V ? j + 1 : j] : r.wr;
       if (byte_of(r.fdn, j) == 0) out[j] += r.wd[j];
-      if ((j > 0 ? byte_of(fd, j - 1) : r.fl) == 1) out[j] += j > 0 ? own[j - 1] : r.wl;
+      if ((j > 0 ? byte_of(fd, j - 1) : r.fl) == 1) out[j] += j > 0 ? own[j > 0 ? j - 1 : 0] : r.wl;
     }
   } else {
     for (uint32_t j = 0; j < n; ++j) {
@@ -868,70 +893,63 @@ __device__ __forceinline__ uint32_t colour_word(const float4 c) {
 
 __device__ __forceinline__ uint32_t sat255(int v) { return (uint32_t)min(max(v, 0), 255); }
 
-// The cells of tile tl of a single-resource world, four consecutive cells per
-// thread and pass (tiles start at multiples of 4 cells; the cell allocation ends at
-// a multiple of 64, so the vector loads of a ragged last group stay inside it).
+// The cells of tile tl of a single-resource world, V consecutive cells per
+// thread and pass (tiles start at multiples of 4 cells).
 // GROW (a step): each empty cell regrows one unit with probability p, and the
 // regrown cells and the resource total go to cnt[0], cnt[1] (LDS).  Then the
 // cell's window channels, from the resources just grown and the occupants after the
 // moves (a birth adds its own, place_child), so the grid is read once a step.  agent,
 // col: the occupants' sense bits by cell and colour words by slot, where the caller
 // has them in LDS; else they are read through the occupancy.
-template <bool GROW>
+template <bool GROW, int V>
 __device__ __forceinline__ void plain_cells(const Dev& d, const WorldParams& wp, const Tile tl, uint32_t step,
                                             unsigned long long* cnt, const uint8_t* agent, const uint32_t* col) {
   unsigned long long grown = 0, total = 0;
 #pragma unroll 1
-  for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
-    const uint32_t c0 = tl.start + i, n = min(4u, tl.count - i), g = wp.cell_off + c0;
-    const uint32_t v = *reinterpret_cast<const uint32_t*>(d.res + g);
-    const uint32_t wl = wp.has_walls ? *reinterpret_cast<const uint32_t*>(d.wall + g) : 0u;
-    int o[4] = {-1, -1, -1, -1};
-    uint32_t q[4] = {0u, 0u, 0u, 0u};   // the occupants' sense bits or colour words
-    if (d.rgb || !agent) {
-      load_cells4(d.occ + g, o);
+  for (uint32_t i = V * threadIdx.x; i < tl.count; i += V * blockDim.x) {
+    const uint32_t c0 = tl.start + i, n = min((uint32_t)V, tl.count - i), g = wp.cell_off + c0;
+    const uint32_t v = load_bytes<V>(d.res + g);
+    const uint32_t wl = wp.has_walls ? load_bytes<V>(d.wall + g) : 0u;
+    int o[V], q[V];   // the occupants, their sense bits or colour words
 #pragma unroll
-      for (uint32_t j = 0; j < 4; ++j) {
+    for (int j = 0; j < V; ++j) {
+      o[j] = -1;
+      q[j] = 0;
+    }
+    if (d.rgb || !agent) {
+      load_cells(d.occ + g, o);
+#pragma unroll
+      for (uint32_t j = 0; j < V; ++j) {
         if (j >= n) o[j] = -1;   // past a ragged tail: no occupant read
         if (o[j] < 0) continue;
         const uint32_t slot = wp.slot_off + (uint32_t)o[j];
-        if (d.rgb) q[j] = col ? col[o[j]] : colour_word(d.colour[slot]);
-        else q[j] = agent_sense(wp, d.energy[slot]);
+        if (d.rgb) q[j] = (int)(col ? col[o[j]] : colour_word(d.colour[slot]));
+        else q[j] = (int)agent_sense(wp, d.energy[slot]);
       }
     } else {
-      const uint32_t ag = *reinterpret_cast<const uint32_t*>(agent + c0);
+      const uint32_t ag = load_bytes<V>(agent + c0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) q[j] = (ag >> (8 * j)) & 0xFFu;
+      for (int j = 0; j < V; ++j) q[j] = (int)((ag >> (8 * j)) & 0xFFu);
     }
     uint32_t nv = v;
     if constexpr (GROW) {
-      nv = regrow_word(wp, c0, n, v, step, grown, total);
-      if (nv != v) {
-        if (n == 4) {
-          *reinterpret_cast<uint32_t*>(d.res + g) = nv;
-        } else {
-          for (uint32_t j = 0; j < n; ++j) d.res[g + j] = (uint8_t)(nv >> (8 * j));
-        }
-      }
+      nv = regrow_word<V>(wp, c0, n, v, step, grown, total);
+      if (nv != v) store_bytes<V>(d.res + g, n, nv);
     }
     if (d.rgb) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < V; ++j) {
         const uint32_t bits = cell_sense(wp, (nv >> (8 * j)) & 0xFFu, (wl >> (8 * j)) & 0xFFu);
-        if (o[j] < 0) q[j] = (bits & 2u) ? 255u << 8 : ((bits & 4u) ? 0x808080u : 0u);
-        q[j] |= ((o[j] >= 0 ? 1u : 0u) | bits) << 24;
+        if (o[j] < 0) q[j] = (bits & 2u) ? 255 << 8 : ((bits & 4u) ? 0x808080 : 0);
+        q[j] |= (int)(((o[j] >= 0 ? 1u : 0u) | bits) << 24);
       }
-      store_cells4(reinterpret_cast<int32_t*>(d.rgb + g), n, reinterpret_cast<const int*>(q));
+      store_cells(reinterpret_cast<int32_t*>(d.rgb + g), n, q);
     } else {
       uint32_t sv = 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        sv |= (q[j] | cell_sense(wp, (nv >> (8 * j)) & 0xFFu, (wl >> (8 * j)) & 0xFFu)) << (8 * j);
-      if (n == 4) {
-        *reinterpret_cast<uint32_t*>(d.sense + g) = sv;
-      } else {
-        for (uint32_t j = 0; j < n; ++j) d.sense[g + j] = (uint8_t)(sv >> (8 * j));
-      }
+      for (int j = 0; j < V; ++j)
+        sv |= ((uint32_t)q[j] | cell_sense(wp, (nv >> (8 * j)) & 0xFFu, (wl >> (8 * j)) & 0xFFu)) << (8 * j);
+      store_bytes<V>(d.sense + g, n, sv);
     }
   }
   if constexpr (GROW) {
@@ -940,10 +958,10 @@ __device__ __forceinline__ void plain_cells(const Dev& d, const WorldParams& wp,
   }
 }
 
-// The cells of tile tl of an ecology, four consecutive cells per thread and pass.
+// The cells of tile tl of an ecology, V consecutive cells per thread and pass.
 // STEP: photosynthesis, one energy unit with probability min(1, rate * biomass) on
 // cells holding biomass below the energy ceiling (the threshold in exact integers;
-// the four cells' draws are the four outputs of one Philox block); the strikes of
+// the draws of four cells are the four outputs of one Philox block); the strikes of
 // this step cleared (they have been counted); with terrain, the water's flow
 // gathered into cw_next (copied back by the next pass, once every cell has read the
 // old layer); the photosynthesised units and the grid totals of energy, water and
@@ -952,84 +970,80 @@ __device__ __forceinline__ void plain_cells(const Dev& d, const WorldParams& wp,
 // cell as others see it (occupant's colour, wall grey, else energy / biomass / water
 // as red / green / blue); the agent / wall bits and the rock height in the top byte.
 // col: the live agents' colour words by slot, where the caller has them in LDS.
-template <bool STEP>
+template <bool STEP, int V>
 __device__ __forceinline__ void ecology_cells(const Dev& d, const WorldParams& wp, const eco_ecology& e, const Tile tl,
                                               uint32_t step, unsigned long long* cnt, const uint32_t* col) {
   unsigned long long grown = 0, total = 0, wsum = 0, bsum = 0;
 #pragma unroll 1
-  for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
-    const uint32_t c0 = tl.start + i, n = min(4u, tl.count - i), g = wp.cell_off + c0;
-    int b[4], en[4], wv[4], o[4], rk[4] = {0, 0, 0, 0};
-    load_cells4(d.occ + g, o);
-    load_cells4(d.cb + g, b);
-    load_cells4(d.ce + g, en);
-    load_cells4(d.cw + g, wv);
-    if (d.rock) load_cells4(d.rock + g, rk);
-    const uint32_t wl4 = wp.has_walls ? *reinterpret_cast<const uint32_t*>(d.wall + g) : 0u;
-    const uint32_t fd = (STEP && d.rock) ? *reinterpret_cast<const uint32_t*>(d.flowdir + g) : 0u;
-    FlowRows fr{};   // the flow's neighbour rows, loaded with the cells' own values
+  for (uint32_t i = V * threadIdx.x; i < tl.count; i += V * blockDim.x) {
+    const uint32_t c0 = tl.start + i, n = min((uint32_t)V, tl.count - i), g = wp.cell_off + c0;
+    int b[V], en[V], wv[V], o[V], rk[V] = {}, q[V] = {};
+    load_cells(d.occ + g, o);
+    load_cells(d.cb + g, b);
+    load_cells(d.ce + g, en);
+    load_cells(d.cw + g, wv);
+    if (d.rock) load_cells(d.rock + g, rk);
+    const uint32_t wl4 = wp.has_walls ? load_bytes<V>(d.wall + g) : 0u;
+    const uint32_t fd = (STEP && d.rock) ? load_bytes<V>(d.flowdir + g) : 0u;
+    FlowRows<V> fr{};   // the flow's neighbour rows, loaded with the cells' own values
     const bool rows = STEP && d.rock && flow_rows_load(d, wp, c0, n, fr);
 #pragma unroll
-    for (uint32_t j = 0; j < 4; ++j)
+    for (uint32_t j = 0; j < V; ++j)
       if (j >= n) o[j] = -1;   // past a ragged tail: no occupant read
-    uint32_t q[4] = {0u, 0u, 0u, 0u};
     if (d.colour) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (o[j] >= 0) q[j] = col ? col[o[j]] : colour_word(d.colour[wp.slot_off + (uint32_t)o[j]]);
+      for (int j = 0; j < V; ++j)
+        if (o[j] >= 0) q[j] = (int)(col ? col[o[j]] : colour_word(d.colour[wp.slot_off + (uint32_t)o[j]]));
     }
     if constexpr (STEP) {
       bool any = false;
 #pragma unroll
-      for (uint32_t j = 0; j < 4; ++j) any |= j < n && b[j] > 0 && en[j] < e.cell_energy_max;
+      for (uint32_t j = 0; j < V; ++j) any |= j < n && b[j] > 0 && en[j] < e.cell_energy_max;
       if (any) {
         const uint4 x = regrow_draws(wp, c0 >> 2, step);
         bool grew = false;
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j)
+        for (uint32_t j = 0; j < V; ++j)
           if (j < n && b[j] > 0 && en[j] < e.cell_energy_max &&
-              (uint64_t)word_of(x, (int)j) < photo_threshold(e.photo_rate, b[j])) {
+              (uint64_t)word_of(x, V == 4 ? (int)j : (int)(c0 & 3u)) < photo_threshold(e.photo_rate, b[j])) {
             ++en[j];
             ++grown;
             grew = true;
           }
-        if (grew) store_cells4(d.ce + g, n, en);
+        if (grew) store_cells(d.ce + g, n, en);
       }
 #pragma unroll
-      for (uint32_t j = 0; j < 4; ++j)
+      for (uint32_t j = 0; j < V; ++j)
         if (j < n) {
           total += (unsigned long long)(uint32_t)en[j];
           wsum += (unsigned long long)(uint32_t)wv[j];
           bsum += (unsigned long long)(uint32_t)b[j];
         }
       if (wp.attack) {
-        if (n == 4) {
-          *reinterpret_cast<uint4*>(d.mark + g) = make_uint4(0u, 0u, 0u, 0u);
-        } else {
-          for (uint32_t j = 0; j < n; ++j) d.mark[g + j] = 0u;
-        }
+        const int none[V] = {};
+        store_cells(reinterpret_cast<int32_t*>(d.mark + g), n, none);
       }
       if (d.rock) {
-        int nw[4];
-        flow_gather4(d, wp, c0, n, wv, fd, rows, fr, nw);
-        store_cells4(d.cw_next + g, n, nw);
+        int nw[V];
+        flow_gather(d, wp, c0, n, wv, fd, rows, fr, nw);
+        store_cells(d.cw_next + g, n, nw);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) wv[j] = nw[j];
+        for (int j = 0; j < V; ++j) wv[j] = nw[j];
       }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < V; ++j) {
       const bool wl = ((wl4 >> (8 * j)) & 0xFFu) != 0;
       if (!d.colour) {
-        q[j] = sat255(wv[j]) | (sat255(en[j]) << 8) | (sat255(b[j]) << 16);
+        q[j] = (int)(sat255(wv[j]) | (sat255(en[j]) << 8) | (sat255(b[j]) << 16));
       } else if (o[j] < 0) {
-        q[j] = wl ? 0x808080u
-                  : (sat255(16 * min(en[j], 1 << 20)) | (sat255(64 * min(b[j], 1 << 20)) << 8) |
-                     (sat255(16 * min(wv[j], 1 << 20)) << 16));
+        q[j] = (int)(wl ? 0x808080u
+                        : (sat255(16 * min(en[j], 1 << 20)) | (sat255(64 * min(b[j], 1 << 20)) << 8) |
+                           (sat255(16 * min(wv[j], 1 << 20)) << 16)));
       }
-      q[j] |= ((o[j] >= 0 ? 1u : 0u) | (wl ? 4u : 0u) | ((uint32_t)rk[j] << 3)) << 24;
+      q[j] |= (int)(((o[j] >= 0 ? 1u : 0u) | (wl ? 4u : 0u) | ((uint32_t)rk[j] << 3)) << 24);
     }
-    store_cells4(reinterpret_cast<int32_t*>(d.rgb + g), n, reinterpret_cast<const int*>(q));
+    store_cells(reinterpret_cast<int32_t*>(d.rgb + g), n, q);
   }
   if constexpr (STEP) {
     wave_add_u64(grown, &cnt[0]);
@@ -1043,8 +1057,8 @@ __device__ __forceinline__ void ecology_cells(const Dev& d, const WorldParams& w
 // terrain writes).
 __device__ __forceinline__ void window_cells(const Dev& d, const Tile tl) {
   const WorldParams wp = d.wp[tl.world];
-  if (d.ep) ecology_cells<false>(d, wp, d.ep[tl.world], tl, 0u, nullptr, nullptr);
-  else plain_cells<false>(d, wp, tl, 0u, nullptr, nullptr, nullptr);
+  if (d.ep) ecology_cells<false, 4>(d, wp, d.ep[tl.world], tl, 0u, nullptr, nullptr);
+  else plain_cells<false, 4>(d, wp, tl, 0u, nullptr, nullptr, nullptr);
 }
 
 // With terrain: the water after the flow becomes the water of the cells of tile tl
@@ -1053,14 +1067,15 @@ __device__ __forceinline__ void settle_water(const Dev& d, const WorldParams& wp
   for (uint32_t i = 4 * threadIdx.x; i < tl.count; i += 4 * blockDim.x) {
     const uint32_t n = min(4u, tl.count - i), g = wp.cell_off + tl.start + i;
     int wv[4];
-    load_cells4(d.cw_next + g, wv);
-    store_cells4(d.cw + g, n, wv);
+    load_cells(d.cw_next + g, wv);
+    store_cells(d.cw + g, n, wv);
   }
 }
 
 // Birth claims, free lists and the survivors' sums (slot tiles), and in the same
 // launch the cell pass (cell tiles): independent work, since a claim changes neither
-// the occupancy nor the resources.
+// the occupancy nor the resources.  V: consecutive cells per thread.
+template <int V>
 __global__ __launch_bounds__(256) void k_claim_cells(Dev d, TileScratch ts, uint32_t n_actions) {
   __shared__ unsigned long long cnt[kCellPart];
   if (blockIdx.x < ts.n_slot_tiles) {
@@ -1073,8 +1088,8 @@ __global__ __launch_bounds__(256) void k_claim_cells(Dev d, TileScratch ts, uint
   const Tile tl = cell_tile(ts, tile);
   const WorldParams wp = d.wp[tl.world];
   const uint32_t step = (uint32_t)d.wv[tl.world].step;
-  if (d.ep) ecology_cells<true>(d, wp, d.ep[tl.world], tl, step, cnt, nullptr);
-  else plain_cells<true>(d, wp, tl, step, cnt, nullptr, nullptr);
+  if (d.ep) ecology_cells<true, V>(d, wp, d.ep[tl.world], tl, step, cnt, nullptr);
+  else plain_cells<true, V>(d, wp, tl, step, cnt, nullptr, nullptr);
   __syncthreads();
   if (threadIdx.x < kCellPart) ts.part_cell[tile * kCellPart + threadIdx.x] = cnt[threadIdx.x];
 }
@@ -2039,7 +2054,7 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
   const uint32_t n_children = d.wv[w].n_births;
   if (n_children) {
     const uint32_t lgp = child_split(ts, H, n_children);
-    for (uint32_t k = tid; k < n_children; k += NT)
+    for (uint32_t k = NT - 1 - tid; k < n_children; k += NT)   // from the last threads on: the first have the agents
       d.trait[wp.slot_off + (uint32_t)d.freel[wp.slot_off + k]] = child_trait(d, ts, lgp, true, k, 0u);
   }
   // 1. moves, eating, costs and deaths of the step's live agents (what the thread's
@@ -2106,8 +2121,8 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
   nblk = wave_scan(nblk);
   if (lane == 63 && nblk) atomicAdd(&cnt[PC_BB_CELL], nblk);
   const Tile all{w, 0u, cells, 0u};
-  if constexpr (ECO) ecology_cells<true>(d, wp, d.ep[w], all, step, ccnt, s_col);
-  else plain_cells<true>(d, wp, all, step, ccnt, s_agent, s_col);
+  if constexpr (ECO) ecology_cells<true, 4>(d, wp, d.ep[w], all, step, ccnt, s_col);
+  else plain_cells<true, 4>(d, wp, all, step, ccnt, s_agent, s_col);
   // the waves' sums (whole waves without agents have none), combined below
   {
     const uint32_t n_w = lane_value(wave_scan(n_t), 63);
@@ -2610,7 +2625,8 @@ __global__ __launch_bounds__(512) void k_stream_read(const probe_u32x4* __restri
 // instead of the object's own buffers.  Each GPU the library runs on holds one
 // copy until the process ends; every call on that GPU shares it.
 // ---------------------------------------------------------------------------
-constexpr size_t kStaticScratchBytes = (size_t(16) << 20) + ECO_MAX_WORLDS * sizeof(StepDraft) + ECO_MAX_PARTS * sizeof(double);
+constexpr size_t kStaticScratchBytes = (size_t(16) << 20) + ECO_MAX_WORLDS * sizeof(StepDraft) +
+                                       ECO_MAX_PARTS * sizeof(double) + ECO_SMALL_CELL_TILES * kCellPart * sizeof(uint64_t);
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 // This GPU's address of the array (the array's name in host code is only a host
@@ -2656,7 +2672,8 @@ hipError_t launch_settle(hipStream_t s, const Dev& d, const TileScratch& ts, uin
 hipError_t launch_claim_cells(hipStream_t s, const Dev& d, const TileScratch& ts, uint32_t A) {
   const uint32_t nb = ts.n_slot_tiles + ts.n_cell_tiles;
   if (nb == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_claim_cells, dim3(nb), dim3(256), 0, s, d, ts, A);
+  if (ts.cell_tile == ECO_SMALL_CELL_TILE) hipLaunchKernelGGL(k_claim_cells<1>, dim3(nb), dim3(256), 0, s, d, ts, A);
+  else hipLaunchKernelGGL(k_claim_cells<4>, dim3(nb), dim3(256), 0, s, d, ts, A);
   ECO_CHECK_LAUNCH();
 }
 // Resident blocks per CU of the birth-commit kernel for this layout (its register
