@@ -1005,14 +1005,28 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
     return fail(ECO_EDEVICE, "no HIP device");
   }
   w->birth_bpc = std::max(1, w->birth_bpc);
-  // The policy launch until the tuner or the caller sets one: 16 waves a CU with eight
-  // loads in flight each, and from 96 agents a CU on half of both, which keeps fewer
-  // streams open on each memory channel.  Measured, us per step with 16 x 8 / 8 x 4:
-  // 16,345 FP8 agents 118.3 / above 118.5, 32,768 wide BF16 agents 1,377 / 1,370, 91,431
-  // BF16 agents of 24 worlds 1,082 / 1,053, 80,900 BF16 agents with births 1,498 / 1,445.
+  // The policy launch until the tuner or the caller sets one: waves per block, blocks per
+  // CU, loads in flight per wave.
+  //  - Few agents (below 32 a CU): 4, 4, 8; nothing else is faster over their range.
+  //  - Small agents (below 20 KB of weights): 8, 2, 4, bound by instructions, not memory.
+  //    us per step against 4, 4, 8: 18,000 FP8 agents of 10 KB 49.0 / 54.8, 60,000 BF16
+  //    agents of 16 KB 173 / 191, 200,000 FP8 agents of 5 KB 334 / 357; of 31 KB the other
+  //    way, 60,000 in FP32 305 / 301.
+  //  - Others: 8, 4, 8 (blocks past the resident ones even out the ends): 16,345 FP8
+  //    agents of 37 KB 115.1 / 117.4, 8,500 BF16 agents of 72 KB 109.0 / 111.7, 60,000 FP32
+  //    agents of 71 KB 629.7 / 633.9.
+  //  - From 4.5 GB of weights: 4, 2, 4, which keeps fewer streams open on each memory
+  //    channel.  Against 8, 4, 8: 65,536 BF16 agents (4.7 GB) 728 / 736, in FP32 (9.5 GB)
+  //    1,365 / 1,374, 100,000 of 69 KB 1,001 / 1,011; 60,000 of 71 KB (4.2 GB) 633.5 / 629.7,
+  //    65,536 in FP8 (2.3 GB) 390.7 / 382.6.
   uint64_t n_init = 0;
   for (uint32_t i = 0; i < n_worlds; ++i) n_init += descs[i].n_agents_init;
-  if (n_init >= 96ull * (uint64_t)w->n_cus) w->launch = eco_launch{4, 2, 4, 0};
+  if (const uint64_t bytes = weight_bytes(w->L); n_init >= 32ull * (uint64_t)w->n_cus) {
+    if (bytes < 20480) w->launch = eco_launch{8, 2, 4, 0};
+    else if (n_init * bytes < 4500000000ull) w->launch = eco_launch{8, 4, 8, 0};
+    else w->launch = eco_launch{4, 2, 4, 0};
+  }
+
   w->ts.split_below = std::min<uint32_t>(4u * (uint32_t)w->n_cus, ECO_MAX_PARTS / 2);
   d.n_worlds = n_worlds;
   d.total_slots = w->total_slots;
