@@ -1015,16 +1015,16 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   //  - Others: 8, 4, 8 (blocks past the resident ones even out the ends): 16,345 FP8
   //    agents of 37 KB 115.1 / 117.4, 8,500 BF16 agents of 72 KB 109.0 / 111.7, 60,000 FP32
   //    agents of 71 KB 629.7 / 633.9.
-  //  - From 4.5 GB of weights: 4, 2, 4, which keeps fewer streams open on each memory
-  //    channel.  Against 8, 4, 8: 65,536 BF16 agents (4.7 GB) 728 / 736, in FP32 (9.5 GB)
-  //    1,365 / 1,374, 100,000 of 69 KB 1,001 / 1,011; 60,000 of 71 KB (4.2 GB) 633.5 / 629.7,
-  //    65,536 in FP8 (2.3 GB) 390.7 / 382.6.
+  //  - From 4.5 GB of weights: 8, 1, 4, which keeps fewer streams open on each memory
+  //    channel.  Against 8, 4, 8: 65,536 BF16 agents (4.7 GB) 727 / 736, in FP32 (9.5 GB)
+  //    1,366 / 1,374; 100,000 of 69 KB with 4, 2, 4 1,001 / 1,011, but 60,000 of 71 KB (4.2
+  //    GB) 633.5 / 629.7 and 65,536 in FP8 (2.3 GB) 390.7 / 382.6.
   uint64_t n_init = 0;
   for (uint32_t i = 0; i < n_worlds; ++i) n_init += descs[i].n_agents_init;
   if (const uint64_t bytes = weight_bytes(w->L); n_init >= 32ull * (uint64_t)w->n_cus) {
     if (bytes < 20480) w->launch = eco_launch{8, 2, 4, 0};
     else if (n_init * bytes < 4500000000ull) w->launch = eco_launch{8, 4, 8, 0};
-    else w->launch = eco_launch{4, 2, 4, 0};
+    else w->launch = eco_launch{8, 1, 4, 0};
   }
 
   w->ts.split_below = std::min<uint32_t>(4u * (uint32_t)w->n_cus, ECO_MAX_PARTS / 2);
