@@ -903,12 +903,12 @@ __device__ __forceinline__ uint32_t sat255(int v) { return (uint32_t)min(max(v, 
 // col: the occupants' sense bits by cell and colour words by slot, where the caller
 // has them in LDS; else they are read through the occupancy.
 template <bool GROW, int V>
-__device__ __forceinline__ void plain_cells(const Dev& d, const WorldParams& wp, const Tile tl, uint32_t step,
+__device__ __forceinline__ void plain_cells(const Dev& d, const WorldParams& wp, uint32_t cell_off, const Tile tl, uint32_t step,
                                             unsigned long long* cnt, const uint8_t* agent, const uint32_t* col) {
   unsigned long long grown = 0, total = 0;
 #pragma unroll 1
   for (uint32_t i = V * threadIdx.x; i < tl.count; i += V * blockDim.x) {
-    const uint32_t c0 = tl.start + i, n = min((uint32_t)V, tl.count - i), g = wp.cell_off + c0;
+    const uint32_t c0 = tl.start + i, n = min((uint32_t)V, tl.count - i), g = cell_off + c0;
     const uint32_t v = load_bytes<V>(d.res + g);
     const uint32_t wl = wp.has_walls ? load_bytes<V>(d.wall + g) : 0u;
     int o[V], q[V];   // the occupants, their sense bits or colour words
@@ -972,12 +972,12 @@ __device__ __forceinline__ void plain_cells(const Dev& d, const WorldParams& wp,
 // as red / green / blue); the agent / wall bits and the rock height in the top byte.
 // col: the live agents' colour words by slot, where the caller has them in LDS.
 template <bool STEP, int V>
-__device__ __forceinline__ void ecology_cells(const Dev& d, const WorldParams& wp, const eco_ecology& e, const Tile tl,
-                                              uint32_t step, unsigned long long* cnt, const uint32_t* col) {
+__device__ __forceinline__ void ecology_cells(const Dev& d, const WorldParams& wp, const eco_ecology& e,
+                                              uint32_t cell_off, const Tile tl, uint32_t step, unsigned long long* cnt, const uint32_t* col) {
   unsigned long long grown = 0, total = 0, wsum = 0, bsum = 0;
 #pragma unroll 1
   for (uint32_t i = V * threadIdx.x; i < tl.count; i += V * blockDim.x) {
-    const uint32_t c0 = tl.start + i, n = min((uint32_t)V, tl.count - i), g = wp.cell_off + c0;
+    const uint32_t c0 = tl.start + i, n = min((uint32_t)V, tl.count - i), g = cell_off + c0;
     int b[V], en[V], wv[V], o[V], rk[V] = {}, q[V] = {};
     load_cells(d.occ + g, o);
     load_cells(d.cb + g, b);
@@ -1058,8 +1058,8 @@ __device__ __forceinline__ void ecology_cells(const Dev& d, const WorldParams& w
 // terrain writes).
 __device__ __forceinline__ void window_cells(const Dev& d, const Tile tl) {
   const WorldParams wp = d.wp[tl.world];
-  if (d.ep) ecology_cells<false, 4>(d, wp, d.ep[tl.world], tl, 0u, nullptr, nullptr);
-  else plain_cells<false, 4>(d, wp, tl, 0u, nullptr, nullptr, nullptr);
+  if (d.ep) ecology_cells<false, 4>(d, wp, d.ep[tl.world], wp.cell_off, tl, 0u, nullptr, nullptr);
+  else plain_cells<false, 4>(d, wp, wp.cell_off, tl, 0u, nullptr, nullptr, nullptr);
 }
 
 // With terrain: the water after the flow becomes the water of the cells of tile tl
@@ -1087,10 +1087,11 @@ __global__ __launch_bounds__(256) void k_claim_cells(Dev d, TileScratch ts, uint
   if (threadIdx.x < kCellPart) cnt[threadIdx.x] = 0;
   __syncthreads();
   const Tile tl = cell_tile(ts, tile);
+  const uint32_t cell_off = ts.cap0 ? 0u : d.wp[tl.world].cell_off;   // (the only world's cells: no load to wait for)
   const WorldParams wp = d.wp[tl.world];
   const uint32_t step = (uint32_t)d.wv[tl.world].step;
-  if (d.ep) ecology_cells<true, V>(d, wp, d.ep[tl.world], tl, step, cnt, nullptr);
-  else plain_cells<true, V>(d, wp, tl, step, cnt, nullptr, nullptr);
+  if (d.ep) ecology_cells<true, V>(d, wp, d.ep[tl.world], cell_off, tl, step, cnt, nullptr);
+  else plain_cells<true, V>(d, wp, cell_off, tl, step, cnt, nullptr, nullptr);
   __syncthreads();
   if (threadIdx.x < kCellPart) ts.part_cell[tile * kCellPart + threadIdx.x] = cnt[threadIdx.x];
 }
@@ -1102,25 +1103,28 @@ __global__ __launch_bounds__(256) void k_claim_cells(Dev d, TileScratch ts, uint
 // deviations about it: M2 = sum (M2_i + n_i (mean_i - mean)^2); the slot tiles of a
 // world hold 256 slots each but the last).
 template <int NT>
-__device__ __forceinline__ void world_draft(const Dev& d, const TileScratch& ts, uint32_t w, StepDraft* dr) {
+__device__ __forceinline__ void world_draft(const Dev& d, const TileScratch& ts, uint32_t w, StepDraft* dr,
+                                            uint32_t* winners) {
   constexpr int NW = NT / 64;
-  __shared__ uint32_t s_cnt[kSlotPart + 1][NW];
+  __shared__ uint32_t s_cnt[kSlotPart + 2][NW];
   __shared__ unsigned long long s_sum[kCellPart + 4][NW];
   __shared__ double s_f[NW], s_m2[NW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t cap = d.wp[w].cap;
+  const uint32_t cap = ts.cap0 ? ts.cap0 : d.wp[w].cap;
   const uint32_t t0 = first_slot_tile(ts, w), t1 = end_slot_tile(ts, w);
   const uint32_t c0 = ts.cap0 ? 0u : ts.tile_rng[4 * w + 2], c1 = ts.cap0 ? ts.n_cell_tiles : ts.tile_rng[4 * w + 3];
-  uint32_t c[kSlotPart + 1];
+  uint32_t c[kSlotPart + 2];   // the counters, survivors, claim winners
   unsigned long long u[kCellPart + 4];
 #pragma unroll
-  for (int k = 0; k <= kSlotPart; ++k) c[k] = 0;
+  for (int k = 0; k < kSlotPart + 2; ++k) c[k] = 0;
 #pragma unroll
   for (int k = 0; k < kCellPart + 4; ++k) u[k] = 0;
   double sum = 0.0;
   for (uint32_t t = t0 + threadIdx.x; t < t1; t += NT) {
     const uint4* pr = reinterpret_cast<const uint4*>(ts.part_slot + t * kSlotPart);
-    const uint32_t n = min((uint32_t)kSlotTile, cap - (t - t0) * kSlotTile) - ts.scan[t * 4 + 1];
+    const uint2 sc = *reinterpret_cast<const uint2*>(ts.scan + t * 4);   // winners, free slots
+    const uint32_t n = min((uint32_t)kSlotTile, cap - (t - t0) * kSlotTile) - sc.y;
+    c[kSlotPart + 1] += sc.x;
 #pragma unroll
     for (int k = 0; k < kSlotPart / 4; ++k) {
       const uint4 v = pr[k];
@@ -1148,7 +1152,7 @@ __device__ __forceinline__ void world_draft(const Dev& d, const TileScratch& ts,
   sum = wave_scan(sum);
   if (lane == 63) s_f[wave] = sum;
 #pragma unroll
-  for (int k = 0; k <= kSlotPart; ++k) {
+  for (int k = 0; k < kSlotPart + 2; ++k) {
     const uint32_t v = wave_scan(c[k]);
     if (lane == 63) s_cnt[k][wave] = v;
   }
@@ -1181,6 +1185,11 @@ __device__ __forceinline__ void world_draft(const Dev& d, const TileScratch& ts,
 #pragma unroll
     for (int i = 0; i < NW; ++i) v += s_cnt[threadIdx.x][i];
     dr->count[threadIdx.x] = v;
+  } else if (threadIdx.x == 32) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) v += s_cnt[kSlotPart + 1][i];
+    *winners = v;
   } else if (threadIdx.x == 64) {
     unsigned long long v[kCellPart + 4];
 #pragma unroll
@@ -1606,23 +1615,12 @@ __device__ __forceinline__ void place_child(const Dev& d, uint32_t w, uint32_t k
 // or by the small-world kernel) completed by the births.  With births, the trait moments follow once
 // the children are written (settle_record).
 __device__ __forceinline__ void world_record(const Dev& d, const TileScratch& ts, uint32_t w, bool ranked) {
-  __shared__ uint32_t s_win[kSlotTile / 64];
   __shared__ StepDraft drafted;
-  if (!ranked) world_draft<kSlotTile>(d, ts, w, &drafted);
+  __shared__ uint32_t winners;
+  if (!ranked) world_draft<kSlotTile>(d, ts, w, &drafted, &winners);
   const StepDraft& dr = ranked ? d.draft[w] : drafted;
   WorldVar& v = d.wv[w];
-  uint32_t nw = v.n_win;
-  const uint32_t n_free = v.n_free;
-  if (ts.cap0 && !ranked) {
-    uint32_t win = 0;
-    for (uint32_t i = threadIdx.x; i < ts.n_slot_tiles; i += kSlotTile) win += ts.scan[i * 4];
-    win = wave_scan(win);
-    if ((threadIdx.x & 63u) == 63u) s_win[threadIdx.x >> 6] = win;
-    __syncthreads();
-    nw = 0;
-#pragma unroll
-    for (int i = 0; i < kSlotTile / 64; ++i) nw += s_win[i];
-  }
+  const uint32_t nw = ranked ? v.n_win : winners, n_free = v.n_free;
   if (threadIdx.x != 0) return;
   const uint32_t nb = min(nw, n_free), n = dr.n0 + nb;
   eco_stats st = {};
@@ -1716,7 +1714,7 @@ __device__ __forceinline__ void live_tile(const Dev& d, const TileScratch& ts, u
 // read from bparent where the small-world kernel has ranked the winners.
 // base: the first block's number (the roles can be launched apart).
 template <int WDT, int H>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WDT == 0 ? 6 : 5)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WDT == 1 ? 6 : 7)))
 void k_birth_commit(CommitArgs by_value) {
   __shared__ uint32_t off[kMaxWorlds + 1], off_win[kMaxWorlds + 1];
   __shared__ uint32_t run_win[256 + 1];
@@ -2122,8 +2120,8 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
   nblk = wave_scan(nblk);
   if (lane == 63 && nblk) atomicAdd(&cnt[PC_BB_CELL], nblk);
   const Tile all{w, 0u, cells, 0u};
-  if constexpr (ECO) ecology_cells<true, 4>(d, wp, d.ep[w], all, step, ccnt, s_col);
-  else plain_cells<true, 4>(d, wp, all, step, ccnt, s_agent, s_col);
+  if constexpr (ECO) ecology_cells<true, 4>(d, wp, d.ep[w], wp.cell_off, all, step, ccnt, s_col);
+  else plain_cells<true, 4>(d, wp, wp.cell_off, all, step, ccnt, s_agent, s_col);
   // the waves' sums (whole waves without agents have none), combined below
   {
     const uint32_t n_w = lane_value(wave_scan(n_t), 63);
