@@ -71,3 +71,36 @@ def test_revived_slots_have_their_initial_weights(eco, wdtype, ecology):
     compare_world(gw, ow, "revived", 3, weights_slots=200)
     assert_stats_match(gw.stats()[3], ow.stats(), "revived")
     gw.close()
+
+
+# row maxima inside and outside 2^-60 ... 2^100 times 448, where the quantiser changes path; the smallest and
+# largest floats; ties between two FP8 values, values that round to a zero of either sign
+@pytest.mark.parametrize("hidden", [32, 128])
+@pytest.mark.parametrize("top", [1e-44, 2.0 ** -100, 448 * 2.0 ** -60, 448 * 2.0 ** -60 * (1 - 2.0 ** -23), 448 * 2.0 ** -20,
+                                 1.0, 3.7, 448.0, 448 * 2.0 ** 100, 448 * 2.0 ** 100 * (1 + 2.0 ** -22), 3.4e38])
+def test_written_fp8_weights_are_quantised_exactly(eco, hidden, top):
+    cfg = wl.desc(width=16, height=16, n_agents_init=3, capacity=5, window=3, n_scalars=8, n_actions=7, hidden1=hidden,
+                  hidden2=hidden, wdtype=wl.FP8, seed=1)
+    gw = eco.World(cfg)
+    D, H, A = gw.info["input_dim"], hidden, 7
+    rng = np.random.default_rng([hidden, int(np.float32(top).view(np.int32))])
+    grid = np.array([orc.fp8_decode(q) for q in range(127)], np.float64)
+    ties = np.concatenate([(grid[:-1] + grid[1:]) / 2, grid, [1e-4, 0.0]])
+    layers, want = [], []
+    for rows, cols, bias in ((H, D, H), (H, H, H), (A, H, A)):
+        amax = np.float32(top) * rng.choice(np.float32([1, 0.75, 2.0 ** -6]), rows).astype(np.float32)
+        scale = np.where(amax > 0, amax / np.float32(448), np.float32(1)).astype(np.float32)
+        pick = rng.choice(ties, (rows, cols)) / 448 * rng.choice([-1, 1], (rows, cols))
+        w = np.where(rng.random((rows, cols)) < 0.5, pick, rng.uniform(-1, 1, (rows, cols))) * amax[:, None].astype(np.float64)
+        w = np.clip(w, -amax[:, None].astype(np.float64), amax[:, None].astype(np.float64)).astype(np.float32)
+        w[:, 0] = amax * rng.choice(np.float32([-1, 1]), rows)
+        with np.errstate(over="ignore", under="ignore", divide="ignore", invalid="ignore"):
+            q = w / scale[:, None]
+        dec = np.array([orc.fp8_decode(orc.fp8_rne_sat(float(x))) for x in q.ravel()]).reshape(q.shape)
+        b = rng.standard_normal(bias).astype(np.float32)
+        layers += [w.ravel(), b]
+        want += [(dec * scale[:, None].astype(np.float64)).ravel(), b.astype(np.float64)]
+    gw.write_weights(1, np.concatenate(layers))
+    np.testing.assert_array_equal(gw.read_weights(1, master=True), np.concatenate(layers).astype(np.float64))
+    np.testing.assert_array_equal(gw.read_weights(1), np.concatenate(want))
+    gw.close()
