@@ -422,7 +422,16 @@ struct AgentId {
 };
 __device__ __forceinline__ AgentId find_agent(const uint32_t* woff, bool one, uint32_t g, uint32_t w) {
   if (one) return AgentId{0u, (uint32_t)sload(DEV_ARG(live) + g)};
-  while (g >= uni(woff[w + 1])) ++w;
+  // the next world or the one after it, else by halving: a wave's agents lie n_waves
+  // apart (1,024 worlds of 60 agents, passed one by one 230.8 us a step, now 226.0)
+  if (g >= uni(woff[w + 1]) && g >= uni(woff[++w + 1])) {
+    uint32_t hi = DEV_ARG(n_worlds);   // woff[w + 1] <= g < woff[hi]
+    for (++w; hi - w > 1;) {
+      const uint32_t mid = (w + hi) / 2;
+      if (g >= uni(woff[mid])) w = mid;
+      else hi = mid;
+    }
+  }
   return AgentId{w, (uint32_t)sload(DEV_ARG(live) + WORLD_PARAM(w, slot_off) + (g - uni(woff[w])))};
 }
 
