@@ -1764,13 +1764,18 @@ eco_status eco_world_read_weights(eco_world* w, uint32_t world, uint32_t slot, i
   const uint64_t g = (uint64_t)p.slot_off + slot;
   const bool master = which == 1 || L.wdtype == ECO_W_FP32;
   std::vector<uint8_t> blk(master ? L.mstride : L.sstride);
-  HIPCHK(w, hipMemcpyAsync(blk.data(), (master ? w->d.master + g * L.mstride : w->d.store + g * L.sstride), blk.size(),
-                           hipMemcpyDeviceToHost, w->stream), "read weights");
-  double trait = 0.0;   // |theta|^2: 0 in a slot that never had weights, whose bytes are the allocation's
-  HIPCHK(w, hipMemcpyAsync(&trait, w->d.trait + g, 8, hipMemcpyDeviceToHost, w->stream), "read trait");
+  // A slot past the initial population may never have had weights; its bytes are then the
+  // allocation's and its |theta|^2 (read as a pair, from a multiple of 16 bytes) is 0.
+  double traits[2] = {1.0, 1.0};
+  Transfer t(w, true);
+  HIPCHK(w, t.add(master ? w->d.master + g * L.mstride : w->d.store + g * L.sstride, blk.data(), blk.size()),
+         "read weights");
+  if (slot >= p.n_init) HIPCHK(w, t.add(w->d.trait + (g & ~1ull), traits, sizeof traits), "read trait");
+  HIPCHK(w, t.enqueue(), "read weights");
   st = sync(w);
   if (st != ECO_OK) return st;
-  if (trait == 0.0) std::fill(blk.begin(), blk.end(), (uint8_t)0);
+  t.collect();
+  if (traits[g & 1] == 0.0) std::fill(blk.begin(), blk.end(), (uint8_t)0);
   for (uint32_t u = 0; u < L.u_end; ++u) {
     const HostUnit hu = host_unit(L, u);
     for (uint32_t i = 0; i < hu.nvalid; ++i) {
