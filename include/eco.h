@@ -294,7 +294,7 @@ eco_status eco_world_prepare(eco_world* w, uint32_t n_steps);
  * allocation, no graph and no allocating library call.  The step's scratch
  * (tile partials, birth lists, step counters: about 8 bytes per slot plus
  * 128 bytes per 256-slot tile) lives in one static device array of 16 MiB per
- * GPU, held until the process ends; an object that needs more gets EINVAL and
+ * GPU (0.3 MiB behind it hold what does not grow with the slots), held until the process ends; an object that needs more gets EINVAL and
  * nothing runs.  Every call on a GPU shares that GPU's array and nothing in it
  * has to start cleared; calls that overlap on one GPU (objects stepped on
  * different streams at once) race and must be serialised by the caller.
