@@ -294,10 +294,11 @@ eco_status eco_world_prepare(eco_world* w, uint32_t n_steps);
  * allocation, no graph and no allocating library call.  The step's scratch
  * (tile partials, birth lists, step counters: about 8 bytes per slot plus
  * 128 bytes per 256-slot tile) lives in one static device array of 16 MiB per
- * GPU (0.3 MiB behind it hold what does not grow with the slots), held until the process ends; an object that needs more gets EINVAL and
- * nothing runs.  Every call on a GPU shares that GPU's array and nothing in it
- * has to start cleared; calls that overlap on one GPU (objects stepped on
- * different streams at once) race and must be serialised by the caller.
+ * GPU (0.3 MiB behind it hold what does not grow with the slots), held until
+ * the process ends; an object that needs more gets EINVAL and nothing runs.
+ * Every call on a GPU shares that GPU's array and nothing in it has to start
+ * cleared; calls that overlap on one GPU (objects stepped on different streams
+ * at once) race and must be serialised by the caller.
  * Returns like eco_world_step (asynchronous; ECO_RT_TIME_KERNELS and
  * ECO_RT_USE_GRAPH are ignored, ECO_RT_KEEP_LOGITS applies). */
 eco_status eco_world_step_static(eco_world* w, uint32_t n_steps);
