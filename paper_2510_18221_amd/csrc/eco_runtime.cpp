@@ -39,7 +39,7 @@ hipError_t launch_segments(hipStream_t s, const Segments& g, uint32_t n, uint32_
 hipError_t launch_records_out(hipStream_t s, const Dev& d, uint32_t n, void* host);
 hipError_t launch_stream_read(hipStream_t s, const void* p, uint64_t n16, uint32_t* sink, uint32_t blocks,
                               uint32_t threads);
-hipError_t launch_resource_total(hipStream_t s, const Dev& d, int only_world);
+hipError_t launch_resource_total(hipStream_t s, const Dev& d, int only_world, uint32_t most_cells);
 hipError_t launch_render(hipStream_t s, const Dev& d, const TileScratch& ts, int world);
 hipError_t launch_flowdir(hipStream_t s, const Dev& d, const TileScratch& ts, int world);
 hipError_t launch_init_cells(hipStream_t s, const Dev& d, const Tile* tiles, uint32_t nt);
@@ -461,7 +461,9 @@ eco_status run_init(eco_world* w) {
   HIPCHK(w, launch_init_weights(s, d, w->L, nullptr, (uint32_t)n, false, w->std1, w->std2, w->std3, (uint32_t)w->n_cus),
          "init weights");
   HIPCHK(w, launch_compact(s, d, w->ts, -1), "compact");
-  HIPCHK(w, launch_resource_total(s, d, -1), "resource total");
+  uint32_t most_cells = 0;
+  for (const auto& p : w->wp) most_cells = std::max(most_cells, p.cells);
+  HIPCHK(w, launch_resource_total(s, d, -1, most_cells), "resource total");
   eco_status st = sync(w);
   if (st != ECO_OK) return st;
   w->broken = false;
@@ -1649,7 +1651,7 @@ eco_status eco_world_write_state(eco_world* w, uint32_t world, const void* buf, 
                                   w->std3, (uint32_t)w->n_cus), "init weights");
   }
   HIPCHK(w, launch_compact(s, w->d, w->ts, (int)world), "compact");
-  HIPCHK(w, launch_resource_total(s, w->d, (int)world), "resource total");
+  HIPCHK(w, launch_resource_total(s, w->d, (int)world, p.cells), "resource total");
   return sync(w);
 }
 

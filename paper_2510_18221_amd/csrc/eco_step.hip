@@ -2273,11 +2273,11 @@ __global__ __launch_bounds__(256) void k_flowdir(Dev d, const Tile* __restrict__
 }
 
 // Grid totals of the records of init and state writes, whose record has just been
-// written with zeros there: blockIdx.y is the world, its blocks add their shares.
-__global__ __launch_bounds__(256) void k_resource_total(Dev d, int only_world) {
+// written with zeros there: first_world + blockIdx.y is the world, its blocks of 1,024
+// cells (or slots, at 256 at least) a pass add their shares.
+__global__ __launch_bounds__(256) void k_resource_total(Dev d, uint32_t first_world) {
   __shared__ unsigned long long cnt[3];
-  const uint32_t w = blockIdx.y;
-  if (only_world >= 0 && (int)w != only_world) return;
+  const uint32_t w = first_world + blockIdx.y;
   if (threadIdx.x < 3) cnt[threadIdx.x] = 0;
   __syncthreads();
   const WorldParams wp = d.wp[w];
@@ -2781,9 +2781,10 @@ hipError_t launch_render(hipStream_t s, const Dev& d, const TileScratch& ts, int
   hipLaunchKernelGGL(k_render, dim3(ts.n_cell_tiles), dim3(256), 0, s, d, ts.cell_tiles, world);
   ECO_CHECK_LAUNCH();
 }
-hipError_t launch_resource_total(hipStream_t s, const Dev& d, int only_world) {
-  const uint32_t blocks = std::min<uint32_t>(64u, std::max<uint32_t>(1u, d.total_cells / 16384u));
-  hipLaunchKernelGGL(k_resource_total, dim3(blocks, d.n_worlds), dim3(256), 0, s, d, only_world);
+// most_cells: of one of the worlds.
+hipError_t launch_resource_total(hipStream_t s, const Dev& d, int only_world, uint32_t most_cells) {
+  const dim3 grid(std::min<uint32_t>(256u, (most_cells + 1023u) / 1024u), only_world < 0 ? d.n_worlds : 1u);
+  hipLaunchKernelGGL(k_resource_total, grid, dim3(256), 0, s, d, only_world < 0 ? 0u : (uint32_t)only_world);
   ECO_CHECK_LAUNCH();
 }
 hipError_t launch_init_cells(hipStream_t s, const Dev& d, const Tile* tiles, uint32_t nt) {
