@@ -1211,24 +1211,24 @@ eco_status eco_world_step_with_actions(eco_world* w, const uint8_t* actions) {
   eco_status st = check_world(w);
   if (st != ECO_OK) return st;
   if (!actions) return fail(ECO_EINVAL, "actions is NULL");
-  // validate against the live slots
-  std::vector<uint8_t> flags(w->total_slots), act(w->total_slots, 0);
-  {
+  std::vector<uint8_t> act(w->total_slots, 0);
+  bool in_range = true;
+  uint64_t k = 0;
+  for (const auto& p : w->wp)
+    for (uint32_t s = 0; s < p.cap; ++s, ++k) {
+      act[p.slot_off + s] = actions[k];
+      in_range &= actions[k] < w->L.A;
+    }
+  if (!in_range) {   // only a live slot's action has to be one (else no look at them, 13 us with the wait for it)
+    std::vector<uint8_t> flags(w->total_slots);
     Transfer in(w, true);
     HIPCHK(w, in.add(w->d.flags, flags.data(), w->total_slots), "read flags");
     HIPCHK(w, in.enqueue(), "read flags");
     st = sync(w);
     if (st != ECO_OK) return st;
     in.collect();
-  }
-  uint64_t k = 0;
-  for (uint32_t i = 0; i < w->n_worlds; ++i) {
-    const WorldParams& p = w->wp[i];
-    for (uint32_t s = 0; s < p.cap; ++s, ++k) {
-      const uint8_t a = actions[k];
-      if ((flags[p.slot_off + s] & kAlive) && a >= w->L.A) return fail(ECO_EINVAL, "action out of range for a live slot");
-      act[p.slot_off + s] = a;
-    }
+    for (uint32_t g = 0; g < w->total_slots; ++g)
+      if ((flags[g] & kAlive) && act[g] >= w->L.A) return fail(ECO_EINVAL, "action out of range for a live slot");
   }
   Transfer up(w, false);
   HIPCHK(w, up.add(w->d.act_in, act.data(), w->total_slots), "upload actions");

@@ -68,3 +68,23 @@ def test_written_state_reads_back(eco, cap, w, h, ecology):
     assert [s["population"] for s in stats] == [20, int(st["alive"].sum()), 30]
     assert stats[1]["step"] == st["step"]
     world.close()
+
+
+@pytest.mark.parametrize("worlds", [1, 3])
+def test_actions_out_of_range(eco, worlds):
+    """An action that does not exist is refused for a live slot, before anything moves, and ignored for a free one."""
+    cfgs = [wl.desc(width=9, height=7, n_agents_init=5, capacity=11, window=3, n_actions=7, seed=i) for i in range(worlds)]
+    a, b = eco.World(cfgs), eco.World(cfgs)
+    acts = np.full(11 * worlds, 4, np.uint8)
+    acts[11 * worlds - 1] = 255   # a free slot of the last world
+    a.step_with_actions(acts)
+    b.step_with_actions(np.full(11 * worlds, 4, np.uint8))
+    for bad in (7, 255):
+        acts[11 * worlds - 11] = bad   # a live slot of the last world
+        with pytest.raises(Exception, match="action out of range"):
+            a.step_with_actions(acts)
+    for i in range(worlds):
+        np.testing.assert_array_equal(a.read_state_raw(i), b.read_state_raw(i))
+    assert a.stats() == b.stats()
+    a.close()
+    b.close()
