@@ -249,10 +249,10 @@ typedef struct {
                                    ECO_K_MOVE); this flag runs the separate kernels instead.  Same
                                    integer state and statistics either way (the trait moments to
                                    rounding). */
-/* The single-block launch's limits: the most slots and cells it could hold (each
- * world's ranges rounded up to 64). */
+/* The most slots and cells (each rounded up to 64) of an object of one world that takes
+ * the single-block launch. */
 #define ECO_SMALL_STEP_MAX_SLOTS 8192u
-#define ECO_SMALL_STEP_MAX_CELLS 16384u
+#define ECO_SMALL_STEP_MAX_CELLS 4096u
 
 /* Create n_worlds worlds (all with the same window, n_scalars, hidden sizes,
  * n_actions and wdtype) and run the deterministic init of Sec. 3.3 / placement.

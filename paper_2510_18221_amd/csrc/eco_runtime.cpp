@@ -530,11 +530,9 @@ hipError_t launch_group(eco_world* w, hipStream_t s, const Dev& d, const TileScr
 // 16.7 / 19.1, 80^2 17.7 / 18.8, with three births a step 64^2 21.2 / 20.8, 80^2 22.8 / 21.1,
 // 96^2 23.8 / 21.3; the ecology 48^2 21.4 / 22.4, 64^2 21.9 / 22.8, 80^2 23.8 / 23.0 (with
 // terrain and colours 48^2 24.2 / 25.3, 64^2 25.4 / 25.1, 80^2 28.5 / 25.5).
-constexpr uint32_t kSmallSlots = ECO_SMALL_STEP_MAX_SLOTS, kSmallCells = 4096;
-static_assert(kSmallCells <= ECO_SMALL_STEP_MAX_CELLS, "inside what the kernel holds");
 bool small_step(const eco_world* w) {
-  return w->n_worlds == 1 && w->total_slots <= kSmallSlots && w->total_cells <= kSmallCells &&
-         !(w->rt_flags & ECO_RT_SPLIT_STEP);
+  return w->n_worlds == 1 && w->total_slots <= ECO_SMALL_STEP_MAX_SLOTS &&
+         w->total_cells <= ECO_SMALL_STEP_MAX_CELLS && !(w->rt_flags & ECO_RT_SPLIT_STEP);
 }
 
 // Enqueue one step's kernels.  timed: bracket each kernel group with events.

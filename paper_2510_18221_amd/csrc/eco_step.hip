@@ -2035,6 +2035,7 @@ __global__ __launch_bounds__(1024) void k_step_small(Dev d, TileScratch ts, uint
   // the slots (the capacity is at most NT CH NP)
   constexpr int NT = 1024, CH = 4, NP = 2, NW = NT / 64;
   static_assert(NT * CH * NP == ECO_SMALL_STEP_MAX_SLOTS, "the slot passes cover the largest object taken");
+  static_assert(NT * CH == ECO_SMALL_STEP_MAX_CELLS, "a group of four cells per thread");
   static_assert(64 * CH == kSlotTile, "one wave's slots of a pass are one slot tile");
   if (blockIdx.x == 1) {   // the second block completes the last step's record from the blocks' shares
     settle_record<NT, false>(d, ts, 0, H, true);
