@@ -25,6 +25,7 @@
 // Every contended write of a move is an atomicMin on a claim word; every other write
 // goes to a unique slot or cell, so the integer state is independent of scheduling.
 #include <algorithm>
+#include <cstddef>
 #include <mutex>
 
 #include "eco_device.h"
@@ -1457,6 +1458,9 @@ struct CommitArgs {
   TileScratch ts;
   uint32_t base, first_birth, n_birth_blocks, ranked;   // first_birth: the first birth block's number
 };
+static_assert(offsetof(CommitArgs, d) == offsetof(WeightArgs, d) && offsetof(CommitArgs, L) == offsetof(WeightArgs, L),
+              "write_weights reads these through WeightArgs");
+// (The segment's address is a kernel's own: whatever calls args() is always inlined.)
 template <typename A = CommitArgs>
 __device__ __forceinline__ const A& args() {
   typedef const __attribute__((address_space(4))) A* seg_ptr;
@@ -1477,7 +1481,7 @@ struct Noise {
   uint32_t key0, key1, slot, step;
 };
 template <int WDT, int H, int NT, int MODE>
-__device__ double write_weights(uint32_t child, uint32_t parent, const Noise nz, const PartRows<H> pr,
+__device__ __forceinline__ double write_weights(uint32_t child, uint32_t parent, const Noise nz, const PartRows<H> pr,
                                 const double2* tab, uint32_t* s_amax, double* s_red) {
   constexpr uint32_t stream = MODE == W_BIRTH ? ST_MUTATE : ST_WINIT;
   const uint32_t tid = threadIdx.x, key0 = nz.key0, key1 = nz.key1, rng_slot = nz.slot, step = nz.step;
@@ -2540,6 +2544,8 @@ struct InitArgs {
   uint32_t n;
   double sd[3];
 };
+static_assert(offsetof(InitArgs, d) == offsetof(WeightArgs, d) && offsetof(InitArgs, L) == offsetof(WeightArgs, L),
+              "write_weights reads these through WeightArgs");
 template <int WDT, int H, int MODE>
 __global__ __launch_bounds__(256) void k_init_weights(InitArgs by_value) {
   __shared__ uint32_t off[kMaxWorlds + 1];
