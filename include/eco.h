@@ -20,9 +20,10 @@
  *  - Device buffers are owned by the eco_world (allocated through the caller's
  *    eco_allocator when one is given, else hipMalloc) and released by
  *    eco_world_destroy.  Host buffers passed in stay owned by the caller.
- *  - The calls that move state, statistics, logits or actions between host and
- *    device use one pinned host buffer of 1 MiB per object, allocated by the first of
- *    them and released by eco_world_destroy (copies do without it if that fails).
+ *  - The calls that move state, statistics, weights, logits or actions between host and
+ *    device borrow a pinned host buffer of 1 MiB for their duration.  The objects of
+ *    a process share at most 8 of them; the first is allocated with the first object,
+ *    and the idle ones are released with the last (a call that gets none copies instead).
  *  - All work is enqueued on the stream given at create (NULL = the null
  *    stream).  eco_world_step is asynchronous; calls that return data to the
  *    host synchronise that stream first.

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "eco_device.h"
+#include "host_pool.h"
 
 namespace eco {
 hipError_t launch_forward_w0(int H, int U, dim3 grid, dim3 block, size_t shmem, hipStream_t s, const Dev& d,
@@ -136,7 +137,8 @@ struct eco_world {
   std::vector<TimedGraph> tgraphs;
   eco_kernel_times kt{};
   uint64_t device_bytes = 0;
-  uint8_t* host = nullptr;   // pinned buffer of the host transfers (kHostBytes, from the first one on)
+  uint8_t* host = nullptr;   // pinned buffer of the present transfer (kHostBytes, the pool's)
+  bool pooled = false;       // has joined the pool
 };
 
 namespace {
@@ -387,25 +389,50 @@ eco_status sync(eco_world* w) {
 }
 
 // Transfers of several arrays between the device and the caller's memory.  Small
-// arrays go through the object's pinned buffer in one launch; an array above
+// arrays go through a pinned buffer in one launch; an array above
 // kSegmentBytes, or one that the buffer has no room for, is copied by itself (the
 // copy's fixed cost, 10 - 17 us, is then small beside its bytes).  The state of the
 // 64 x 64 world, 152 KB in 13 arrays, takes 20 us where copies took 240, that of a
 // 1024 x 1024 world, 10.4 MB, 580 where they took 700.
-// Allocating the buffer takes 20 - 50 us at 1 MiB and up to 330 at 2 MiB.
+// Allocating a buffer takes 15 - 60 us at 1 MiB and 330 at 2 MiB.
 constexpr size_t kHostBytes = size_t(1) << 20, kSegmentBytes = size_t(256) << 10;
 
-bool host_buffer(eco_world* w) {
-  if (!w->host && hipHostMalloc((void**)&w->host, kHostBytes, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    w->host = nullptr;
-  }
-  return w->host != nullptr;
+HostPool& host_pool() {   // (never destroyed: a buffer may outlive main's objects)
+  static HostPool* pool = new HostPool(
+      kHostBytes,
+      [](size_t n) -> void* {
+        void* p = nullptr;
+        if (hipHostMalloc(&p, n, hipHostMallocPortable) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
+      },
+      [](void* p) { (void)hipHostFree(p); });
+  return *pool;
 }
+
+// The object's loan of a buffer for one transfer: given back at the end of the scope, by
+// when the stream has been waited for.  A device error leaves that open and the object in
+// its error state: it keeps the buffer until a reset or its end has waited.
+class Loan {
+ public:
+  explicit Loan(eco_world* w) : w_(w) {
+    if (!w->host) w->host = (uint8_t*)host_pool().take();
+  }
+  ~Loan() {
+    if (!w_->host || w_->broken) return;
+    host_pool().give(w_->host);
+    w_->host = nullptr;
+  }
+  Loan(const Loan&) = delete;
+  Loan& operator=(const Loan&) = delete;
+
+ private:
+  eco_world* w_;
+};
 
 class Transfer {
  public:
-  Transfer(eco_world* w, bool out) : w_(w), out_(out), have_(host_buffer(w)) {}
+  Transfer(eco_world* w, bool out) : w_(w), loan_(w), out_(out), have_(w->host != nullptr) {}
   // Adds an array of n bytes at dev, its host side at mem (out: filled by wait()).
   // dev lies at a multiple of 16 bytes.
   hipError_t add(void* dev, void* mem, size_t n) {
@@ -430,6 +457,7 @@ class Transfer {
 
  private:
   eco_world* w_;
+  Loan loan_;
   bool out_, have_;
   Segments g_{};
   void* mem_[kMaxSegments] = {};
@@ -464,6 +492,10 @@ eco_status run_init(eco_world* w) {
   uint32_t most_cells = 0;
   for (const auto& p : w->wp) most_cells = std::max(most_cells, p.cells);
   HIPCHK(w, launch_resource_total(s, d, -1, most_cells), "resource total");
+  if (!w->pooled) {   // (while the device is at work)
+    host_pool().join();
+    w->pooled = true;
+  }
   eco_status st = sync(w);
   if (st != ECO_OK) return st;
   w->broken = false;
@@ -1078,11 +1110,12 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
 
 void eco_world_destroy(eco_world* w) {
   if (!w) return;
-  (void)hipStreamSynchronize(w->stream);
+  const bool idle = hipStreamSynchronize(w->stream) == hipSuccess;
+  if (w->host && idle) host_pool().give(w->host);   // (else no transfer gets it any more)
+  if (w->pooled) host_pool().leave();
   drop_graph(w);
   for (auto e : w->ev_pool) (void)hipEventDestroy(e);
   if (w->cap_stream) (void)hipStreamDestroy(w->cap_stream);
-  if (w->host) (void)hipHostFree(w->host);
   free_all(w);
   delete w;
 }
@@ -1258,7 +1291,8 @@ eco_status eco_world_stats(eco_world* w, eco_stats* out, uint32_t max_worlds) {
   const uint32_t n = std::min(max_worlds, w->n_worlds);
   if (n == 0) return sync(w);
   static_assert(sizeof(eco_stats) * ECO_MAX_WORLDS <= kHostBytes, "every world's record fits the buffer");
-  if (host_buffer(w)) {
+  Loan loan(w);
+  if (w->host) {
     HIPCHK(w, launch_records_out(w->stream, w->d, n, w->host), "read stats");
     st = sync(w);
     if (st == ECO_OK) std::memcpy(out, w->host, sizeof(eco_stats) * n);
