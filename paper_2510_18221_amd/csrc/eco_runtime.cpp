@@ -394,8 +394,11 @@ eco_status sync(eco_world* w) {
 // copy's fixed cost, 10 - 17 us, is then small beside its bytes).  The state of the
 // 64 x 64 world, 152 KB in 13 arrays, takes 20 us where copies took 240, that of a
 // 1024 x 1024 world, 10.4 MB, 580 where they took 700.
+// A read of one array above kLoneBytes is a copy: the launch, then 5 - 6 GB/s out of the
+// buffer against the copy's 20 (through the buffer / copied, us: 4 KB 12 / 20, 16 KB 12.3 /
+// 20.3, 32 KB 13.4 / 9.8, 128 KB 22.9 / 20.1, weights of 144 KB 44 / 36).
 // Allocating a buffer takes 15 - 60 us at 1 MiB and 330 at 2 MiB.
-constexpr size_t kHostBytes = size_t(1) << 20, kSegmentBytes = size_t(256) << 10;
+constexpr size_t kHostBytes = size_t(1) << 20, kSegmentBytes = size_t(256) << 10, kLoneBytes = size_t(16) << 10;
 
 HostPool& host_pool() {   // (never destroyed: a buffer may outlive main's objects)
   static HostPool* pool = new HostPool(
@@ -448,8 +451,14 @@ class Transfer {
     used_ += room;
     return hipSuccess;
   }
-  // Enqueues the launch; the buffer belongs to it until the stream has been waited for.
-  hipError_t enqueue() { return count_ ? launch_segments(w_->stream, g_, count_, most_, w_->host, out_) : hipSuccess; }
+  // Enqueues the launch (or a lone array's copy); the buffer belongs to it until the stream has been waited for.
+  hipError_t enqueue() {
+    if (out_ && count_ == 1 && g_.s[0].bytes > kLoneBytes) {
+      count_ = 0;
+      return hipMemcpyAsync(mem_[0], g_.s[0].dev, g_.s[0].bytes, hipMemcpyDeviceToHost, w_->stream);
+    }
+    return count_ ? launch_segments(w_->stream, g_, count_, most_, w_->host, out_) : hipSuccess;
+  }
   // After the stream has been waited for: the gathered arrays to their places.
   void collect() {
     for (uint32_t i = 0; i < count_; ++i) std::memcpy(mem_[i], w_->host + 16ull * g_.s[i].at, g_.s[i].bytes);
