@@ -44,7 +44,7 @@ hipError_t launch_resource_total(hipStream_t s, const Dev& d, int only_world, ui
 hipError_t launch_render(hipStream_t s, const Dev& d, const TileScratch& ts, int world);
 hipError_t launch_flowdir(hipStream_t s, const Dev& d, const TileScratch& ts, int world);
 hipError_t launch_init_cells(hipStream_t s, const Dev& d, const Tile* tiles, uint32_t nt);
-hipError_t launch_init_agents(hipStream_t s, const Dev& d, const Tile* tiles, uint32_t nt);
+hipError_t launch_init_agents(hipStream_t s, const Dev& d, const Layout& L, const Tile* tiles, uint32_t nt);
 hipError_t launch_init_weights(hipStream_t s, const Dev& d, const Layout& L, const uint32_t* list, uint32_t n,
                                bool requant, double std1, double std2, double std3, uint32_t n_cus);
 hipError_t launch_placement(hipStream_t s, const Dev& d, const Tile* cell_tiles, uint32_t nt, const void* pinfo,
@@ -492,7 +492,7 @@ eco_status run_init(eco_world* w) {
   HIPCHK(w, hipMemsetAsync(w->place_cnt, 0, 4ull * w->n_buckets, s), "clear placement counts");
   HIPCHK(w, launch_placement(s, d, w->cell_tiles, w->n_cell_tiles, w->place_info, w->place_cnt, w->place_sums,
                              w->place_start, w->most_buckets), "placement");
-  HIPCHK(w, launch_init_agents(s, d, w->slot_tiles, w->n_slot_tiles), "init agents");
+  HIPCHK(w, launch_init_agents(s, d, w->L, w->slot_tiles, w->n_slot_tiles), "init agents");
   uint64_t n = 0;
   for (const auto& de : w->descs) n += de.n_agents_init;
   HIPCHK(w, launch_init_weights(s, d, w->L, nullptr, (uint32_t)n, false, w->std1, w->std2, w->std3, (uint32_t)w->n_cus),
@@ -1807,18 +1807,26 @@ eco_status eco_world_read_weights(eco_world* w, uint32_t world, uint32_t slot, i
   const uint64_t g = (uint64_t)p.slot_off + slot;
   const bool master = which == 1 || L.wdtype == ECO_W_FP32;
   std::vector<uint8_t> blk(master ? L.mstride : L.sstride);
-  // A slot past the initial population may never have had weights; its bytes are then the
-  // allocation's and its |theta|^2 (read as a pair, from a multiple of 16 bytes) is 0.
-  double traits[2] = {1.0, 1.0};
-  Transfer t(w, true);
-  HIPCHK(w, t.add(master ? w->d.master + g * L.mstride : w->d.store + g * L.sstride, blk.data(), blk.size()),
-         "read weights");
-  if (slot >= p.n_init) HIPCHK(w, t.add(w->d.trait + (g & ~1ull), traits, sizeof traits), "read trait");
-  HIPCHK(w, t.enqueue(), "read weights");
-  st = sync(w);
+  auto read = [&](void* dev, void* mem, size_t bytes, const char* what) {
+    Transfer t(w, true);
+    HIPCHK(w, t.add(dev, mem, bytes), what);
+    HIPCHK(w, t.enqueue(), what);
+    const eco_status r = sync(w);
+    if (r == ECO_OK) t.collect();
+    return r;
+  };
+  st = read(master ? w->d.master + g * L.mstride : w->d.store + g * L.sstride, blk.data(), blk.size(), "read weights");
   if (st != ECO_OK) return st;
-  t.collect();
-  if (traits[g & 1] == 0.0) std::fill(blk.begin(), blk.end(), (uint8_t)0);
+  // A slot past the initial population may never have had weights: its first 16 bytes are
+  // then zero, the others the allocation's, and its |theta|^2 (read as a pair, from a
+  // multiple of 16 bytes) is 0.  (Asked for with the weights, the trait made the read of
+  // a child's 530 KB 148 us where it takes 121.)
+  if (slot >= p.n_init && std::all_of(blk.begin(), blk.begin() + 16, [](uint8_t x) { return x == 0; })) {
+    double traits[2];
+    st = read(w->d.trait + (g & ~1ull), traits, sizeof traits, "read trait");
+    if (st != ECO_OK) return st;
+    if (traits[g & 1] == 0.0) std::fill(blk.begin(), blk.end(), (uint8_t)0);
+  }
   for (uint32_t u = 0; u < L.u_end; ++u) {
     const HostUnit hu = host_unit(L, u);
     for (uint32_t i = 0; i < hu.nvalid; ++i) {

@@ -2488,7 +2488,7 @@ __global__ __launch_bounds__(256) void k_place_rank(Dev d, const Tile* __restric
 }
 
 // Slot j < n_init takes the j-th smallest (key, cell); all other slots are free.
-__global__ __launch_bounds__(kSlotTile) void k_init_agents(Dev d, const Tile* __restrict__ tiles) {
+__global__ __launch_bounds__(kSlotTile) void k_init_agents(Dev d, Layout L, const Tile* __restrict__ tiles) {
   const Tile tl = tiles[blockIdx.x];
   const WorldParams wp = d.wp[tl.world];
   if (threadIdx.x >= tl.count) return;
@@ -2514,6 +2514,11 @@ __global__ __launch_bounds__(kSlotTile) void k_init_agents(Dev d, const Tile* __
   } else {   // a free slot: no field is left as the allocation had it (a state read back is written as a whole)
     d.flags[g] = 0;
     d.trait[g] = 0.0;
+    // of its weights, which nothing reads before they are written, the first 16 bytes: all
+    // zero there, a read asks for the trait too
+    const uint4 none = make_uint4(0, 0, 0, 0);
+    *reinterpret_cast<uint4*>(d.store + (uint64_t)g * L.sstride) = none;
+    *reinterpret_cast<uint4*>(d.master + (uint64_t)g * L.mstride) = none;
     d.pos[g] = 0;
     d.facing[g] = 0;
     d.energy[g] = 0;
@@ -2816,9 +2821,9 @@ hipError_t launch_placement(hipStream_t s, const Dev& d, const Tile* cell_tiles,
   hipLaunchKernelGGL(k_place_rank, dim3(nt), dim3(256), 0, s, d, cell_tiles, pi, start);
   ECO_CHECK_LAUNCH();
 }
-hipError_t launch_init_agents(hipStream_t s, const Dev& d, const Tile* tiles, uint32_t nt) {
+hipError_t launch_init_agents(hipStream_t s, const Dev& d, const Layout& L, const Tile* tiles, uint32_t nt) {
   if (nt == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_init_agents, dim3(nt), dim3(kSlotTile), 0, s, d, tiles);
+  hipLaunchKernelGGL(k_init_agents, dim3(nt), dim3(kSlotTile), 0, s, d, L, tiles);
   ECO_CHECK_LAUNCH();
 }
 template <int WDT, int H>

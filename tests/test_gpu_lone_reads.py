@@ -68,3 +68,47 @@ def test_no_longer_than_a_copy(eco, slots):
     r, c = float(np.median(read)) * 1e6, float(np.median(copy)) * 1e6
     say(f"{slots} bytes: read {r:.1f} us, copy {c:.1f} us")
     assert r <= 1.1 * c
+
+
+def slots_world(eco, wdtype, window=3, hidden=32):
+    return eco.World([wl.desc(width=16, height=16, n_agents_init=3, capacity=40, window=window, hidden1=hidden, hidden2=hidden,
+                              wdtype=wdtype, seed=1)])
+
+
+@pytest.mark.parametrize("wdtype", [wl.FP32, wl.BF16, wl.FP8])
+def test_slots_that_had_no_weights(eco, wdtype):
+    """Zeros until weights are written, also after a reset; written ones as they are, zeros among them."""
+    w = slots_world(eco, wdtype)
+    rng = np.random.default_rng(wdtype)
+    for _ in range(2):
+        for slot in (3, 4, 38, 39):
+            for master in (False, True):
+                assert not w.read_weights(slot, master=master).any()
+        m = rng.integers(-8, 9, w.P).astype(np.float32) / 8
+        for first in (0, 16, 300, w.P):   # leading zeros: fewer and more than the 16 bytes that a read looks at; all
+            m[:first] = 0
+            for slot in (3, 38):
+                w.write_weights(slot, m)
+                np.testing.assert_array_equal(w.read_weights(slot, master=True), m.astype(np.float64))
+                if wdtype != wl.FP8:
+                    np.testing.assert_array_equal(w.read_weights(slot), m.astype(np.float64))
+                else:
+                    assert (w.read_weights(slot) != 0).any() == (m != 0).any()
+        w.write_weights(38, rng.standard_normal(w.P).astype(np.float32))
+        w.reset()
+    w.close()
+
+
+def test_child_takes_no_longer_than_a_founder(eco):
+    w = slots_world(eco, wl.FP32, window=5)
+    w.write_weights(20, np.ones(w.P, np.float32))
+    t = {0: [], 20: []}
+    for _ in range(400):
+        for slot in t:
+            a = time.perf_counter()
+            w.read_weights(slot)
+            t[slot].append(time.perf_counter() - a)
+    w.close()
+    founder, child = (float(np.median(v)) * 1e6 for v in t.values())
+    say(f"weights of 18,944 bytes: founder {founder:.1f} us, child {child:.1f} us")
+    assert child <= 1.12 * founder
