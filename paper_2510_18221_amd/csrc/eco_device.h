@@ -332,11 +332,6 @@ __device__ __forceinline__ void gauss4k(uint32_t key0, uint32_t key1, uint32_t a
   }
 }
 
-__device__ __forceinline__ void gauss4(const WorldParams& w, uint32_t a, uint32_t step, uint32_t stream,
-                                       uint32_t blk, const double2* __restrict__ tab, double z[4]) {
-  gauss4k(w.key0, w.key1, a, step, stream, blk, tab, z);
-}
-
 // The tables into LDS (all threads of the block take part).
 __device__ __forceinline__ void load_trig(const double2* __restrict__ src, double2* dst) {
   for (int i = threadIdx.x; i < kNoiseTable; i += blockDim.x) dst[i] = src[i];

@@ -434,9 +434,10 @@ __device__ void settle_record(const Dev& d, const TileScratch& ts, uint32_t w, u
   }
   const uint32_t lgp = child_split(ts, H, total), slot_off = d.wp[w].slot_off, n = v.n0 + nb;
   const bool shares = small || lgp > 0;
-  // In one pass, with deviations from a value near the mean, the survivors' mean (or
-  // without any the first child's trait): with e = t - c, mean = c + sum e / n, and the
-  // squared deviations about it are sum e^2 less n (mean - c)^2, small next to it.  Several
+  // In one pass, with deviations from the survivors' mean: with e = t - c, mean = c +
+  // sum e / n, and the squared deviations about it are sum e^2 less n (mean - c)^2.  Every
+  // child has a surviving parent of its own, so n0 >= nb, and that is (sum e)^2 / n <=
+  // sum e^2 nb / n, at most half of what it is taken from.  Several
   // children a thread at once, the next ones' slots loaded with their traits, so that the
   // dependent loads overlap (a block for 6,600 children: two passes 17 us, now 13).
   constexpr int U = NT > 256 ? 2 : 8;
@@ -448,11 +449,10 @@ __device__ void settle_record(const Dev& d, const TileScratch& ts, uint32_t w, u
       slot[i] = (k < nb && slots) ? slot_off + (uint32_t)d.freel[slot_off + k] : 0u;
     }
   };
+  const double c = v.mean;
   double s = 0.0, q = 0.0;
   uint32_t slot[U];
   load_slots(threadIdx.x, slot);
-  const double c = v.n0 ? v.mean
-                        : child_trait(d, ts, lgp, shares, before, slots ? slot_off + (uint32_t)d.freel[slot_off] : 0u);
   for (uint32_t k = threadIdx.x; k < nb; k += U * NT) {
     double t[U];
     uint32_t next[U];
