@@ -3,11 +3,11 @@
 // Data layout in HBM (all worlds of one object concatenated):
 //   per slot (SoA, global slot = world.slot_off + local slot):
 //     pos i32, energy i32, age i32, tgt i32 (move / birth target cell),
-//     facing u8, flags u8 (bit0 alive, bit1 birth claim made, bit2 birth won),
+//     facing u8, flags u8 (1 alive, 0 free),
 //     act u8 (action applied), sampled u8 (policy's choice), act_in u8 (injected),
 //     uid u64, puid u64, trait f64 (|theta_master|^2)
 //   per cell (global cell = world.cell_off + y*W + x):
-//     occ i32 (local slot or -1), claim u32 (lowest claiming global slot), res u8, wall u8,
+//     occ i32 (local slot or -1), claim u32 (lowest global slot that moves here), res u8, wall u8,
 //     sense u8 (the cell's window channels at step start, built before the policy kernel)
 //   weights: storage[slot][storage_stride bytes] in the blocked layout below,
 //            master[slot][master_stride bytes] FP32 (BF16/FP8 only; FP32 storage is the master)
@@ -133,8 +133,8 @@ struct Dev {
   int32_t* occ;
   uint32_t* claim;
   uint32_t* mark;               // [total_cells] step + 1 of the last attack that struck the cell (the
-                                // ecology: strikes on the cell this step, cleared by the regrowth
-                                // tiles), or null when no world of the object has attacks
+                                // ecology: strikes on the cell this step, cleared by the cell
+                                // pass), or null when no world of the object has attacks
   uint8_t *res, *wall;
   uint8_t* sense;               // [total_cells] bit0 agent, bit1 resource, bit2 wall, bits3..5 energy bin
   uint32_t* rgb;                // [total_cells] window words, colour vision: R | G << 8 | B << 16, ecology:
@@ -184,7 +184,7 @@ struct Segments {
 };
 
 // Per-tile scratch of the multi-block passes (slot tiles of 256 slots, cell
-// tiles of 1024 cells; a world's tiles are contiguous: tile_rng[4w..4w+3] =
+// tiles of cell_tile cells; a world's tiles are contiguous: tile_rng[4w..4w+3] =
 // first/last slot tile, first/last cell tile).
 struct TileScratch {
   const Tile* slot_tiles;

@@ -509,12 +509,16 @@ hipError_t launch_group(eco_world* w, hipStream_t s, const Dev& d, const TileScr
 // An object of one small world steps with the policy kernel, one single-block launch
 // (k_step_small) and the birth launch, unless ECO_RT_SPLIT_STEP asks for the separate
 // kernels: its step is bound by the latency of its launches, and one block spares one of
-// them; the line lies where the block's threads take one group of four cells each, since
-// a second pass keeps it longer than the launch it spares.
-// Measured, one block / separate kernels, us per step: single resource without births 64^2
-// 16.7 / 19.1, 80^2 17.7 / 18.8, with three births a step 64^2 21.2 / 20.8, 80^2 22.8 / 21.1,
-// 96^2 23.8 / 21.3; the ecology 48^2 21.4 / 22.4, 64^2 21.9 / 22.8, 80^2 23.8 / 23.0 (with
-// terrain and colours 48^2 24.2 / 25.3, 64^2 25.4 / 25.1, 80^2 28.5 / 25.5).
+// them.  The line lies at one group of four cells for each of the block's threads (a second
+// pass keeps it longer than the launch it spares: 80^2 cells 22.8 / 21.1 us) and, with
+// 8,192 slots, at two of four slots; it is one line for every kind of world, and near it
+// some are faster without the block.
+// Measured, one block / separate kernels, us per step, 48^2 and 64^2 cells with one agent per
+// sixteen: single resource 16.6 / 18.8 and 16.8 / 18.6, with one birth a step 20.2 / 20.5
+// and 20.4 / 20.3, with ten 21.1 / 21.2 and 21.0 / 21.2; the ecology 20.8 / 21.8 and 21.8 /
+// 22.1, with terrain and colours 22.4 / 23.2 and 24.2 / 23.6, and with attacks and 64-wide
+// layers 23.8 / 24.2 and 25.7 / 24.9.  More agents than the block has threads: 64^2 with
+// 1,365 21.6 / 20.1.
 bool small_step(const eco_world* w) {
   return w->n_worlds == 1 && w->total_slots <= ECO_SMALL_STEP_MAX_SLOTS &&
          w->total_cells <= ECO_SMALL_STEP_MAX_CELLS && !(w->rt_flags & ECO_RT_SPLIT_STEP);
@@ -525,7 +529,7 @@ bool small_step(const eco_world* w) {
 // array's for eco_world_step_static).
 eco_status enqueue_step(eco_world* w, hipStream_t s, const Dev& d, const TileScratch& ts, bool timed) {
   if (d.keep_logits) HIPCHK(w, launch_prestep_fill(s, d), "prestep fill");
-  if (small_step(w)) {   // the policy kernel, then the rest of the step in one launch (timed as MOVE)
+  if (small_step(w)) {   // the policy kernel, then the rest of the step in two launches (timed together as MOVE)
     for (int k : {ECO_K_FORWARD, ECO_K_MOVE}) {
       hipEvent_t a = nullptr, b = nullptr;
       if (timed) {
@@ -1000,10 +1004,15 @@ eco_status eco_world_create(const eco_world_desc* descs, uint32_t n_worlds, void
   //  - Others: 8, 4, 8 (blocks past the resident ones even out the ends): 16,345 FP8
   //    agents of 37 KB 115.1 / 117.4, 8,500 BF16 agents of 72 KB 109.0 / 111.7, 60,000 FP32
   //    agents of 71 KB 629.7 / 633.9.
-  //  - From 4.5 GB of weights: 8, 1, 4, which keeps fewer streams open on each memory
-  //    channel.  Against 8, 4, 8: 65,536 BF16 agents (4.7 GB) 727 / 736, in FP32 (9.5 GB)
-  //    1,366 / 1,374; 100,000 of 69 KB with 4, 2, 4 1,001 / 1,011, but 60,000 of 71 KB (4.2
-  //    GB) 633.5 / 629.7 and 65,536 in FP8 (2.3 GB) 390.7 / 382.6.
+  //  - From 4.5 GB of weights: 8, 1, 4, by measurement only: against 8, 4, 8 65,536 BF16
+  //    agents (4.7 GB) 711 / 718.5, in FP32 (9.5 GB) 1,368.6 / 1,378, 32,768 BF16 agents of
+  //    268 KB (8.8 GB) 1,271 / 1,280; below it the other way, 60,000 of 71 KB (4.2 GB)
+  //    633.5 / 629.7 and 65,536 in FP8 (2.3 GB) 390.7 / 382.6.
+  // The population at creation decides, and a graph keeps its launch: a world that has lost
+  // most of its agents, or is given them by a written state, is stepped with the shape of
+  // its first day.  What that costs against 4, 4, 8: 65,536 FP32 agents down to 4,000 109.7
+  // / 107.6, to 500 39.1 / 32.1 (fewer loads in flight for each of them); 16,345 FP8 agents
+  // down to 4,000 44.7 / 40.9 (8, 4, 8).  The tuner or eco_world_set_launch sets another.
   uint64_t n_init = 0;
   for (uint32_t i = 0; i < n_worlds; ++i) n_init += descs[i].n_agents_init;
   if (const uint64_t bytes = weight_bytes(w->L); n_init >= 32ull * (uint64_t)w->n_cus) {
