@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "eco_device.h"
@@ -344,8 +345,8 @@ eco_status sync(eco_world* w) {
 // Allocating a buffer takes 15 - 60 us at 1 MiB and 330 at 2 MiB.
 constexpr size_t kHostBytes = size_t(1) << 20, kSegmentBytes = size_t(256) << 10, kLoneBytes = size_t(16) << 10;
 
-HostPool& host_pool() {   // (never destroyed: a buffer may outlive main's objects)
-  static HostPool* pool = new HostPool(
+HostPool& host_pool() {
+  static HostPool pool(
       kHostBytes,
       [](size_t n) -> void* {
         void* p = nullptr;
@@ -354,7 +355,8 @@ HostPool& host_pool() {   // (never destroyed: a buffer may outlive main's objec
         return nullptr;
       },
       [](void* p) { (void)hipHostFree(p); });
-  return *pool;
+  static_assert(std::is_trivially_destructible_v<HostPool>, "an object may outlive main");
+  return pool;
 }
 
 // The object's loan of a buffer for one transfer: given back at the end of the scope, by
@@ -1101,7 +1103,8 @@ eco_status eco_world_step(eco_world* w, uint32_t n_steps) {
     return drain_events(w);
   }
   if (graph) {
-    // (on a stream under capture a graph's replay is refused, and so are its launches)
+    // (On a stream under capture a replayed graph runs at once and is no part of the capture,
+    // where launches would be recorded instead of run: there all steps stay graphs.)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (n_steps % kGraphSteps && hipStreamIsCapturing(w->stream, &cap) != hipSuccess) {
       (void)hipGetLastError();
